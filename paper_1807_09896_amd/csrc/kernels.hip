@@ -1234,16 +1234,107 @@ __global__ void k_import(int64_t nf, float4 *pos4, float4 *vel4, float4 *frc4,
   frc4[s] = make_float4(frc[3 * g], frc[3 * g + 1], frc[3 * g + 2], 0.f);
 }
 
-__global__ void k_profile(const KGeom G, int64_t nf, const float4 *__restrict__ pos4,
-                          const float4 *__restrict__ vel4, int axis, int nbins, double *out) {
+__device__ __forceinline__ int profile_bin(const KGeom &G, const float4 x, int axis, int nbins) {
+  const float c = axis == 0 ? x.x : (axis == 1 ? x.y : x.z);
+  const int b = (int)floorf(c / G.L[axis] * (float)nbins);
+  return b < 0 ? 0 : (b >= nbins ? nbins - 1 : b);
+}
+
+// Binned observables, each block into bins of its own in LDS first.  Global
+// FP64 atomics of every particle serialise on a few hundred addresses: 5 per
+// particle took 1.41 ms for 330k particles in 80 bins and 7.5 ms for 777k in
+// 40, where reading them takes 0.01 ms.  A lane sums the particles it visits
+// in registers while they fall in one bin (cell order makes that the rule along
+// z) and adds the sums to the LDS bin when the bin changes; a wavefront
+// whose lanes all hold one bin reduces first and adds once.  At most 256 blocks
+// add their bins to the result, so an address sees 256 global atomics at most.
+constexpr int kProfThreads = 1024;
+constexpr int kProfBlocks = 256;
+constexpr int kProfBins = 1024;   // 40 KB of LDS
+
+__global__ __launch_bounds__(kProfThreads) void k_profile(const KGeom G, int64_t nf, int64_t per,
+                                                          const float4 *__restrict__ pos4,
+                                                          const float4 *__restrict__ vel4, int axis,
+                                                          int nbins, double *out) {
+  __shared__ double bins[5 * kProfBins];
+  for (int q = (int)threadIdx.x; q < 5 * nbins; q += kProfThreads) bins[q] = 0.0;
+  __syncthreads();
+  const int64_t first = (int64_t)blockIdx.x * per, last = min(nf, first + per);
+  int cur = 0, n = 0;
+  double sx = 0.0, sy = 0.0, sz = 0.0, sq = 0.0;
+  auto add = [&]() {
+    double *o = bins + 5 * cur;
+    atomicAdd(o, (double)n);
+    atomicAdd(o + 1, sx);
+    atomicAdd(o + 2, sy);
+    atomicAdd(o + 3, sz);
+    atomicAdd(o + 4, sq);
+  };
+  auto clear = [&]() {
+    n = 0;
+    sx = sy = sz = sq = 0.0;
+  };
+  // sums into their bins, of every lane where all hold one bin, else of the
+  // lanes that need it; called by whole wavefronts
+  auto flush = [&](bool need) {
+    const unsigned long long held = __ballot(n > 0);
+    if (held == 0ull) return;
+    const int b0 = __shfl(cur, __ffsll((long long)held) - 1, 64);
+    if (wave_any(n > 0 && cur != b0)) {
+      if (need && n > 0) {
+        add();
+        clear();
+      }
+      return;
+    }
+    for (int m = 32; m > 0; m >>= 1) {
+      n += __shfl_xor(n, m, 64);
+      sx += __shfl_xor(sx, m, 64);
+      sy += __shfl_xor(sy, m, 64);
+      sz += __shfl_xor(sz, m, 64);
+      sq += __shfl_xor(sq, m, 64);
+    }
+    cur = b0;
+    if (__lane_id() == 0) add();
+    clear();
+  };
+  for (int64_t base = first; base < last; base += kProfThreads) {
+    const int64_t s = base + threadIdx.x;
+    const bool act = s < last;
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f), v = x;
+    if (act) {
+      x = pos4[s];
+      v = vel4[s];
+    }
+    const int b = act ? profile_bin(G, x, axis, nbins) : cur;
+    const bool need = n > 0 && b != cur;
+    if (wave_any(need)) flush(need);
+    if (act) {
+      cur = b;
+      ++n;
+      sx += (double)v.x;
+      sy += (double)v.y;
+      sz += (double)v.z;
+      sq += (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z;
+    }
+  }
+  flush(true);
+  __syncthreads();
+  for (int b = (int)threadIdx.x; b < nbins; b += kProfThreads) {
+    if (bins[5 * b] == 0.0) continue;
+    for (int q = 0; q < 5; ++q) atomicAdd(out + 5 * (size_t)b + q, bins[5 * b + q]);
+  }
+}
+
+// More bins than LDS holds: global atomics per particle (the addresses are
+// many then).
+__global__ void k_profile_direct(const KGeom G, int64_t nf, const float4 *__restrict__ pos4,
+                                 const float4 *__restrict__ vel4, int axis, int nbins,
+                                 double *out) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= nf) return;
-  const float4 x = pos4[s];
   const float4 v = vel4[s];
-  const float c = axis == 0 ? x.x : (axis == 1 ? x.y : x.z);
-  int b = (int)floorf(c / G.L[axis] * (float)nbins);
-  b = b < 0 ? 0 : (b >= nbins ? nbins - 1 : b);
-  double *o = out + 5 * (size_t)b;
+  double *o = out + 5 * (size_t)profile_bin(G, pos4[s], axis, nbins);
   atomicAdd(o, 1.0);
   atomicAdd(o + 1, (double)v.x);
   atomicAdd(o + 2, (double)v.y);
@@ -1717,7 +1808,13 @@ hipError_t launch_import(hipStream_t s, int64_t nf, float4 *pos4, float4 *vel4, 
 hipError_t launch_profile(hipStream_t s, const KGeom &G, int64_t nf, const float4 *pos4,
                           const float4 *vel4, int axis, int nbins, double *out) {
   if (nf <= 0) return hipSuccess;
-  k_profile<<<grid_for(nf), kBlock, 0, s>>>(G, nf, pos4, vel4, axis, nbins, out);
+  if (nbins > kProfBins) {
+    k_profile_direct<<<grid_for(nf), kBlock, 0, s>>>(G, nf, pos4, vel4, axis, nbins, out);
+    return hipGetLastError();
+  }
+  const int64_t nb = std::min<int64_t>(kProfBlocks, (nf + kProfThreads - 1) / kProfThreads);
+  const int64_t per = (nf + nb - 1) / nb;
+  k_profile<<<(unsigned)nb, kProfThreads, 0, s>>>(G, nf, per, pos4, vel4, axis, nbins, out);
   return hipGetLastError();
 }
 
