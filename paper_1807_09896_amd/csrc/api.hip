@@ -97,6 +97,7 @@ struct dpd_ctx {
 
   Box *boxes = nullptr;
   int ppt = 2, fblock = 256;            // launch shapes (autotuned)
+  bool wide = false;      // pair forces with 16 lanes per particle (use_wide)
   Tile *itiles = nullptr, *ftiles = nullptr;
   int n_itiles = 0, n_ftiles = 0;
   int itiles_cap = 0, ftiles_cap = 0;
@@ -398,6 +399,16 @@ int build_persistent(dpd_ctx *c);
 // -> 0.073 ms), and small contexts need the blocks that 2 gives them.
 int wide_ppt(const dpd_ctx *c) { return !c->reflect && c->NF >= ((int64_t)1 << 20) ? 4 : 2; }
 
+// Pair forces with 16 lanes per particle (k_force_wide) up to this many fluid
+// particles in the context.  It spends about 0.43 ns per particle where the
+// one-lane kernel spends 0.14 to 0.17, but the latter takes 27 (density 3) to 33
+// us (density 4) however few there are.  Measured (graph-replayed step, us, 16
+// lanes against one): 31 / 50 at 2,000 particles, 40 / 57 at 16,000, 46 / 57
+// at 29,000, 54 / 58 at 56,000 (density 4: 65 / 69 at 75,000), and 68 / 62 at
+// 97,000 (86 / 74 at 129,000).  The bits are the same either way.
+constexpr int64_t kWideMax = 65536;
+bool use_wide(const dpd_ctx *c) { return c->NF <= kWideMax; }
+
 // Launch shapes: particles per thread of integrate (1, 2 or 4; at most 2
 // under the persistent step, whose kernel holds every phase at six
 // wavefronts per SIMD) and the pair kernel's work-group size.
@@ -408,7 +419,9 @@ int set_shapes(dpd_ctx *c, int ppt, int fblock) {
   drop_graphs(c);
   int rc = build_tiles(c, 256 * ppt, &c->itiles, &c->n_itiles, &c->itiles_cap);
   if (!rc) rc = build_tiles(c, fblock, &c->ftiles, &c->n_ftiles, &c->ftiles_cap);
-  if (!rc) rc = build_tiles(c, fblock, &c->otiles, &c->n_otiles, &c->otiles_cap, true, true);
+  if (!rc)
+    rc = build_tiles(c, c->wide ? dpd::wide_parts() : fblock, &c->otiles, &c->n_otiles,
+                     &c->otiles_cap, true, true);
   if (!rc && c->persistent) rc = build_persistent(c);
   return rc;
 }
@@ -646,7 +659,8 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
             return dpd::launch_sort_cells(s, c->NCELL, c->cstart, c->idx, key4, c->fluid_off,
                                           c->idx_all);
           }));
-  if (codes)
+  // the pair kernel with 16 lanes per particle reads no codes
+  if (codes && !c->wide)
     HIP_TRY(c, timed(c, s, K_CODES, [&] {
               return dpd::launch_quant_runs(s, c->NF + c->NW, c->idx_all, c->pos[c->cur], c->cq);
             }));
@@ -658,6 +672,11 @@ int force_pass(dpd_ctx *c, hipStream_t s, int init) {
   const int a = c->cur, b = 1 - c->cur;
   if (c->n_otiles > 0)
     HIP_TRY(c, timed(c, s, K_FORCE, [&] {
+              if (c->wide)
+                return dpd::launch_force_wide(s, c->boxes, c->otiles, c->n_otiles, c->NF, init,
+                                              c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
+                                              c->idx_all, c->start_all, c->pos[b], c->vel[b],
+                                              c->frc[b], c->dk, c->status, c->sph ? 1 : 0);
               return dpd::launch_force(s, c->fblock, c->boxes, c->otiles, c->n_otiles, c->NF,
                                        (int32_t)(c->NF + c->NW), (int32_t)c->NCELL, init,
                                        c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
@@ -1246,6 +1265,7 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
     if (rc) return bail(rc);
   }
   rc = build_bricks(c);
+  c->wide = use_wide(c);
   if (!rc) rc = set_shapes(c, wide_ppt(c), 256);
   if (rc) return bail(rc);
   c->cur = 0;

@@ -169,6 +169,16 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
                         float4 *pos_out, float4 *vel_out, float4 *frc_out,
                         const unsigned long long *dk, Status *st, int sph);
 
+// The same pair forces with 16 lanes per particle, for small contexts, over
+// tiles of up to wide_parts() fluid slots.  It reads no coarse codes.
+int wide_parts();
+hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,
+                             int64_t NF, int init, const float4 *pos4, const float4 *vt4,
+                             const float4 *vel4, const float4 *frc4, const int32_t *idx,
+                             const int32_t *idx_all, const int32_t *start_all, float4 *pos_out,
+                             float4 *vel_out, float4 *frc_out, const unsigned long long *dk,
+                             Status *st, int sph);
+
 // The same pair forces, body force and velocity update for the boxes cut
 // into bricks: one block per brick stages the brick's cells and a one-cell
 // halo in LDS (force_brick.hip).  cstart: fluid slot start of each cell;

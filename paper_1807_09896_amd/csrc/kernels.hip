@@ -336,6 +336,19 @@ __global__ void k_scatter(int64_t n, const int32_t *__restrict__ cell_of,
   scatter_one(p, n, cell_of, rank_of, start, idx, nw, wcell, wstart, start_all, idx_all);
 }
 
+// Insertion network of compare-exchanges over K registers.
+template <int K>
+__device__ __forceinline__ void sort_network(uint32_t (&v)[K]) {
+#pragma unroll
+  for (int i = 1; i < K; ++i)
+#pragma unroll
+    for (int j = i; j > 0; --j) {
+      const uint32_t lo = min(v[j - 1], v[j]), hi = max(v[j - 1], v[j]);
+      v[j - 1] = lo;
+      v[j] = hi;
+    }
+}
+
 // A cell's run of up to K storage indices (the common case: about four per
 // cell at density 4), loaded into registers with independent loads and sorted by a
 // fixed insertion network of compare-exchanges, the slots past the run padded
@@ -346,20 +359,38 @@ __device__ __forceinline__ void sort_run_regs(int32_t *__restrict__ idx, int a, 
   uint32_t v[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) v[i] = i < n ? (uint32_t)idx[a + i] : 0xffffffffu;
-#pragma unroll
-  for (int i = 1; i < K; ++i)
-#pragma unroll
-    for (int j = i; j > 0; --j) {
-      const uint32_t lo = min(v[j - 1], v[j]), hi = max(v[j - 1], v[j]);
-      v[j - 1] = lo;
-      v[j] = hi;
-    }
+  sort_network<K>(v);
 #pragma unroll
   for (int i = 0; i < K; ++i)
     if (i < n) {
       idx[a + i] = (int32_t)v[i];
       if (out) out[i] = (int32_t)v[i];
     }
+}
+
+// A cell's run idx[a .. b) sorted by storage index and, if out, copied to out:
+// in registers up to 16, by an insertion sort in memory above.
+__device__ __forceinline__ void sort_run(int32_t *__restrict__ idx, int a, int b,
+                                         int32_t *__restrict__ out) {
+  if (b - a <= 4) {
+    sort_run_regs<4>(idx, a, b - a, out);
+  } else if (b - a <= 8) {
+    sort_run_regs<8>(idx, a, b - a, out);
+  } else if (b - a <= 16) {
+    sort_run_regs<16>(idx, a, b - a, out);
+  } else {
+    for (int i = a + 1; i < b; ++i) {
+      const int v = idx[i];
+      int j = i - 1;
+      while (j >= a && idx[j] > v) {
+        idx[j + 1] = idx[j];
+        --j;
+      }
+      idx[j + 1] = v;
+    }
+    if (out)
+      for (int i = a; i < b; ++i) out[i - a] = idx[i];
+  }
 }
 
 // Atomic ranks arrive in any order: sort each cell's run by storage index so
@@ -377,21 +408,15 @@ __device__ __forceinline__ void sort_cell(int64_t c, const int32_t *__restrict__
                                           const int32_t *__restrict__ fluid_off,
                                           int32_t *__restrict__ idx_all) {
   const int a = start[c], b = start[c + 1];
-  if (!BY_GID && b - a <= 16) {
-    int32_t *out = idx_all ? idx_all + fluid_off[c] : nullptr;
-    if (b - a <= 4)
-      sort_run_regs<4>(idx, a, b - a, out);
-    else if (b - a <= 8)
-      sort_run_regs<8>(idx, a, b - a, out);
-    else
-      sort_run_regs<16>(idx, a, b - a, out);
+  if (!BY_GID) {
+    sort_run(idx, a, b, idx_all ? idx_all + fluid_off[c] : nullptr);
     return;
   }
   for (int i = a + 1; i < b; ++i) {
     const int v = idx[i];
-    const uint32_t kv = BY_GID ? __float_as_uint(key4[v].w) : (uint32_t)v;
+    const uint32_t kv = __float_as_uint(key4[v].w);
     int j = i - 1;
-    while (j >= a && (BY_GID ? __float_as_uint(key4[idx[j]].w) : (uint32_t)idx[j]) > kv) {
+    while (j >= a && __float_as_uint(key4[idx[j]].w) > kv) {
       idx[j + 1] = idx[j];
       --j;
     }
@@ -886,30 +911,72 @@ struct Acc {
   float x, y, z;
 };
 
+// One pair's force on i: mag along the unit vector (ex, ey, ez).
+struct PairTerm {
+  float mag, ex, ey, ez;
+};
+
 // SPH: compiled with the conservative force of Eq. 22-24 for boxes that use
-// it (wall: j is a wall particle, selecting the fluid-wall strengths).
+// it (wall: j is a wall particle, selecting the fluid-wall strengths).  Each
+// operation is written out (fused where it says so), so that every kernel that
+// evaluates a pair gets the same bits.
 template <bool SPH>
-__device__ __forceinline__ void add_pair(Acc &acc, float dx, float dy, float dz, float r2,
-                                         float dvx, float dvy, float dvz, float a, bool wall,
-                                         const KParams &P, uint32_t gi, uint32_t gj,
-                                         uint32_t klo, uint32_t khi) {
+__device__ __forceinline__ PairTerm pair_term(float dx, float dy, float dz, float r2, float dvx,
+                                              float dvy, float dvz, bool wall, const KParams &P,
+                                              uint32_t gi, uint32_t gj, uint32_t klo,
+                                              uint32_t khi) {
+#pragma clang fp contract(off)
   const float rinv = rsqrtf(r2);
   const float r = r2 * rinv;
-  const float w = fmaxf(1.0f - r * P.inv_rc, 0.0f);
-  const float ex = dx * rinv, ey = dy * rinv, ez = dz * rinv;
-  const float edv = ex * dvx + ey * dvy + ez * dvz;
+  const float w = fmaxf(__builtin_fmaf(-r, P.inv_rc, 1.0f), 0.0f);
+  PairTerm t;
+  t.ex = dx * rinv;
+  t.ey = dy * rinv;
+  t.ez = dz * rinv;
+  const float edv = __builtin_fmaf(t.ez, dvz, __builtin_fmaf(t.ex, dvx, t.ey * dvy));
   const float xi = pair_gauss(gi, gj, klo, khi, P.key0, P.key1);
-  float mag;
+  const float gw = P.gamma * w;
   if (SPH && P.sph) {
     const float cr = wall ? P.cr_fw : P.cr_ff, ca = wall ? P.ca_fw : P.ca_ff;
-    const float fc = ca * spline_dp(r * P.inv_ha) - cr * spline_dp(r * P.inv_hr);
-    mag = fc + w * (P.sigma_rdt * xi - P.gamma * w * edv);
+    const float fc = __builtin_fmaf(ca, spline_dp(r * P.inv_ha), -(cr * spline_dp(r * P.inv_hr)));
+    t.mag = __builtin_fmaf(w, __builtin_fmaf(P.sigma_rdt, xi, -(gw * edv)), fc);
   } else {
-    mag = w * (a - P.gamma * w * edv + P.sigma_rdt * xi);
+    const float a = wall ? P.a_fw : P.a_ff;
+    t.mag = w * __builtin_fmaf(P.sigma_rdt, xi, __builtin_fmaf(-edv, gw, a));
   }
-  acc.x += mag * ex;
-  acc.y += mag * ey;
-  acc.z += mag * ez;
+  return t;
+}
+
+// Velocity and carried force of particle i after its pair sum (acc) is
+// complete, written with its position to slot s of the next buffers.
+struct Finished {
+  float4 vel, frc;
+};
+
+template <bool INIT>
+__device__ __forceinline__ Finished finish_particle(const KParams &P, const Acc &acc, int i,
+                                                          const float4 &vti,
+                                                          const float4 *__restrict__ vel4,
+                                                          const float4 *__restrict__ frc4) {
+#pragma clang fp contract(off)
+  Finished r;
+  const float fx = acc.x + P.g[0], fy = acc.y + P.g[1], fz = acc.z + P.g[2];
+  r.frc = make_float4(fx, fy, fz, 0.f);
+  const float4 vo = load_stream(&vel4[i]);
+  if (INIT) {
+    r.vel = make_float4(vo.x, vo.y, vo.z, __int_as_float(0));
+    return r;
+  }
+  const int event = __float_as_int(vti.w);
+  if (event) {
+    r.vel = make_float4(vti.x, vti.y, vti.z, __int_as_float(event));
+  } else {
+    const float4 fo = load_stream(&frc4[i]);
+    r.vel = make_float4(__builtin_fmaf(P.hdt, fo.x + fx, vo.x),
+                        __builtin_fmaf(P.hdt, fo.y + fy, vo.y),
+                        __builtin_fmaf(P.hdt, fo.z + fz, vo.z), __int_as_float(0));
+  }
+  return r;
 }
 
 // Tile tid by one block of BS threads; list: kListCap x BS words of LDS.
@@ -973,15 +1040,17 @@ __device__ __forceinline__ void force_tile(
       const float dx = sep(pi.x, pj.x, G.L[0]);
       const float dy = sep(pi.y, pj.y, G.L[1]);
       const float dz = sep(pi.z, pj.z, G.L[2]);
-      const float r2 = dx * dx + dy * dy + dz * dz;
-      const bool wall = (int64_t)j >= NF;
-      const float a = wall ? P.a_fw : P.a_ff;
       // the pair decision (r2 > 0 also drops coincident particles, whose
       // force is 0)
-      const float r2d = pair_r2(dx, dy, dz);
-      if (r2d < P.rc2 && r2d > 0.0f)
-        add_pair<SPH>(acc, dx, dy, dz, r2, vti.x - vtj.x, vti.y - vtj.y, vti.z - vtj.z, a, wall,
-                      P, gi, __float_as_uint(pj.w), klo, khi);
+      const float r2 = pair_r2(dx, dy, dz);
+      if (r2 < P.rc2 && r2 > 0.0f) {
+        const PairTerm t = pair_term<SPH>(dx, dy, dz, r2, vti.x - vtj.x, vti.y - vtj.y,
+                                          vti.z - vtj.z, (int64_t)j >= NF, P, gi,
+                                          __float_as_uint(pj.w), klo, khi);
+        acc.x = __builtin_fmaf(t.ex, t.mag, acc.x);
+        acc.y = __builtin_fmaf(t.ey, t.mag, acc.y);
+        acc.z = __builtin_fmaf(t.ez, t.mag, acc.z);
+      }
       j = jn;
       pj = pjn;
       vtj = vtjn;
@@ -1061,25 +1130,12 @@ __device__ __forceinline__ void force_tile(
     }
   }
   flush();
-  const float fx = acc.x + P.g[0], fy = acc.y + P.g[1], fz = acc.z + P.g[2];
-  const float4 vo = load_stream(&vel4[i]);
-  float4 vn;
-  if (INIT) {
-    vn = make_float4(vo.x, vo.y, vo.z, __int_as_float(0));
-  } else {
-    const int event = __float_as_int(vti.w);
-    if (event) {
-      vn = make_float4(vti.x, vti.y, vti.z, __int_as_float(event));
-    } else {
-      const float4 fo = load_stream(&frc4[i]);
-      vn = make_float4(vo.x + P.hdt * (fo.x + fx), vo.y + P.hdt * (fo.y + fy),
-                       vo.z + P.hdt * (fo.z + fz), __int_as_float(0));
-    }
-  }
-  if (!(isfinite(fx) && isfinite(fy) && isfinite(fz))) atomicAdd(&st->nonfinite, 1ull);
+  const Finished fin = finish_particle<INIT>(P, acc, i, vti, vel4, frc4);
+  if (!(isfinite(fin.frc.x) && isfinite(fin.frc.y) && isfinite(fin.frc.z)))
+    atomicAdd(&st->nonfinite, 1ull);
   store_stream(&pos_out[s], pi);
-  store_stream(&vel_out[s], vn);
-  store_stream(&frc_out[s], make_float4(fx, fy, fz, 0.f));
+  store_stream(&vel_out[s], fin.vel);
+  store_stream(&frc_out[s], fin.frc);
 }
 
 // Six wavefronts per SIMD: at most 80 VGPRs, so the walk and the pair pass
@@ -1099,6 +1155,178 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_
   if (tid >= ntiles) return;
   force_tile<INIT, BS, SPH>(tid, list, boxes, tiles, NF, pad, ncell_all, pos4, vt4, vel4, frc4,
                             idx, idx_all, start_all, cq, pos_out, vel_out, frc_out, dk, st);
+}
+
+// ---------------------------------------------------------------------------
+// Pair force of small contexts: 16 lanes per particle.
+//
+// With one lane per particle a context of a few thousand particles fills a
+// few wavefronts, each walking nine neighbour rows in sequence: 27 us for 2,100
+// particles and 26 us for 16,000, whatever the arithmetic.  Here the candidates of a particle's
+// nine rows are numbered through (row by row, as the walk visits them) and
+// taken 16 lanes x 8 at a time, so their indices are one level of loads and
+// their positions another; the pairs found are listed in candidate order, the
+// 16 lanes evaluate 16 of them at a time, and three lanes add the terms up
+// in list order.  The terms and their order are those of force_tile, so the
+// results are too, bit for bit, and a box gives the same in a context of any size.
+// ---------------------------------------------------------------------------
+constexpr int kWideLanes = 16;
+constexpr int kWideParts = kBlock / kWideLanes;   // particles per block
+constexpr int kWideBatch = 8;                     // candidates per lane in flight
+constexpr int kWideRing = 256;                    // >= 8 x 16 + 15 listed pairs, a power of two
+
+// LDS written by some lanes of a wavefront, read by others of the same one.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The candidates of one particle, by the 16 lanes of its group: their nine
+// neighbour rows (two runs where a row wraps in x) numbered through.
+struct WideRows {
+  int total;        // candidates
+  int off[8];       // number of the first candidate of rows 1 .. 8
+  const int4 *row;  // LDS: {first candidate, run A's first entry, its length, run B's first entry}
+
+  __device__ __forceinline__ void init(const KGeom &G, int co, int cx, int cy, int cz, int g,
+                                       const int32_t *__restrict__ start_all, int4 *lds) {
+    int ta = 0, na = 0, tb = 0, nb = 0;
+    if (g < 9) {
+      const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
+      int qy = cy + g % 3 - 1, qz = cz + g / 3 - 1;
+      qy += qy < 0 ? ny : (qy >= ny ? -ny : 0);
+      qz += qz < 0 ? nz : (qz >= nz ? -nz : 0);
+      const int32_t *s = start_all + co + (qz * ny + qy) * nx;
+      const bool left = cx == 0, right = cx == nx - 1;
+      const int a0 = left ? nx - 1 : (right ? nx - 2 : cx - 1);
+      ta = s[a0];
+      na = s[a0 + (left ? 1 : (right ? 2 : 3))] - ta;
+      if (left || right) {
+        tb = s[0];
+        nb = s[left ? 2 : 1] - tb;
+      }
+    }
+    int incl = na + nb;
+#pragma unroll
+    for (int d = 1; d < kWideLanes; d <<= 1) {
+      const int v = __shfl_up(incl, d, kWideLanes);
+      if (g >= d) incl += v;
+    }
+    total = __shfl(incl, kWideLanes - 1, kWideLanes);
+    if (g < 9) lds[g] = make_int4(incl - na - nb, ta, na, tb);
+    wave_lds_sync();
+    row = lds;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) off[q] = lds[q + 1].x;
+  }
+
+  // run entry of candidate c, 0 <= c < total: in the last row that starts at
+  // or before c (rows without candidates start where the next one does)
+  __device__ __forceinline__ int entry(int c) const {
+    int r = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) r += c >= off[q] ? 1 : 0;
+    const int4 R = row[r];
+    const int u = c - R.x;
+    return u < R.z ? R.y + u : R.w + (u - R.z);
+  }
+};
+
+template <bool INIT, bool SPH>
+__global__ __launch_bounds__(kBlock) void k_force_wide(
+    const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles, int64_t NF,
+    const float4 *__restrict__ pos4, const float4 *__restrict__ vt4,
+    const float4 *__restrict__ vel4, const float4 *__restrict__ frc4,
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ idx_all,
+    const int32_t *__restrict__ start_all, float4 *__restrict__ pos_out,
+    float4 *__restrict__ vel_out, float4 *__restrict__ frc_out,
+    const unsigned long long *__restrict__ dk, Status *st) {
+  // padded so that the four groups of a wavefront use different banks
+  __shared__ int ring[kWideParts][kWideRing + 8];
+  __shared__ float4 term[kWideParts][kWideLanes + 1];
+  __shared__ int4 rows_lds[kWideParts][9];
+  const int tid = xcd_block();
+  if (tid >= ntiles) return;
+  const Tile tile = tiles[tid];
+  const int grp = (int)threadIdx.x / kWideLanes, g = (int)threadIdx.x % kWideLanes;
+  if (grp >= tile.count) return;   // whole groups
+  const Box &B = boxes[tile.box];
+  const KGeom G = B.G;
+  const KParams P = B.P;
+  const unsigned long long kk = *dk;
+  const uint32_t klo = (uint32_t)kk;
+  const uint32_t khi = ((uint32_t)(kk >> 32) & 0xFFFFu) | (P.replica << 16);
+  const int64_t s = (int64_t)tile.first + grp;
+  const int i = idx[s];
+  const float4 pi = pos4[i];
+  const float4 vti = vt4[i];
+  const uint32_t gi = __float_as_uint(pi.w);
+  int cx, cy, cz;
+  cell_index(G, pi.x, pi.y, pi.z, cx, cy, cz);
+  WideRows rows;
+  rows.init(G, (int)B.co, cx, cy, cz, g, start_all, rows_lds[grp]);
+  int *const list = ring[grp];
+  float4 *const terms = term[grp];
+  const int shift = ((int)__lane_id() / kWideLanes) * kWideLanes;   // the group's bits of a ballot
+  int listed = 0, done = 0;
+  float acc = 0.f;   // lanes 0, 1, 2: the sum of component x, y, z
+  // the next 16 listed pairs (the last call: fewer), one per lane, then their
+  // terms added up in list order
+  auto evaluate = [&]() {
+    const int e = done + g;
+    PairTerm t = {0.f, 0.f, 0.f, 0.f};
+    if (e < listed) {
+      const int j = list[e & (kWideRing - 1)];
+      const float4 pj = pos4[j], vtj = vt4[j];
+      const float dx = sep(pi.x, pj.x, G.L[0]), dy = sep(pi.y, pj.y, G.L[1]),
+                  dz = sep(pi.z, pj.z, G.L[2]);
+      t = pair_term<SPH>(dx, dy, dz, pair_r2(dx, dy, dz), vti.x - vtj.x, vti.y - vtj.y,
+                         vti.z - vtj.z, (int64_t)j >= NF, P, gi, __float_as_uint(pj.w), klo, khi);
+    }
+    terms[g] = make_float4(t.mag, t.ex, t.ey, t.ez);
+    wave_lds_sync();
+    if (g < 3) {
+      const float *m = (const float *)terms;
+#pragma unroll
+      for (int q = 0; q < kWideLanes; ++q) acc = __builtin_fmaf(m[4 * q + 1 + g], m[4 * q], acc);
+    }
+    wave_lds_sync();
+    done += kWideLanes;
+  };
+  for (int c0 = 0; c0 < rows.total; c0 += kWideBatch * kWideLanes) {
+    int j[kWideBatch];
+    float4 pj[kWideBatch];
+#pragma unroll
+    for (int k = 0; k < kWideBatch; ++k)
+      j[k] = idx_all[rows.entry(min(c0 + k * kWideLanes + g, rows.total - 1))];
+#pragma unroll
+    for (int k = 0; k < kWideBatch; ++k) pj[k] = pos4[j[k]];
+#pragma unroll
+    for (int k = 0; k < kWideBatch; ++k) {
+      const float r2 = pair_r2(sep(pi.x, pj[k].x, G.L[0]), sep(pi.y, pj[k].y, G.L[1]),
+                               sep(pi.z, pj[k].z, G.L[2]));
+      // the pair decision (r2 > 0 drops the particle itself and coincident
+      // ones, whose force is 0)
+      const bool hit = r2 < P.rc2 && r2 > 0.0f && c0 + k * kWideLanes + g < rows.total;
+      const uint32_t m = (uint32_t)(__ballot(hit) >> shift) & 0xFFFFu;
+      if (hit) list[(listed + __popc(m & ((1u << g) - 1u))) & (kWideRing - 1)] = j[k];
+      listed += __popc(m);
+    }
+    wave_lds_sync();
+    while (listed - done >= kWideLanes) evaluate();
+  }
+  if (done < listed) evaluate();
+  const Acc sum = {__shfl(acc, 0, kWideLanes), __shfl(acc, 1, kWideLanes),
+                   __shfl(acc, 2, kWideLanes)};
+  const Finished fin = finish_particle<INIT>(P, sum, i, vti, vel4, frc4);
+  if (g == 0) {
+    if (!(isfinite(fin.frc.x) && isfinite(fin.frc.y) && isfinite(fin.frc.z)))
+      atomicAdd(&st->nonfinite, 1ull);
+    pos_out[s] = pi;
+    vel_out[s] = fin.vel;
+    frc_out[s] = fin.frc;
+  }
 }
 
 // Interacting pairs with the same decision as the force kernel.  Each thread
@@ -1766,6 +1994,28 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
   }
 #undef DPD_FORCE_S
 #undef DPD_FORCE
+  return hipGetLastError();
+}
+
+int wide_parts() { return kWideParts; }
+
+hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,
+                             int64_t NF, int init, const float4 *pos4, const float4 *vt4,
+                             const float4 *vel4, const float4 *frc4, const int32_t *idx,
+                             const int32_t *idx_all, const int32_t *start_all, float4 *pos_out,
+                             float4 *vel_out, float4 *frc_out, const unsigned long long *dk,
+                             Status *st, int sph) {
+  if (ntiles <= 0) return hipSuccess;
+  const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
+#define DPD_WIDE(I, S)                                                                            \
+  k_force_wide<I, S><<<nb, kBlock, 0, s>>>(boxes, tiles, ntiles, NF, pos4, vt4, vel4, frc4, idx, \
+                                           idx_all, start_all, pos_out, vel_out, frc_out, dk, st)
+  if (init) {
+    if (sph) DPD_WIDE(true, true); else DPD_WIDE(true, false);
+  } else {
+    if (sph) DPD_WIDE(false, true); else DPD_WIDE(false, false);
+  }
+#undef DPD_WIDE
   return hipGetLastError();
 }
 
