@@ -233,7 +233,8 @@ int dpd_counters(dpd_ctx *ctx, int64_t *out);
  * and the number of timed launches in out_launches ("scatter" also writes
  * the wall part of the merged cell runs; "pair_codes" writes the coarse
  * position codes of the merged runs that the pair kernel's candidate
- * pre-test reads; "step_persistent" is the one launch of a step under
+ * pre-test reads, which small contexts do without; where every box is small,
+ * one launch named "sort_cells" builds the whole cell list; "step_persistent" is the one launch of a step under
  * dpd_use_persistent, which then replaces the six step kernels).
  * Synchronises. */
 #define DPD_NUM_KERNELS 9

@@ -54,6 +54,15 @@ hipError_t launch_sort_cells(hipStream_t s, int64_t ncell, const int32_t *start,
 // every sorted wall position to cell_out.
 hipError_t launch_sort_wall_cells(hipStream_t s, int64_t ncell, const int32_t *start,
                                   int32_t *idx, int32_t *cell_out);
+// The cell list of every box (scan, scatter and sort above, with the wall part
+// of the merged runs and the advance of dk) in one launch, one block per box;
+// each box has at most kBoxCells cells and kBoxFluid fluid particles.
+constexpr int kBoxCells = 14336, kBoxFluid = 18000;   // 63 KB of LDS
+hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int64_t NF,
+                            const int32_t *cell_of, const int32_t *rank_of, int32_t *count,
+                            const int32_t *wcstart, int32_t *cstart, int32_t *start_all,
+                            int32_t *fluid_off, int32_t *idx, int32_t *idx_all,
+                            const int32_t *wcell, unsigned long long *dk);
 // Coarse position codes of the merged runs, cq[t] from pos4[idx_all[t]] for
 // t < n (one word per entry), which the pair kernel's candidate pre-test
 // reads; n = NF + NW, after the scatter and sort.

@@ -450,6 +450,108 @@ __global__ void k_sort_wall_cells(int64_t ncell, const int32_t *__restrict__ sta
   for (int i = a; i < b; ++i) cell_out[i] = (int32_t)c;
 }
 
+// The whole cell list of small boxes in one launch, one block per box: the
+// exclusive scan of the box's cell counts, the scatter of its fluid and walls
+// and the per-cell sort, with the starts and the fluid's slots in LDS as 16-bit
+// numbers within the box.  The four separate launches (scan_reduce, scan_down,
+// scatter, sort_cells) take 4 to 5 us each, most of it the launch.  Every list
+// has one entry order (cells in order, each sorted by storage index), so the
+// result is theirs exactly.
+constexpr int kBoxThreads = 1024;
+
+__global__ __launch_bounds__(kBoxThreads) void k_cells_box(
+    const Box *__restrict__ boxes, int nbox, int64_t NF, const int32_t *__restrict__ cell_of,
+    const int32_t *__restrict__ rank_of, int32_t *__restrict__ count,
+    const int32_t *__restrict__ wcstart, int32_t *__restrict__ cstart,
+    int32_t *__restrict__ start_all, int32_t *__restrict__ fluid_off, int32_t *__restrict__ idx,
+    int32_t *__restrict__ idx_all, const int32_t *__restrict__ wcell,
+    unsigned long long *__restrict__ dk) {
+  __shared__ uint16_t start[kBoxCells + 1];
+  __shared__ uint16_t slot[kBoxFluid];
+  __shared__ int wave_total[kBoxThreads / 64];
+  const int t = (int)threadIdx.x;
+  const Box &B = boxes[blockIdx.x];
+  const int co = (int)B.co, nc = (int)B.ncell, fo = (int)B.fo, nf = (int)B.nf;
+  const int wo = (int)B.wo, nw = (int)B.nw;
+  if (dk && blockIdx.x == 0 && t == 0) *dk += 1ull;
+#pragma unroll 4
+  for (int c = t; c < nc; c += kBoxThreads) {
+    start[c] = (uint16_t)count[co + c];
+    count[co + c] = 0;
+  }
+  __syncthreads();
+  // each thread's run of cells (an odd number, against bank conflicts), after
+  // those of the threads before it
+  const int per = ((nc + kBoxThreads - 1) / kBoxThreads) | 1;
+  const int c0 = min(t * per, nc), c1 = min(c0 + per, nc);
+  int sum = 0;
+  for (int c = c0; c < c1; ++c) sum += start[c];
+  int incl = sum;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int v = __shfl_up(incl, d, 64);
+    if ((t & 63) >= d) incl += v;
+  }
+  if ((t & 63) == 63) wave_total[t >> 6] = incl;
+  __syncthreads();
+  int run = incl - sum;
+  for (int w = 0; w < (t >> 6); ++w) run += wave_total[w];
+  for (int c = c0; c < c1; ++c) {
+    const int n = start[c];
+    start[c] = (uint16_t)run;
+    run += n;
+  }
+  if (t == 0) start[nc] = (uint16_t)nf;
+  __syncthreads();
+#pragma unroll 4
+  for (int p = t; p < nf; p += kBoxThreads)
+    slot[start[cell_of[fo + p] - co] + rank_of[fo + p]] = (uint16_t)p;
+#pragma unroll 4
+  for (int w = wo + t; w < wo + nw; w += kBoxThreads) {
+    // entry start_all[c] + (w - wcstart[c]) of the merged runs
+    idx_all[fo + start[wcell[w] - co] + w] = (int)NF + w;
+  }
+  __syncthreads();
+#pragma unroll 2
+  for (int c = t; c < nc; c += kBoxThreads) {
+    const int a = start[c], n = start[c + 1] - a;
+    const int w0 = wcstart[co + c], w1 = wcstart[co + c + 1];
+    cstart[co + c] = fo + a;
+    start_all[co + c] = fo + a + w0;
+    fluid_off[co + c] = fo + a + w1;
+    int32_t *const out = idx + fo + a, *const all = idx_all + fo + a + w1;
+    if (n <= 8) {
+      uint32_t v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = i < n ? (uint32_t)slot[a + i] : 0xffffu;
+      sort_network<8>(v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (i < n) {
+          out[i] = fo + (int)v[i];
+          all[i] = fo + (int)v[i];
+        }
+    } else {
+      for (int i = a + 1; i < a + n; ++i) {
+        const uint16_t v = slot[i];
+        int j = i - 1;
+        while (j >= a && slot[j] > v) {
+          slot[j + 1] = slot[j];
+          --j;
+        }
+        slot[j + 1] = v;
+      }
+      for (int i = 0; i < n; ++i) {
+        out[i] = fo + slot[a + i];
+        all[i] = fo + slot[a + i];
+      }
+    }
+  }
+  if ((int)blockIdx.x == nbox - 1 && t == 0) {
+    cstart[co + nc] = fo + nf;
+    start_all[co + nc] = fo + nf + wcstart[co + nc];
+  }
+}
+
 // Coarse codes of the merged runs, cq[t] = qcode3(pos4[idx_all[t]]): one
 // thread per entry, so that the index reads and code writes coalesce.
 __global__ void k_quant_runs(int64_t n, const int32_t *__restrict__ idx_all,
@@ -2016,6 +2118,18 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
     if (sph) DPD_WIDE(false, true); else DPD_WIDE(false, false);
   }
 #undef DPD_WIDE
+  return hipGetLastError();
+}
+
+hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int64_t NF,
+                            const int32_t *cell_of, const int32_t *rank_of, int32_t *count,
+                            const int32_t *wcstart, int32_t *cstart, int32_t *start_all,
+                            int32_t *fluid_off, int32_t *idx, int32_t *idx_all,
+                            const int32_t *wcell, unsigned long long *dk) {
+  if (nbox <= 0) return hipSuccess;
+  k_cells_box<<<(unsigned)nbox, kBoxThreads, 0, s>>>(boxes, nbox, NF, cell_of, rank_of, count,
+                                                     wcstart, cstart, start_all, fluid_off, idx,
+                                                     idx_all, wcell, dk);
   return hipGetLastError();
 }
 

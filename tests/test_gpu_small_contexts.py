@@ -1,7 +1,8 @@
 """The kernels of small contexts against those of large ones, bit for bit.
 
 A context of at most 65,536 fluid particles takes its pair forces with 16 lanes
-per particle.  The same box beside a large one runs the kernels of large
+per particle, and one whose boxes all fit in a block's LDS builds its cell lists
+in one launch.  The same box beside a large one runs the kernels of large
 contexts, and every result has to be the same: state, forces, events, pairs.
 """
 import numpy as np
@@ -59,6 +60,12 @@ BOXES = {
     "slab": lambda: workloads.tiny_slab_system(seed=14),
     "sph": lambda: _sph(workloads.sinusoid_slit_system(L=(12.0, 8.0, 12.0), base=3.0, amp=1.0)),
     "couette": lambda: workloads.couette_system(L=(8.0, 6.0, 7.0), seed=15, specular=True),
+    # the largest box of the one-launch cell list, in particles and in cells,
+    # and one past each
+    "fluid_max": lambda: _edge_box((18, 18, 19), 18000),
+    "fluid_over": lambda: _edge_box((18, 18, 19), 18001),
+    "cells_max": lambda: _edge_box((32, 28, 16), 9000),
+    "cells_over": lambda: _edge_box((31, 31, 15), 9000),
 }
 
 
