@@ -10,7 +10,7 @@
 // flat instead of pointing along rounding noise).
 //
 // Data flow: a block owns a 64 x 16 column of nodes and marches it through a
-// chunk of 64 z planes.  phi planes (with a two-node x/y halo) live in an
+// chunk of z planes (planes_per_block).  phi planes (with a two-node x/y halo) live in an
 // LDS ring of four; the x and y components of the normal (one-node halo) in
 // a ring of two planes, its z component in the owning thread's registers
 // (the divergence needs n_z only in the node's own column).  Each z step
@@ -27,14 +27,16 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace dpd {
 namespace {
 
-constexpr int kBX = 64, kBY = 16, kTZ = 64;
+constexpr int kBX = 64, kBY = 16;
 constexpr int kThreads = 512;
-constexpr int kRows = kBY * kBX / kThreads;   // nodes per thread in a plane (rows ty, ty + 4)
+constexpr int kRows = kBY * kBX / kThreads;   // nodes per thread in a plane (rows ty, ty + 8)
 constexpr int kRing = 4;                      // phi planes z-1 .. z+2 at step z
 constexpr int kPW = kBX + 4, kPH = kBY + 4;   // phi plane with a 2-node halo
 constexpr int kNW = kBX + 2, kNH = kBY + 2;   // normal plane with a 1-node halo
@@ -49,6 +51,7 @@ struct RelaxArgs {
   T *dst;
   int32_t nx, ny, nz;
   int32_t tiles_x, tiles_y;
+  int32_t tz;     // z planes per block
   uint32_t tiles;
   T cx, cy, cz;   // eps^2 / h_a^2
   T gx, gy, gz;   // eps / (2 h_a)
@@ -97,8 +100,8 @@ __global__ __launch_bounds__(kThreads) void k_phi_relax(RelaxArgs<T> a) {
   const int tix = (int)(t % (uint32_t)a.tiles_x);
   const uint32_t rest = t / (uint32_t)a.tiles_x;
   const int tiy = (int)(rest % (uint32_t)a.tiles_y), tiz = (int)(rest / (uint32_t)a.tiles_y);
-  const int x0 = tix * kBX, y0 = tiy * kBY, z0 = tiz * kTZ;
-  const int z1 = min(z0 + kTZ, a.nz);
+  const int x0 = tix * kBX, y0 = tiy * kBY, z0 = tiz * a.tz;
+  const int z1 = min(z0 + a.tz, a.nz);
   const int tid = threadIdx.x;
   const size_t plane = (size_t)a.nx * (size_t)a.ny;
 
@@ -234,14 +237,21 @@ __global__ __launch_bounds__(kThreads) void k_phi_relax(RelaxArgs<T> a) {
   // prologue: phi planes z0-2 .. z0+1 (z0-2 in the slot that plane z0+2
   // takes next), z0+2 in flight; the thread's own phi on z0-2 and z0-1;
   // planes z0-1 and z0 prepared
-  fetch(wrap(z0 - 2, a.nz));
-  store(s3);
-  fetch(wrap(z0 - 1, a.nz));
-  store(s0);
-  fetch(wrap(z0, a.nz));
-  store(s1);
-  fetch(wrap(z0 + 1, a.nz));
-  store(s2);
+  // (all five planes' loads in flight together)
+  {
+    T first[4][kLoadSlots];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const T *p = a.src + (size_t)wrap(z0 - 2 + q, a.nz) * plane;
+#pragma unroll
+      for (int s = 0; s < kLoadSlots; ++s) first[q][s] = p[loff[s]];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int s = 0; s < kLoadSlots; ++s)
+        sphi[(q == 0 ? s3 : (q == 1 ? s0 : (q == 2 ? s1 : s2))) + lslot[s]] = first[q][s];
+  }
   int zf = wrap(z0 + 2, a.nz);     // wrapped index of the plane in flight
   fetch(zf);
   __syncthreads();
@@ -285,6 +295,29 @@ __global__ __launch_bounds__(kThreads) void k_phi_relax(RelaxArgs<T> a) {
   }
 }
 
+// z planes per block.  A block prepares four planes besides its own, so long
+// columns of planes waste least, but a grid has to give every CU blocks enough:
+// the one with the least work for the busiest CU is taken, (blocks on it) x
+// (planes + 4).  A CU with a single block, or in float with two (three fit), lacks
+// wavefronts to hide the LDS latency and counts for more.  Measured with this choice
+// against 64 planes throughout (us per step): float 24^3 8 / 16, 160^3 18 / 46,
+// 187 x 130 x 201 20 / 50, 256^3 40 / 62, 672^3 600 / 608; double 187 x 130 x 201 31 / 71, 256^3 68 / 78.
+int planes_per_block(int64_t columns, int nz, bool f64) {
+  constexpr int kCUs = 256;
+  int best = 0;
+  double least = 0.0;
+  for (int tz : {4, 8, 12, 16, 24, 32, 48}) {
+    const int64_t per_cu = (columns * ((nz + tz - 1) / tz) + kCUs - 1) / kCUs;
+    const double work =
+        (double)per_cu * (tz + 4) * (per_cu == 1 ? 1.3 : (per_cu == 2 && !f64 ? 1.2 : 1.0));
+    if (!best || work < least) {
+      best = tz;
+      least = work;
+    }
+  }
+  return best;
+}
+
 template <typename T>
 hipError_t launch_relax_t(hipStream_t s, const void *src, void *dst, const int32_t n[3],
                           const double coef[8], void *res) {
@@ -294,10 +327,6 @@ hipError_t launch_relax_t(hipStream_t s, const void *src, void *dst, const int32
   a.nx = n[0];
   a.ny = n[1];
   a.nz = n[2];
-  a.tiles_x = (n[0] + kBX - 1) / kBX;
-  a.tiles_y = (n[1] + kBY - 1) / kBY;
-  const int tiles_z = (n[2] + kTZ - 1) / kTZ;
-  a.tiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y * (uint32_t)tiles_z;
   a.cx = (T)coef[0];
   a.cy = (T)coef[1];
   a.cz = (T)coef[2];
@@ -307,6 +336,10 @@ hipError_t launch_relax_t(hipStream_t s, const void *src, void *dst, const int32
   a.delta2 = (T)coef[6];
   a.dtau = (T)coef[7];
   a.res = res;
+  a.tiles_x = (a.nx + kBX - 1) / kBX;
+  a.tiles_y = (a.ny + kBY - 1) / kBY;
+  a.tz = planes_per_block((int64_t)a.tiles_x * a.tiles_y, a.nz, sizeof(T) == 8);
+  a.tiles = (uint32_t)a.tiles_x * (uint32_t)a.tiles_y * (uint32_t)((a.nz + a.tz - 1) / a.tz);
   k_phi_relax<T><<<a.tiles, kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
@@ -314,7 +347,10 @@ hipError_t launch_relax_t(hipStream_t s, const void *src, void *dst, const int32
 }  // namespace
 
 int64_t phi_relax_blocks(const int32_t n[3]) {
-  return (int64_t)((n[0] + kBX - 1) / kBX) * ((n[1] + kBY - 1) / kBY) * ((n[2] + kTZ - 1) / kTZ);
+  const int64_t columns = (int64_t)((n[0] + kBX - 1) / kBX) * ((n[1] + kBY - 1) / kBY);
+  const int tz = planes_per_block(columns, n[2], false);
+  const int tz64 = planes_per_block(columns, n[2], true);
+  return columns * ((n[2] + std::min(tz, tz64) - 1) / std::min(tz, tz64));
 }
 
 hipError_t launch_phi_relax(hipStream_t s, int f64, const void *src, void *dst,
