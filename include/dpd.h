@@ -295,9 +295,10 @@ int dpd_use_graph(dpd_ctx *ctx, int32_t enable);
 int dpd_use_persistent(dpd_ctx *ctx, int32_t enable);
 
 /* Choose the launch shapes of the integrate kernel (particles per thread:
- * P or 1, with P the context's default, 4 for contexts of at least 2^20
+ * P or 1, with P 4 for contexts of at least 2^20
  * fluid particles without moving walls or specular reflection and 2
- * otherwise, and 2 under dpd_use_persistent) and of the pair-force kernel
+ * otherwise, and 2 under dpd_use_persistent; a context starts with 1 below
+ * 2^20 fluid particles, a batch below 2^18, and with P above) and of the pair-force kernel
  * (work-group size, 128 or 256; default 256) by
  * timing `steps` steps of each of the four combinations from the current
  * state: one untimed round of all four, then two timed rounds in opposite

@@ -392,13 +392,24 @@ int build_tiles(dpd_ctx *c, int size, Tile **dst, int *n, int *cap, bool without
 
 int build_persistent(dpd_ctx *c);
 
-// The context's wider integrate shape, its default: 4 particles per thread
+// The context's wider integrate shape: 4 particles per thread
 // (86 VGPRs, five wavefronts per SIMD, four particles' loads in flight per
 // lane) for contexts of at least 2^20 fluid particles whose boxes all use
 // the plain instance; 2 otherwise.  The instance with moving walls and
 // specular reflection needs 118 VGPRs at 4 (Couette channel: integrate 0.051
-// -> 0.073 ms), and small contexts need the blocks that 2 gives them.
+// -> 0.073 ms).
 int wide_ppt(const dpd_ctx *c) { return !c->reflect && c->NF >= ((int64_t)1 << 20) ? 4 : 2; }
+
+// The shape a context starts with: 1 particle per thread below 2^20, where a
+// step waits for one thread's chain of loads rather than for the chip (whole step,
+// us, 1 against 2: 22.1 / 23.6 at 2,000 particles, 37.9 / 40.1 at 16,000, 71.6 /
+// 73.8 at 177,000, 89.4 / 91.4 at 330,000, 221 / 222 at 746,000 with moving
+// walls), the wider one above (4 against 1: 1.199 / 1.217 ms at 6.3 million) and for
+// batches from 2^18 on, whose boxes end in part-filled tiles (127.4 against 128.7
+// at 64 uneven boxes of 350,000).
+int default_ppt(const dpd_ctx *c) {
+  return c->NF < ((int64_t)1 << (c->R > 1 ? 18 : 20)) ? 1 : wide_ppt(c);
+}
 
 // Pair forces with 16 lanes per particle (k_force_wide) up to this many fluid
 // particles in the context.  It spends about 0.43 ns per particle where the
@@ -1286,7 +1297,7 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   rc = build_bricks(c);
   c->wide = use_wide(c);
   c->box_list = use_box_list(c);
-  if (!rc) rc = set_shapes(c, wide_ppt(c), 256);
+  if (!rc) rc = set_shapes(c, default_ppt(c), 256);
   if (rc) return bail(rc);
   c->cur = 0;
   c->k = 0;

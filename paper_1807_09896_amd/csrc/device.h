@@ -304,7 +304,12 @@ __device__ __forceinline__ T lerp_nc(T a, T b, T t) {
   return a + t * (b - a);
 }
 
+// Index of a periodic axis of n nodes.  Positions lie in [0, L], so i is in
+// [0, n] but for positions set from outside; the division (some 40 instructions
+// an axis, three axes per lookup) is for those alone.
 __device__ __forceinline__ int wrapi(int i, int n) {
+  if ((uint32_t)i < (uint32_t)n) return i;
+  if (i == n) return 0;
   i = i % n;
   return i < 0 ? i + n : i;
 }
