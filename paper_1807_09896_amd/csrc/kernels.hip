@@ -600,33 +600,33 @@ __global__ void k_permute(int64_t n, const int32_t *__restrict__ idx, const floa
 // whose corners are all >= 0 is >= 0 in the rounding of the decision form
 // (each lerp of non-negative values is non-negative), so particles in
 // unflagged cubes cannot have phi < 0 and skip the interpolation.
+// One thread per cube, so that the node reads coalesce (a thread per word of 32
+// cubes read nodes 128 B apart: 4.8 ms for 672^3, 31 us for 80^3); a wavefront
+// writes two words.
 template <typename T>
-__global__ void k_cube_mask(const KGeom G, const T *__restrict__ grid, int64_t nwords,
-                            uint32_t *__restrict__ bits) {
-  const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nwords) return;
-  const int64_t ncube = (int64_t)G.ng[0] * G.ng[1] * G.ng[2];
-  const size_t nx = (size_t)G.ng[0], nxy = nx * (size_t)G.ng[1];
-  uint32_t word = 0;
-  for (int b = 0; b < 32; ++b) {
-    const int64_t q = w * 32 + b;
-    if (q >= ncube) break;
-    const int i = (int)(q % G.ng[0]);
-    const int j = (int)((q / G.ng[0]) % G.ng[1]);
-    const int k = (int)(q / ((int64_t)G.ng[0] * G.ng[1]));
-    const int i1 = i + 1 == G.ng[0] ? 0 : i + 1;
-    const int j1 = j + 1 == G.ng[1] ? 0 : j + 1;
-    const int k1 = k + 1 == G.ng[2] ? 0 : k + 1;
-    bool neg = false;
+__global__ __launch_bounds__(kBlock) void k_cube_mask(const KGeom G, const T *__restrict__ grid,
+                                                      int64_t nwords,
+                                                      uint32_t *__restrict__ bits) {
+  const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t nx = G.ng[0], ny = G.ng[1], nz = G.ng[2];
+  bool neg = false;
+  if (q < nx * ny * nz) {
+    const int64_t r = q / nx;
+    const int i = (int)(q - r * nx), j = (int)(r % ny), k = (int)(r / ny);
+    const int i1 = i + 1 == nx ? 0 : i + 1;
+    const int j1 = j + 1 == ny ? 0 : j + 1;
+    const int k1 = k + 1 == nz ? 0 : k + 1;
     for (int dk = 0; dk < 2; ++dk)
       for (int dj = 0; dj < 2; ++dj) {
-        const T *row = grid + (size_t)(dk ? k1 : k) * nxy + (size_t)(dj ? j1 : j) * nx;
+        const T *row = grid + ((dk ? k1 : k) * ny + (dj ? j1 : j)) * nx;
         neg |= row[i] < (T)0;
         neg |= row[i1] < (T)0;
       }
-    if (neg) word |= 1u << b;
   }
-  bits[w] = word;
+  const unsigned long long m = __ballot(neg);
+  const int lane = (int)__lane_id();
+  const int64_t w = (q - lane) / 32 + (lane >> 5);
+  if ((lane & 31) == 0 && w < nwords) bits[w] = (uint32_t)(m >> lane);
 }
 
 // The face layout of the phase field (PhiQuad): node (i, j, k) gets
@@ -1985,9 +1985,9 @@ hipError_t launch_permute(hipStream_t s, int64_t n, const int32_t *idx, const fl
 hipError_t launch_cube_mask(hipStream_t s, const KGeom &G, const void *grid, int grid_f64,
                             int64_t nwords, uint32_t *bits) {
   if (grid_f64)
-    k_cube_mask<double><<<grid_for(nwords), kBlock, 0, s>>>(G, (const double *)grid, nwords, bits);
+    k_cube_mask<double><<<grid_for(32 * nwords), kBlock, 0, s>>>(G, (const double *)grid, nwords, bits);
   else
-    k_cube_mask<float><<<grid_for(nwords), kBlock, 0, s>>>(G, (const float *)grid, nwords, bits);
+    k_cube_mask<float><<<grid_for(32 * nwords), kBlock, 0, s>>>(G, (const float *)grid, nwords, bits);
   return hipGetLastError();
 }
 
