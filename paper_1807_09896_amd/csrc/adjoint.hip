@@ -193,6 +193,52 @@ __global__ __launch_bounds__(kBlockA) void k_adj_prep(
 // Pairs are found with the force kernel's decision at the same positions,
 // so the set is the forward's.
 // ---------------------------------------------------------------------------
+struct VjpSums {
+  float rx, ry, rz;           // rbar_i
+  float vx, vy, vz;           // vtbar_i
+  double aff, afw, gam;       // parameter terms
+};
+
+__device__ __forceinline__ void vjp_pair(VjpSums &S, const KGeom &G, const KParams &P,
+                                         const float4 &pi, const float4 &vti, const float4 &Fi,
+                                         const float4 &pj, const float4 &vtj, const float4 &Fj,
+                                         bool fluid_j, uint32_t klo, uint32_t khi) {
+  const float dx = sep(pi.x, pj.x, G.L[0]);
+  const float dy = sep(pi.y, pj.y, G.L[1]);
+  const float dz = sep(pi.z, pj.z, G.L[2]);
+  const float r2 = dx * dx + dy * dy + dz * dz;
+  const float rinv = rsqrtf(r2);
+  const float r = r2 * rinv;
+  const float w = 1.0f - r * P.inv_rc;
+  if (!(w > 0.0f)) return;   // the forward's force is zero there
+  const float ex = dx * rinv, ey = dy * rinv, ez = dz * rinv;
+  const float dvx = vti.x - vtj.x, dvy = vti.y - vtj.y, dvz = vti.z - vtj.z;
+  const float u = ex * dvx + ey * dvy + ez * dvz;
+  const float xi = pair_gauss(__float_as_uint(pi.w), __float_as_uint(pj.w), klo, khi, P.key0,
+                              P.key1);
+  const float sr = P.sigma_rdt * xi;
+  const float a = fluid_j ? P.a_ff : P.a_fw;
+  const float c = w * (a - P.gamma * w * u + sr);
+  const float mx = Fi.x - Fj.x, my = Fi.y - Fj.y, mz = Fi.z - Fj.z;
+  const float em = ex * mx + ey * my + ez * mz;
+  const float gw = -(a - 2.0f * P.gamma * w * u + sr) * P.inv_rc * em;
+  const float gwu = -P.gamma * w * w;
+  const float gu = gwu * rinv * em;
+  const float cr = c * rinv;
+  S.rx += gw * ex + gu * (dvx - u * ex) + cr * (mx - ex * em);
+  S.ry += gw * ey + gu * (dvy - u * ey) + cr * (my - ey * em);
+  S.rz += gw * ez + gu * (dvz - u * ez) + cr * (mz - ez * em);
+  S.vx += gwu * em * ex;
+  S.vy += gwu * em * ey;
+  S.vz += gwu * em * ez;
+  const float eF = ex * Fi.x + ey * Fi.y + ez * Fi.z;
+  if (fluid_j)
+    S.aff += (double)(w * eF);
+  else
+    S.afw += (double)(w * eF);
+  S.gam += (double)((-w * w * u + P.dsig_rdt * w * xi) * eF);
+}
+
 template <int BS>
 __global__ __launch_bounds__(BS) void k_force_vjp(
     const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles, int64_t NF,
@@ -209,7 +255,7 @@ __global__ __launch_bounds__(BS) void k_force_vjp(
     tile = tiles[tid];
     act = (int)threadIdx.x < tile.count;
   }
-  double p_aff = 0.0, p_afw = 0.0, p_gam = 0.0;
+  VjpSums S = {};
   if (act) {
     const Box &B = boxes[tile.box];
     const KGeom G = B.G;
@@ -227,7 +273,6 @@ __global__ __launch_bounds__(BS) void k_force_vjp(
     int cx, cy, cz;
     cell_index(G, pi.x, pi.y, pi.z, cx, cy, cz);
     uint32_t *mine = list + threadIdx.x;
-    float rbx = 0.f, rby = 0.f, rbz = 0.f, vbx = 0.f, vby = 0.f, vbz = 0.f;
     NeighbourRows rows;
     rows.init(cx, cy, cz);
     int t = 0, t_end = 0;
@@ -269,51 +314,107 @@ __global__ __launch_bounds__(BS) void k_force_vjp(
         const float4 vtj = vt4[j];
         const bool fluid_j = (int64_t)j < NF;
         const float4 Fj = fluid_j ? fbar[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float dx = sep(pi.x, pj.x, G.L[0]);
-        const float dy = sep(pi.y, pj.y, G.L[1]);
-        const float dz = sep(pi.z, pj.z, G.L[2]);
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        const float rinv = rsqrtf(r2);
-        const float r = r2 * rinv;
-        const float w = 1.0f - r * P.inv_rc;
-        if (!(w > 0.0f)) continue;   // the forward's force is zero there
-        const float ex = dx * rinv, ey = dy * rinv, ez = dz * rinv;
-        const float dvx = vti.x - vtj.x, dvy = vti.y - vtj.y, dvz = vti.z - vtj.z;
-        const float u = ex * dvx + ey * dvy + ez * dvz;
-        const float xi = pair_gauss(gi, __float_as_uint(pj.w), klo, khi, P.key0, P.key1);
-        const float sr = P.sigma_rdt * xi;
-        const float a = fluid_j ? P.a_ff : P.a_fw;
-        const float c = w * (a - P.gamma * w * u + sr);
-        const float mx = Fi.x - Fj.x, my = Fi.y - Fj.y, mz = Fi.z - Fj.z;
-        const float em = ex * mx + ey * my + ez * mz;
-        const float gw = -(a - 2.0f * P.gamma * w * u + sr) * P.inv_rc * em;
-        const float gwu = -P.gamma * w * w;
-        const float gu = gwu * rinv * em;
-        const float cr = c * rinv;
-        rbx += gw * ex + gu * (dvx - u * ex) + cr * (mx - ex * em);
-        rby += gw * ey + gu * (dvy - u * ey) + cr * (my - ey * em);
-        rbz += gw * ez + gu * (dvz - u * ez) + cr * (mz - ez * em);
-        vbx += gwu * em * ex;
-        vby += gwu * em * ey;
-        vbz += gwu * em * ez;
-        const float eF = ex * Fi.x + ey * Fi.y + ez * Fi.z;
-        if (fluid_j)
-          p_aff += (double)(w * eF);
-        else
-          p_afw += (double)(w * eF);
-        p_gam += (double)((-w * w * u + P.dsig_rdt * w * xi) * eF);
+        vjp_pair(S, G, P, pi, vti, Fi, pj, vtj, Fj, fluid_j, klo, khi);
       }
     }
     if (rn) {
       const float4 b = rn[i];
-      rbx += b.x;
-      rby += b.y;
-      rbz += b.z;
+      S.rx += b.x;
+      S.ry += b.y;
+      S.rz += b.z;
     }
-    rt_out[i] = make_float4(rbx, rby, rbz, 0.f);
-    vt_out[i] = make_float4(vbx, vby, vbz, 0.f);
+    rt_out[i] = make_float4(S.rx, S.ry, S.rz, 0.f);
+    vt_out[i] = make_float4(S.vx, S.vy, S.vz, 0.f);
   }
-  block_add3<BS>(p_aff, p_afw, p_gam, part + 3 * (size_t)tid);
+  block_add3<BS>(S.aff, S.afw, S.gam, part + 3 * (size_t)tid);
+}
+
+// The same with 16 lanes per particle, for small contexts (see WideRows): the
+// lanes sum every sixteenth pair and their sums meet in a fixed order at the end.
+// One lane per particle took 54 us for 15,000 particles, 12 us of it arithmetic.
+__global__ __launch_bounds__(kBlockA) void k_force_vjp_wide(
+    const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles, int64_t NF,
+    const float4 *__restrict__ pos4, const float4 *__restrict__ vt4,
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ idx_all,
+    const int32_t *__restrict__ start_all, const float4 *__restrict__ fbar,
+    const float4 *__restrict__ rn, float4 *__restrict__ rt_out, float4 *__restrict__ vt_out,
+    const unsigned long long *__restrict__ dk0, unsigned long long koff, double *part) {
+  __shared__ int ring[kWideParts][kWideRing + 8];
+  __shared__ int4 rows_lds[kWideParts][9];
+  const int tid = xcd_block();
+  const int grp = (int)threadIdx.x / kWideLanes, g = (int)threadIdx.x % kWideLanes;
+  bool act = tid < ntiles;
+  Tile tile{0, 0, 0, 0};
+  if (act) {
+    tile = tiles[tid];
+    act = grp < tile.count;   // whole groups
+  }
+  VjpSums S = {};
+  if (act) {
+    const Box &B = boxes[tile.box];
+    const KGeom G = B.G;
+    const KParams P = B.P;
+    const unsigned long long kk = *dk0 + koff;
+    const uint32_t klo = (uint32_t)kk;
+    const uint32_t khi = ((uint32_t)(kk >> 32) & 0xFFFFu) | (P.replica << 16);
+    const int i = idx[(int64_t)tile.first + grp];
+    const float4 pi = pos4[i], vti = vt4[i], Fi = fbar[i];
+    int cx, cy, cz;
+    cell_index(G, pi.x, pi.y, pi.z, cx, cy, cz);
+    WideRows rows;
+    rows.init(G, (int)B.co, cx, cy, cz, g, start_all, rows_lds[grp]);
+    int *const list = ring[grp];
+    const int shift = ((int)__lane_id() / kWideLanes) * kWideLanes;
+    int listed = 0, done = 0;
+    auto evaluate = [&]() {
+      const int e = done + g;
+      if (e < listed) {
+        const int j = list[e & (kWideRing - 1)];
+        const bool fluid_j = (int64_t)j < NF;
+        const float4 pj = pos4[j], vtj = vt4[j];
+        const float4 Fj = fluid_j ? fbar[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+        vjp_pair(S, G, P, pi, vti, Fi, pj, vtj, Fj, fluid_j, klo, khi);
+      }
+      done += kWideLanes;
+    };
+    for (int c0 = 0; c0 < rows.total; c0 += kWideBatch * kWideLanes) {
+      int j[kWideBatch];
+      float4 pj[kWideBatch];
+#pragma unroll
+      for (int k = 0; k < kWideBatch; ++k)
+        j[k] = idx_all[rows.entry(min(c0 + k * kWideLanes + g, rows.total - 1))];
+#pragma unroll
+      for (int k = 0; k < kWideBatch; ++k) pj[k] = pos4[j[k]];
+#pragma unroll
+      for (int k = 0; k < kWideBatch; ++k) {
+        const float r2 = pair_r2(sep(pi.x, pj[k].x, G.L[0]), sep(pi.y, pj[k].y, G.L[1]),
+                                 sep(pi.z, pj[k].z, G.L[2]));
+        const bool hit = r2 < P.rc2 && r2 > 0.0f && c0 + k * kWideLanes + g < rows.total;
+        const uint32_t m = (uint32_t)(__ballot(hit) >> shift) & 0xFFFFu;
+        if (hit) list[(listed + __popc(m & ((1u << g) - 1u))) & (kWideRing - 1)] = j[k];
+        listed += __popc(m);
+      }
+      wave_lds_sync();
+      while (listed - done >= kWideLanes) evaluate();
+      wave_lds_sync();
+    }
+    if (done < listed) evaluate();
+#pragma unroll
+    for (int d = kWideLanes / 2; d > 0; d >>= 1) {
+      S.rx += __shfl_xor(S.rx, d, kWideLanes);
+      S.ry += __shfl_xor(S.ry, d, kWideLanes);
+      S.rz += __shfl_xor(S.rz, d, kWideLanes);
+      S.vx += __shfl_xor(S.vx, d, kWideLanes);
+      S.vy += __shfl_xor(S.vy, d, kWideLanes);
+      S.vz += __shfl_xor(S.vz, d, kWideLanes);
+    }
+    if (g == 0) {
+      const float4 b = rn ? rn[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+      rt_out[i] = make_float4(S.rx + b.x, S.ry + b.y, S.rz + b.z, 0.f);
+      vt_out[i] = make_float4(S.vx, S.vy, S.vz, 0.f);
+    }
+  }
+  block_add3<kBlockA>(S.aff, S.afw, S.gam, part + 3 * (size_t)tid);
 }
 
 // Gradient of the trilinear interpolant at a located point (per unit
@@ -444,17 +545,19 @@ __global__ __launch_bounds__(kBlockA) void k_integrate_vjp(
 
 // Fixed-order final sums of the per-block partials:
 // out = {a_ff, a_fw, gamma} from the pair VJP and {g_x, g_y, g_z}.
-__global__ void k_reduce_partials(int nb_f, const double *__restrict__ part_f, int nb_g,
-                                  const double *__restrict__ part_g, double *out) {
-  const int k = (int)threadIdx.x;
-  if (k >= 6) return;
+// (one wavefront per sum, each lane every 64th block)
+__global__ __launch_bounds__(6 * 64) void k_reduce_partials(int nb_f,
+                                                            const double *__restrict__ part_f,
+                                                            int nb_g,
+                                                            const double *__restrict__ part_g,
+                                                            double *out) {
+  const int k = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+  const double *p = k < 3 ? part_f + k : part_g + (k - 3);
+  const int nb = k < 3 ? nb_f : nb_g;
   double s = 0.0;
-  if (k < 3) {
-    for (int b = 0; b < nb_f; ++b) s += part_f[3 * b + k];
-  } else {
-    for (int b = 0; b < nb_g; ++b) s += part_g[3 * b + k - 3];
-  }
-  out[k] = s;
+  for (int b = lane; b < nb; b += 64) s += p[3 * (size_t)b];
+  s = wave_sum(s);
+  if (lane == 0) out[k] = s;
 }
 
 }  // namespace
@@ -516,7 +619,10 @@ hipError_t launch_force_vjp(hipStream_t s, int block, const Box *boxes, const Ti
                             unsigned long long koff, double *part) {
   if (ntiles <= 0) return hipSuccess;
   const unsigned nb = (unsigned)force_vjp_blocks(ntiles);
-  if (block == 128)
+  if (block == 0)
+    k_force_vjp_wide<<<nb, kBlockA, 0, s>>>(boxes, tiles, ntiles, NF, pos4, vt4, idx, idx_all,
+                                            start_all, fbar, rn, rt_out, vt_out, dk0, koff, part);
+  else if (block == 128)
     k_force_vjp<128><<<nb, 128, 0, s>>>(boxes, tiles, ntiles, NF, pad, pos4, vt4, idx, idx_all,
                                         start_all, fbar, rn, rt_out, vt_out, dk0, koff, part);
   else
@@ -544,7 +650,7 @@ hipError_t launch_integrate_vjp(hipStream_t s, const Box *boxes, int64_t nf, con
 
 hipError_t launch_reduce_partials(hipStream_t s, int nb_f, const double *part_f, int nb_g,
                                   const double *part_g, double *out) {
-  k_reduce_partials<<<1, 64, 0, s>>>(nb_f, part_f, nb_g, part_g, out);
+  k_reduce_partials<<<1, 6 * 64, 0, s>>>(nb_f, part_f, nb_g, part_g, out);
   return hipGetLastError();
 }
 

@@ -67,6 +67,12 @@ struct Window {
   float scale = 0.f;
   uint64_t k0 = 0, gen = 0;
   int64_t nf = 0;
+  // the whole window kept (store), where it fits kWindowStore: per step its
+  // start state, drifted positions, predicted velocities and cell list, so that
+  // the sweep recomputes nothing
+  bool full = false;
+  char *store = nullptr;
+  size_t store_cap = 0;
   float4 *ck = nullptr;    // nck checkpoints of 3 x NF (pos, vel, frc)
   float4 *seg = nullptr;   // ckpt states of one segment, 3 x NF each
   float4 *save = nullptr;  // the context state during a backward sweep
@@ -440,9 +446,11 @@ int set_shapes(dpd_ctx *c, int ppt, int fblock) {
   c->fblock = fblock;
   drop_graphs(c);
   int rc = build_tiles(c, 256 * ppt, &c->itiles, &c->n_itiles, &c->itiles_cap);
-  if (!rc) rc = build_tiles(c, fblock, &c->ftiles, &c->n_ftiles, &c->ftiles_cap);
   if (!rc)
-    rc = build_tiles(c, c->wide ? dpd::wide_parts() : fblock, &c->otiles, &c->n_otiles,
+    rc = build_tiles(c, c->wide ? dpd::kWideParts : fblock, &c->ftiles, &c->n_ftiles,
+                     &c->ftiles_cap);
+  if (!rc)
+    rc = build_tiles(c, c->wide ? dpd::kWideParts : fblock, &c->otiles, &c->n_otiles,
                      &c->otiles_cap, true, true);
   if (!rc && c->persistent) rc = build_persistent(c);
   return rc;
@@ -780,7 +788,7 @@ int enqueue_step(dpd_ctx *c, hipStream_t s) {
   }
   HIP_TRY(c, timed(c, s, K_INTEGRATE, [&] {
             return dpd::launch_integrate(s, c->ppt, c->boxes, c->itiles, c->n_itiles, c->pos[a],
-                                         c->vel[a], c->frc[a], c->vt, c->cell_of, c->rank_of,
+                                         c->pos[a], c->vel[a], c->frc[a], c->vt, c->cell_of, c->rank_of,
                                          c->count, c->bits, c->use_mask, c->quad, c->grid_f64,
                                          c->status, c->NF, c->wcstart, c->reflect ? 1 : 0);
           }));
@@ -1395,6 +1403,48 @@ int grow(dpd_ctx *c, P **ptr, size_t count, int *cap, int want) {
   return DPD_OK;
 }
 
+// One step of a stored window: X (3 x NF: the state it starts from), the drifted
+// positions D and predicted velocities V (NF + NW + 1 records, walls and pad at
+// the end) and its cell list.  Steps are `stride` bytes apart, a multiple of 256.
+struct StoredStep {
+  float4 *X, *D, *V;
+  int32_t *idx, *idx_all, *start_all;
+};
+
+struct StoreLayout {
+  size_t d, v, idx, idx_all, start_all, stride;   // byte offsets within a step
+  explicit StoreLayout(const dpd_ctx *c) {
+    const size_t nf = (size_t)c->NF, nrec = nf + (size_t)c->NW + 1;
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    d = up(48 * nf);
+    v = d + up(16 * nrec);
+    idx = v + up(16 * nrec);
+    idx_all = idx + up(4 * nf);
+    start_all = idx_all + up(4 * (nrec - 1 + dpd::kIdxSlack));
+    stride = start_all + up(4 * ((size_t)c->NCELL + 1 + dpd::kStartSlack));
+  }
+};
+
+StoredStep stored_step(const dpd_ctx *c, int t) {
+  const StoreLayout l(c);
+  char *p = c->win.store + (size_t)t * l.stride;
+  return {(float4 *)p,           (float4 *)(p + l.d),         (float4 *)(p + l.v),
+          (int32_t *)(p + l.idx), (int32_t *)(p + l.idx_all), (int32_t *)(p + l.start_all)};
+}
+
+// Windows of up to this many bytes are kept whole.  A step of the 20^3 slit
+// (19,700 particles) takes 1.9 MB; keeping its 24-step window, the sweep
+// launches three kernels per step instead of recomputing the segment and then
+// each step's drift and cell list.  Larger windows keep a state every ckpt
+// steps, as do those whose store cannot be allocated.
+constexpr size_t kWindowStore = (size_t)2 << 30;
+
+// The state a segment starts from.
+const float4 *segment_start(const dpd_ctx *c, int seg) {
+  const Window &W = c->win;
+  return W.full ? stored_step(c, seg * W.ckpt).X : W.ck + (size_t)seg * 3 * c->NF;
+}
+
 int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
   Window &W = c->win;
   const size_t nf = (size_t)std::max<int64_t>(c->NF, 1);
@@ -1408,8 +1458,17 @@ int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
     W.nf = c->NF;
   }
   int dummy = 0;
-  int rc = grow(c, &W.ck, 3 * nf * (size_t)nck, &W.cap_nck, nck);
-  if (!rc) rc = grow(c, &W.seg, 3 * nf * (size_t)ckpt, &W.cap_ckpt, ckpt);
+  int rc = DPD_OK;
+  const size_t want = StoreLayout(c).stride * (size_t)steps;
+  W.full = c->NF > 0 && c->nbricks == 0 && want <= kWindowStore;
+  if (W.full && W.store_cap < want) {
+    if (W.store) dfree(c, W.store);
+    W.store = (char *)dalloc(c, want);
+    W.store_cap = W.store ? want : 0;
+    W.full = W.store != nullptr;
+  }
+  if (!W.full) rc = grow(c, &W.ck, 3 * nf * (size_t)nck, &W.cap_nck, nck);
+  if (!rc && !W.full) rc = grow(c, &W.seg, 3 * nf * (size_t)ckpt, &W.cap_ckpt, ckpt);
   if (!rc && !W.save) rc = grow(c, &W.save, 3 * nf, &dummy, 1);
   if (!rc && !W.wpos) rc = grow(c, &W.wpos, (size_t)(c->NF + c->NW + 1), &dummy, 1);
   if (!rc && !W.adj) rc = grow(c, &W.adj, 11 * nf, &dummy, 1);
@@ -1435,6 +1494,104 @@ int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
   return rc;
 }
 
+// Step t of a window that is kept whole: its launches read and write the
+// store's arrays in place of the context's (the last step's new state goes to
+// the context), so nothing is copied.
+int stored_window_step(dpd_ctx *c, int t, bool last) {
+  const StoredStep st = stored_step(c, t);
+  const int64_t NF = c->NF;
+  const int a = c->cur, b = 1 - a;
+  float4 *const next = last ? nullptr : stored_step(c, t + 1).X;
+  struct Saved {
+    float4 *pos[2], *vel[2], *frc[2], *vt;
+    int32_t *idx, *idx_all, *start_all;
+  } keep = {{c->pos[0], c->pos[1]}, {c->vel[0], c->vel[1]}, {c->frc[0], c->frc[1]}, c->vt,
+            c->idx, c->idx_all, c->start_all};
+  c->pos[a] = st.D;
+  c->vel[a] = st.X + NF;
+  c->frc[a] = st.X + 2 * NF;
+  c->vt = st.V;
+  c->idx = st.idx;
+  c->idx_all = st.idx_all;
+  c->start_all = st.start_all;
+  if (next) {
+    c->pos[b] = next;
+    c->vel[b] = next + NF;
+    c->frc[b] = next + 2 * NF;
+  }
+  auto launches = [&]() -> int {
+    HIP_TRY(c, timed(c, c->stream, K_INTEGRATE, [&] {
+              return dpd::launch_integrate(c->stream, c->ppt, c->boxes, c->itiles, c->n_itiles,
+                                           st.X, st.D, st.X + NF, st.X + 2 * NF, st.V, c->cell_of,
+                                           c->rank_of, c->count, c->bits, c->use_mask, c->quad,
+                                           c->grid_f64, c->status, NF, c->wcstart, 0);
+            }));
+    int rc = scan_scatter_sort(c, c->stream, nullptr, c->dk);
+    return rc ? rc : force_pass(c, c->stream, 0);
+  };
+  const int rc = launches();
+  for (int q = 0; q < 2; ++q) {
+    c->pos[q] = keep.pos[q];
+    c->vel[q] = keep.vel[q];
+    c->frc[q] = keep.frc[q];
+  }
+  c->vt = keep.vt;
+  c->idx = keep.idx;
+  c->idx_all = keep.idx_all;
+  c->start_all = keep.start_all;
+  c->cur = rc || !last ? a : b;
+  if (rc) return rc;
+  c->k += 1;
+  c->steps += 1;
+  return DPD_OK;
+}
+
+// The steps of a window that is kept whole, and its bin sums.
+int stored_window(dpd_ctx *c) {
+  Window &W = c->win;
+  const StoreLayout l(c);
+  const int64_t NF = c->NF, stride = (int64_t)(l.stride / 16);
+  const StoredStep s0 = stored_step(c, 0);
+  int rc = save_state(c, s0.X);
+  if (rc) return rc;
+  HIP_TRY(c, dpd::launch_store_walls(c->stream, c->NW + 1, W.steps, stride, c->pos[c->cur] + NF,
+                                     c->vt + NF, s0.D + NF, s0.V + NF, (int64_t)(l.stride / 4),
+                                     s0.idx_all + NF + c->NW, (int32_t)(NF + c->NW)));
+  for (int t = 0; t < W.steps; ++t) {
+    rc = stored_window_step(c, t, t == W.steps - 1);
+    if (rc) return rc;
+  }
+  // the states after steps 1 .. steps - 1 start the next steps; the last is the context's
+  if (W.steps > 1) {
+    const float4 *x = stored_step(c, 1).X;
+    HIP_TRY(c, dpd::launch_obs(c->stream, NF, W.steps - 1, stride, x, x + NF, W.axis, W.nbins,
+                               W.scale, W.sums, W.counts));
+  }
+  HIP_TRY(c, dpd::launch_obs(c->stream, NF, 1, 0, c->pos[c->cur], c->vel[c->cur], W.axis, W.nbins,
+                             W.scale, W.sums, W.counts));
+  return DPD_OK;
+}
+
+// The VJP kernels of step t from its arrays st: A holds the adjoints of X_{t+1}
+// (slot order), B receives those of X_t.
+int step_vjp(dpd_ctx *c, const StoredStep &st, uint64_t t, const float4 *A, float4 *B,
+             double *dphi) {
+  Window &W = c->win;
+  const int64_t NF = c->NF;
+  hipStream_t s = c->stream;
+  float4 *rn = W.adj + 6 * NF, *vn = W.adj + 7 * NF, *fbar = W.adj + 8 * NF;
+  float4 *rt = W.adj + 9 * NF, *vtb = W.adj + 10 * NF;
+  HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 0, st.idx, st.D, st.V, A, A + NF, A + 2 * NF,
+                                  W.lw, W.axis, W.nbins, W.scale, rn, vn, fbar, W.part_g));
+  HIP_TRY(c, dpd::launch_force_vjp(s, c->wide ? 0 : c->fblock, c->boxes, c->ftiles, c->n_ftiles,
+                                   NF, (int32_t)(NF + c->NW), st.D, st.V, st.idx, st.idx_all,
+                                   st.start_all, fbar, rn, rt, vtb, W.dk0, t + 1, W.part_f));
+  HIP_TRY(c, dpd::launch_integrate_vjp(s, c->boxes, NF, st.X, st.X + NF, st.X + 2 * NF, st.V, rt,
+                                       vtb, vn, c->grid, c->grid_f64, dphi, B, B + NF,
+                                       B + 2 * NF));
+  return DPD_OK;
+}
+
 // Recomputed step t of a segment in the backward sweep: from the stored
 // state X_t (3 x NF block x), redo the drift/bounce-back and the cell list
 // of r_{t+1} in the order of X_t, then the three VJP kernels.  A holds the
@@ -1444,24 +1601,15 @@ int backward_step(dpd_ctx *c, const float4 *x, uint64_t t, const float4 *A, floa
   Window &W = c->win;
   const int64_t NF = c->NF;
   hipStream_t s = c->stream;
-  float4 *rn = W.adj + 6 * NF, *vn = W.adj + 7 * NF, *fbar = W.adj + 8 * NF;
-  float4 *rt = W.adj + 9 * NF, *vtb = W.adj + 10 * NF;
   HIP_TRY(c, hipMemcpyAsync(W.wpos, x, 16 * (size_t)NF, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(c, dpd::launch_integrate(s, c->ppt, c->boxes, c->itiles, c->n_itiles, W.wpos, x + NF,
-                                   x + 2 * NF, c->vt, c->cell_of, c->rank_of, c->count, c->bits,
+  HIP_TRY(c, dpd::launch_integrate(s, c->ppt, c->boxes, c->itiles, c->n_itiles, W.wpos, W.wpos,
+                                   x + NF, x + 2 * NF, c->vt, c->cell_of, c->rank_of, c->count, c->bits,
                                    c->use_mask, c->quad, c->grid_f64, c->status, NF, c->wcstart,
                                    0));
   int rc = scan_scatter_sort(c, s, nullptr, nullptr, false);
   if (rc) return rc;
-  HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 0, c->idx, W.wpos, c->vt, A, A + NF,
-                                  A + 2 * NF, W.lw, W.axis, W.nbins, W.scale, rn, vn, fbar,
-                                  W.part_g));
-  HIP_TRY(c, dpd::launch_force_vjp(s, c->fblock, c->boxes, c->ftiles, c->n_ftiles, NF,
-                                   (int32_t)(NF + c->NW), W.wpos, c->vt, c->idx, c->idx_all,
-                                   c->start_all, fbar, rn, rt, vtb, W.dk0, t + 1, W.part_f));
-  HIP_TRY(c, dpd::launch_integrate_vjp(s, c->boxes, NF, x, x + NF, x + 2 * NF, c->vt, rt, vtb,
-                                       vn, c->grid, c->grid_f64, dphi, B, B + NF, B + 2 * NF));
-  return DPD_OK;
+  return step_vjp(c, {const_cast<float4 *>(x), W.wpos, c->vt, c->idx, c->idx_all, c->start_all}, t,
+                  A, B, dphi);
 }
 
 int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
@@ -1476,9 +1624,13 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
   const int cur0 = c->cur;
   const uint64_t k_save = c->k;
   const int64_t steps_save = c->steps;
-  rc = save_state(c, W.save);
-  if (rc) return rc;
-  HIP_TRY(c, hipMemcpyAsync(W.status_save, c->status, sizeof(Status), hipMemcpyDeviceToDevice, s));
+  const bool recompute = !W.full;
+  if (recompute) {
+    rc = save_state(c, W.save);
+    if (rc) return rc;
+    HIP_TRY(c,
+            hipMemcpyAsync(W.status_save, c->status, sizeof(Status), hipMemcpyDeviceToDevice, s));
+  }
   const bool timing = c->timing;
   c->timing = false;
 
@@ -1491,7 +1643,11 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
   // walls and the pad of the sweep's position array
   HIP_TRY(c, hipMemcpyAsync(W.wpos + NF, c->pos[c->cur] + NF, 16 * (size_t)(c->NW + 1),
                             hipMemcpyDeviceToDevice, s));
-  for (int seg = W.nck - 1; seg >= 0 && !rc; --seg) {
+  for (int t = W.steps - 1; t >= 0 && !rc && !recompute; --t) {
+    rc = step_vjp(c, stored_step(c, t), (uint64_t)t, A, B, dphi);
+    std::swap(A, B);
+  }
+  for (int seg = W.nck - 1; seg >= 0 && !rc && recompute; --seg) {
     const int t0 = seg * W.ckpt, t1 = std::min(W.steps, t0 + W.ckpt);
     rc = load_state(c, W.ck + (size_t)seg * 3 * NF);
     if (rc) break;
@@ -1509,7 +1665,7 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
   }
   if (!rc) {
     // the refreshed starting force f0 = F(r0, v0; k0) + g
-    const float4 *x0 = W.ck;
+    const float4 *x0 = segment_start(c, 0);
     float4 *rt = W.adj + 9 * NF, *vtb = W.adj + 10 * NF, *fbar = W.adj + 8 * NF;
     const Replica &p = c->rep[0];
     HIP_TRY(c, hipMemcpyAsync(W.wpos, x0, 16 * (size_t)NF, hipMemcpyDeviceToDevice, s));
@@ -1520,7 +1676,7 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
       HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 1, c->idx, W.wpos, c->vt, A, A + NF,
                                       A + 2 * NF, W.lw, W.axis, W.nbins, W.scale, nullptr,
                                       nullptr, fbar, W.part_g));
-      HIP_TRY(c, dpd::launch_force_vjp(s, c->fblock, c->boxes, c->ftiles, c->n_ftiles, NF,
+      HIP_TRY(c, dpd::launch_force_vjp(s, c->wide ? 0 : c->fblock, c->boxes, c->ftiles, c->n_ftiles, NF,
                                        (int32_t)(NF + c->NW), W.wpos, c->vt, c->idx, c->idx_all,
                                        c->start_all, fbar, nullptr, rt, vtb, W.dk0, 0, W.part_f));
       HIP_TRY(c, dpd::launch_reduce_partials(s, nb_f, W.part_f, nb_g, W.part_g, W.acc));
@@ -1531,10 +1687,13 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
   c->cur = cur0;
   c->k = k_save;
   c->steps = steps_save;
-  int r2 = load_state(c, W.save);
-  if (!rc) rc = r2;
-  HIP_TRY(c, hipMemcpyAsync(c->status, W.status_save, sizeof(Status), hipMemcpyDeviceToDevice, s));
-  HIP_TRY(c, dpd::launch_set_u64(s, c->dk, c->k));
+  if (recompute) {
+    int r2 = load_state(c, W.save);
+    if (!rc) rc = r2;
+    HIP_TRY(c,
+            hipMemcpyAsync(c->status, W.status_save, sizeof(Status), hipMemcpyDeviceToDevice, s));
+    HIP_TRY(c, dpd::launch_set_u64(s, c->dk, c->k));
+  }
   if (rc) return rc;
   double acc[6];
   HIP_TRY(c, hipMemcpyAsync(acc, W.acc, sizeof acc, hipMemcpyDeviceToHost, s));
@@ -1580,7 +1739,7 @@ int trace_impl(dpd_ctx *c, float *pos_log, float *vel_log, float *frc_log, int32
   };
   for (int seg = 0; seg < W.nck && !rc; ++seg) {
     const int t0 = seg * W.ckpt, t1 = std::min(W.steps, t0 + W.ckpt);
-    rc = load_state(c, W.ck + (size_t)seg * 3 * NF);
+    rc = load_state(c, segment_start(c, seg));
     if (rc) break;
     c->k = W.k0 + (uint64_t)t0;
     HIP_TRY(c, dpd::launch_set_u64(s, c->dk, c->k));
@@ -2049,14 +2208,18 @@ int dpd_window_forward(dpd_ctx *c, int32_t steps, int32_t ckpt, int32_t axis, in
   HIP_TRY(c, dpd::launch_set_u64(c->stream, W.dk0, W.k0));
   HIP_TRY(c, dpd::launch_fill_zero(c->stream, W.sums, 8 * (size_t)nbins));
   HIP_TRY(c, dpd::launch_fill_zero(c->stream, W.counts, 8 * (size_t)nbins));
-  for (int t = 0; t < steps; ++t) {
+  if (W.full) {
+    rc = stored_window(c);
+    if (rc) return rc;
+  }
+  for (int t = 0; t < steps && !W.full; ++t) {
     if (t % ckpt == 0) {
       rc = save_state(c, W.ck + (size_t)(t / ckpt) * 3 * c->NF);
       if (rc) return rc;
     }
     rc = one_step(c);
     if (rc) return rc;
-    HIP_TRY(c, dpd::launch_obs(c->stream, c->NF, c->pos[c->cur], c->vel[c->cur], axis, nbins,
+    HIP_TRY(c, dpd::launch_obs(c->stream, c->NF, 1, 0, c->pos[c->cur], c->vel[c->cur], axis, nbins,
                                W.scale, W.sums, W.counts));
   }
   HIP_TRY(c, dpd::launch_obs_final(c->stream, nbins, W.sums, W.counts, profile, counts));

@@ -617,6 +617,70 @@ struct Ints4 {
 // True when the predicate holds on any active lane of the wavefront.
 __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0ull; }
 
+// Small contexts: 16 lanes share a particle (the pair force and its adjoint).
+constexpr int kWideLanes = 16;
+constexpr int kWideParts = 256 / kWideLanes;      // particles per block of 256
+constexpr int kWideBatch = 8;                     // candidates per lane in flight
+constexpr int kWideRing = 256;                    // >= 8 x 16 + 15 listed pairs, a power of two
+
+// LDS written by some lanes of a wavefront, read by others of the same one.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The candidates of one particle, by the 16 lanes of its group: their nine
+// neighbour rows (two runs where a row wraps in x) numbered through.
+struct WideRows {
+  int total;        // candidates
+  int off[8];       // number of the first candidate of rows 1 .. 8
+  const int4 *row;  // LDS: {first candidate, run A's first entry, its length, run B's first entry}
+
+  __device__ __forceinline__ void init(const KGeom &G, int co, int cx, int cy, int cz, int g,
+                                       const int32_t *__restrict__ start_all, int4 *lds) {
+    int ta = 0, na = 0, tb = 0, nb = 0;
+    if (g < 9) {
+      const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
+      int qy = cy + g % 3 - 1, qz = cz + g / 3 - 1;
+      qy += qy < 0 ? ny : (qy >= ny ? -ny : 0);
+      qz += qz < 0 ? nz : (qz >= nz ? -nz : 0);
+      const int32_t *s = start_all + co + (qz * ny + qy) * nx;
+      const bool left = cx == 0, right = cx == nx - 1;
+      const int a0 = left ? nx - 1 : (right ? nx - 2 : cx - 1);
+      ta = s[a0];
+      na = s[a0 + (left ? 1 : (right ? 2 : 3))] - ta;
+      if (left || right) {
+        tb = s[0];
+        nb = s[left ? 2 : 1] - tb;
+      }
+    }
+    int incl = na + nb;
+#pragma unroll
+    for (int d = 1; d < kWideLanes; d <<= 1) {
+      const int v = __shfl_up(incl, d, kWideLanes);
+      if (g >= d) incl += v;
+    }
+    total = __shfl(incl, kWideLanes - 1, kWideLanes);
+    if (g < 9) lds[g] = make_int4(incl - na - nb, ta, na, tb);
+    wave_lds_sync();
+    row = lds;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) off[q] = lds[q + 1].x;
+  }
+
+  // run entry of candidate c, 0 <= c < total: in the last row that starts at
+  // or before c (rows without candidates start where the next one does)
+  __device__ __forceinline__ int entry(int c) const {
+    int r = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) r += c >= off[q] ? 1 : 0;
+    const int4 R = row[r];
+    const int u = c - R.x;
+    return u < R.z ? R.y + u : R.w + (u - R.z);
+  }
+};
+
 // Map a hardware block index to a logical one so that each of the 8 XCDs
 // (which receive blocks round-robin) works on one contiguous eighth of the
 // index space and its L2 sees one spatial region.  gridDim.x must be a

@@ -143,16 +143,17 @@ hipError_t launch_build_quad(hipStream_t s, const KGeom &G, const void *grid, in
                              void *quad);
 
 // Fused drift + predicted velocity + phi test + reflection + binning, over
-// tiles of up to ppt x 256 particles (ppt 1, 2 or 4); quad is the base of the
+// tiles of up to ppt x 256 particles (ppt 1, 2 or 4), from pos4 to pos_out (which
+// may be the same array); quad is the base of the
 // concatenated phase fields in the face layout, bits of the concatenated
 // cube masks.  reflect = 1
 // (some box has moving walls or specular reflection) runs the instance with
 // those forms: boxes with moving walls look up the solid's velocity among the
 // walls (entries NF + w of pos4 and vt4, runs wcstart over the global cells).
 hipError_t launch_integrate(hipStream_t s, int ppt, const Box *boxes, const Tile *tiles,
-                            int ntiles, float4 *pos4, const float4 *vel4, const float4 *frc4,
-                            float4 *vt4, int32_t *cell_of, int32_t *rank_of, int32_t *count,
-                            const uint32_t *bits, int use_mask, const void *quad, int grid_f64,
+                            int ntiles, const float4 *pos4, float4 *pos_out, const float4 *vel4,
+                            const float4 *frc4, float4 *vt4, int32_t *cell_of, int32_t *rank_of,
+                            int32_t *count, const uint32_t *bits, int use_mask, const void *quad, int grid_f64,
                             Status *st, int64_t NF, const int32_t *wcstart, int reflect);
 
 // Walls of one box from walls_in/vt_in into walls_out/vt_out, advanced by
@@ -179,8 +180,7 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
                         const unsigned long long *dk, Status *st, int sph);
 
 // The same pair forces with 16 lanes per particle, for small contexts, over
-// tiles of up to wide_parts() fluid slots.  It reads no coarse codes.
-int wide_parts();
+// tiles of up to kWideParts fluid slots.  It reads no coarse codes.
 hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,
                              int64_t NF, int init, const float4 *pos4, const float4 *vt4,
                              const float4 *vel4, const float4 *frc4, const int32_t *idx,
@@ -244,9 +244,16 @@ constexpr int kMaxBins = 1024;
 // Window observable of one box: per bin (decision form
 // clamp(floor(fl(x_axis * scale)), 0, nbins - 1)) the sum of v_x and the
 // count, added to sums / counts.
-hipError_t launch_obs(hipStream_t s, int64_t nf, const float4 *pos4, const float4 *vel4,
-                      int axis, int nbins, float scale, double *sums,
+// Over nstates states, `stride` float4 apart in both arrays.
+hipError_t launch_obs(hipStream_t s, int64_t nf, int nstates, int64_t stride, const float4 *pos4,
+                      const float4 *vel4, int axis, int nbins, float scale, double *sums,
                       unsigned long long *counts);
+// Walls and pad (nrec float4 each) from pos and vt into the tails of the nsteps
+// stored steps' positions and predicted velocities, `stride` float4 apart, and the
+// spare entries after each step's merged runs (run_stride int32 apart).
+hipError_t launch_store_walls(hipStream_t s, int64_t nrec, int nsteps, int64_t stride,
+                              const float4 *pos, const float4 *vt, float4 *pos_out,
+                              float4 *vt_out, int64_t run_stride, int32_t *slack, int32_t pad);
 hipError_t launch_obs_final(hipStream_t s, int nbins, const double *sums,
                             const unsigned long long *counts, double *profile,
                             int64_t *counts_out);
@@ -262,6 +269,7 @@ hipError_t launch_adj_prep(hipStream_t s, const Box *boxes, int64_t nf, int init
                            const float *lw, int axis, int nbins, float scale, float4 *rn,
                            float4 *vn, float4 *fbar, double *part_g);
 int force_vjp_blocks(int ntiles);
+// block 0: the kernel with 16 lanes per particle, over tiles of kWideParts.
 hipError_t launch_force_vjp(hipStream_t s, int block, const Box *boxes, const Tile *tiles,
                             int ntiles, int64_t NF, int32_t pad, const float4 *pos4,
                             const float4 *vt4, const int32_t *idx, const int32_t *idx_all,

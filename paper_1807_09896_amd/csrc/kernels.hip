@@ -836,12 +836,14 @@ __device__ __forceinline__ Moved integrate_one(const KGeom &G, const KParams &P,
 }
 
 // Tile tid of up to PPT x kBlock particles of one box, by one block of
-// kBlock threads; each thread advances PPT particles.
+// kBlock threads; each thread advances PPT particles (pos_out may be pos4: a
+// thread reads its own particles before it writes them).
 template <typename T, int PPT, bool REFLECT>
 __device__ __forceinline__ void integrate_tile(
     int tid, const Box *__restrict__ boxes, const Tile *__restrict__ tiles,
-    float4 *__restrict__ pos4, const float4 *__restrict__ vel4, const float4 *__restrict__ frc4,
-    float4 *__restrict__ vt4, int32_t *__restrict__ cell_of, int32_t *__restrict__ rank_of,
+    const float4 *pos4, float4 *pos_out, const float4 *__restrict__ vel4,
+    const float4 *__restrict__ frc4, float4 *__restrict__ vt4,
+    int32_t *__restrict__ cell_of, int32_t *__restrict__ rank_of,
     int32_t *__restrict__ count, const uint32_t *__restrict__ bits_base, int use_mask,
     const typename PhiQuad<T>::type *__restrict__ quad_base, Status *st, int64_t NF,
     const int32_t *__restrict__ wcstart) {
@@ -888,7 +890,7 @@ __device__ __forceinline__ void integrate_tile(
   for (int u = 0; u < PPT; ++u) {
     const int k = wave_rank(r[u], b[u]);
     if (a[u]) {
-      store_stream(&pos4[p[u]], m[u].pos);
+      store_stream(&pos_out[p[u]], m[u].pos);
       store_stream(&vt4[p[u]], m[u].vt);
       store_stream(&cell_of[p[u]], m[u].cell);
       store_stream(&rank_of[p[u]], k);
@@ -912,14 +914,15 @@ __device__ __forceinline__ void integrate_tile(
 template <typename T, int PPT, bool REFLECT>
 __global__ __launch_bounds__(kBlock) void k_integrate(
     const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles,
-    float4 *__restrict__ pos4, const float4 *__restrict__ vel4, const float4 *__restrict__ frc4,
-    float4 *__restrict__ vt4, int32_t *__restrict__ cell_of, int32_t *__restrict__ rank_of,
+    const float4 *pos4, float4 *pos_out, const float4 *__restrict__ vel4,
+    const float4 *__restrict__ frc4, float4 *__restrict__ vt4, int32_t *__restrict__ cell_of,
+    int32_t *__restrict__ rank_of,
     int32_t *__restrict__ count, const uint32_t *__restrict__ bits_base, int use_mask,
     const typename PhiQuad<T>::type *__restrict__ quad_base, Status *st, int64_t NF,
     const int32_t *__restrict__ wcstart) {
   const int tid = xcd_block();
   if (tid >= ntiles) return;
-  integrate_tile<T, PPT, REFLECT>(tid, boxes, tiles, pos4, vel4, frc4, vt4, cell_of, rank_of, count,
+  integrate_tile<T, PPT, REFLECT>(tid, boxes, tiles, pos4, pos_out, vel4, frc4, vt4, cell_of, rank_of, count,
                                   bits_base, use_mask, quad_base, st, NF, wcstart);
 }
 
@@ -1272,69 +1275,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_
 // in list order.  The terms and their order are those of force_tile, so the
 // results are too, bit for bit, and a box gives the same in a context of any size.
 // ---------------------------------------------------------------------------
-constexpr int kWideLanes = 16;
-constexpr int kWideParts = kBlock / kWideLanes;   // particles per block
-constexpr int kWideBatch = 8;                     // candidates per lane in flight
-constexpr int kWideRing = 256;                    // >= 8 x 16 + 15 listed pairs, a power of two
-
-// LDS written by some lanes of a wavefront, read by others of the same one.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The candidates of one particle, by the 16 lanes of its group: their nine
-// neighbour rows (two runs where a row wraps in x) numbered through.
-struct WideRows {
-  int total;        // candidates
-  int off[8];       // number of the first candidate of rows 1 .. 8
-  const int4 *row;  // LDS: {first candidate, run A's first entry, its length, run B's first entry}
-
-  __device__ __forceinline__ void init(const KGeom &G, int co, int cx, int cy, int cz, int g,
-                                       const int32_t *__restrict__ start_all, int4 *lds) {
-    int ta = 0, na = 0, tb = 0, nb = 0;
-    if (g < 9) {
-      const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
-      int qy = cy + g % 3 - 1, qz = cz + g / 3 - 1;
-      qy += qy < 0 ? ny : (qy >= ny ? -ny : 0);
-      qz += qz < 0 ? nz : (qz >= nz ? -nz : 0);
-      const int32_t *s = start_all + co + (qz * ny + qy) * nx;
-      const bool left = cx == 0, right = cx == nx - 1;
-      const int a0 = left ? nx - 1 : (right ? nx - 2 : cx - 1);
-      ta = s[a0];
-      na = s[a0 + (left ? 1 : (right ? 2 : 3))] - ta;
-      if (left || right) {
-        tb = s[0];
-        nb = s[left ? 2 : 1] - tb;
-      }
-    }
-    int incl = na + nb;
-#pragma unroll
-    for (int d = 1; d < kWideLanes; d <<= 1) {
-      const int v = __shfl_up(incl, d, kWideLanes);
-      if (g >= d) incl += v;
-    }
-    total = __shfl(incl, kWideLanes - 1, kWideLanes);
-    if (g < 9) lds[g] = make_int4(incl - na - nb, ta, na, tb);
-    wave_lds_sync();
-    row = lds;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) off[q] = lds[q + 1].x;
-  }
-
-  // run entry of candidate c, 0 <= c < total: in the last row that starts at
-  // or before c (rows without candidates start where the next one does)
-  __device__ __forceinline__ int entry(int c) const {
-    int r = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) r += c >= off[q] ? 1 : 0;
-    const int4 R = row[r];
-    const int u = c - R.x;
-    return u < R.z ? R.y + u : R.w + (u - R.z);
-  }
-};
-
 template <bool INIT, bool SPH>
 __global__ __launch_bounds__(kBlock) void k_force_wide(
     const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles, int64_t NF,
@@ -1716,7 +1656,7 @@ template <typename T, int PPT, bool REFLECT>
 __device__ __attribute__((noinline)) void p_integrate(const PArgs *__restrict__ A0, int tile0) {
   const ArgsPtr A = uniform_args(A0);
   const int tile = uniform_int(tile0);
-  integrate_tile<T, PPT, REFLECT>(tile, A->boxes, A->itiles, A->pos4, A->vel4, A->frc4, A->vt4,
+  integrate_tile<T, PPT, REFLECT>(tile, A->boxes, A->itiles, A->pos4, A->pos4, A->vel4, A->frc4, A->vt4,
                                   A->cell_of, A->rank_of, A->count, A->bits, A->use_mask,
                                   (const typename PhiQuad<T>::type *)A->quad, A->st, A->NF,
                                   A->wcstart);
@@ -2044,14 +1984,15 @@ hipError_t launch_build_quad(hipStream_t s, const KGeom &G, const void *grid, in
 }
 
 hipError_t launch_integrate(hipStream_t s, int ppt, const Box *boxes, const Tile *tiles,
-                            int ntiles, float4 *pos4, const float4 *vel4, const float4 *frc4,
-                            float4 *vt4, int32_t *cell_of, int32_t *rank_of, int32_t *count,
+                            int ntiles, const float4 *pos4, float4 *pos_out, const float4 *vel4,
+                            const float4 *frc4, float4 *vt4, int32_t *cell_of, int32_t *rank_of,
+                            int32_t *count,
                             const uint32_t *bits, int use_mask, const void *quad, int grid_f64,
                             Status *st, int64_t NF, const int32_t *wcstart, int reflect) {
   if (ntiles <= 0) return hipSuccess;
   const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
 #define DPD_INTEGRATE(T, K, R)                                                                   \
-  k_integrate<T, K, R><<<nb, kBlock, 0, s>>>(boxes, tiles, ntiles, pos4, vel4, frc4, vt4,       \
+  k_integrate<T, K, R><<<nb, kBlock, 0, s>>>(boxes, tiles, ntiles, pos4, pos_out, vel4, frc4, vt4, \
                                              cell_of, rank_of, count, bits, use_mask,           \
                                              (const typename PhiQuad<T>::type *)quad, st, NF,   \
                                              wcstart)
@@ -2098,8 +2039,6 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
 #undef DPD_FORCE
   return hipGetLastError();
 }
-
-int wide_parts() { return kWideParts; }
 
 hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,
                              int64_t NF, int init, const float4 *pos4, const float4 *vt4,
