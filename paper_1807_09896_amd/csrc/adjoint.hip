@@ -14,6 +14,8 @@
 // order of step t, which is the slot order of step t - 1.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace dpd {
@@ -78,7 +80,11 @@ __device__ __forceinline__ void block_add3(double a, double b, double c, double 
 // ---------------------------------------------------------------------------
 // Window observable
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlockA) void k_obs(int64_t nf, const float4 *__restrict__ pos4,
+// The states of a window, `per` entries of (state, particle) per block: the
+// blocks' bins meet in global memory once per block, so few blocks with many
+// entries each.
+__global__ __launch_bounds__(kBlockA) void k_obs(int64_t nf, int64_t total, int64_t per,
+                                                 int64_t stride, const float4 *__restrict__ pos4,
                                                  const float4 *__restrict__ vel4, int axis,
                                                  int nbins, float scale, double *sums,
                                                  unsigned long long *counts) {
@@ -89,11 +95,16 @@ __global__ __launch_bounds__(kBlockA) void k_obs(int64_t nf, const float4 *__res
     s_cnt[b] = 0u;
   }
   __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nf; p += stride) {
-    const float4 x = pos4[p];
+  const int64_t first = (int64_t)blockIdx.x * per, last = min(total, first + per);
+  int64_t at = first + threadIdx.x, state = at / nf, p = at - state * nf;
+  for (; at < last; at += kBlockA, p += kBlockA) {
+    while (p >= nf) {
+      p -= nf;
+      ++state;
+    }
+    const float4 x = pos4[state * stride + p];
     const int b = bin_of(axis_of(x, axis), scale, nbins);
-    atomicAdd(&s_sum[b], (double)vel4[p].x);
+    atomicAdd(&s_sum[b], (double)vel4[state * stride + p].x);
     atomicAdd(&s_cnt[b], 1u);
   }
   __syncthreads();
@@ -101,6 +112,27 @@ __global__ __launch_bounds__(kBlockA) void k_obs(int64_t nf, const float4 *__res
     if (s_cnt[b]) {
       atomicAdd(&sums[b], s_sum[b]);
       atomicAdd(&counts[b], (unsigned long long)s_cnt[b]);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlockA) void k_store_walls(int64_t nrec, int nsteps, int64_t stride,
+                                                         const float4 *__restrict__ pos,
+                                                         const float4 *__restrict__ vt,
+                                                         float4 *pos_out, float4 *vt_out,
+                                                         int64_t run_stride, int32_t *slack,
+                                                         int32_t pad) {
+  const int64_t w = (int64_t)blockIdx.x * kBlockA + threadIdx.x;
+  float4 x, v;
+  if (w < nrec) {
+    x = pos[w];
+    v = vt[w];
+  }
+  for (int64_t t = blockIdx.y; t < nsteps; t += gridDim.y) {
+    if (w < kIdxSlack) slack[t * run_stride + w] = pad;
+    if (w < nrec) {
+      pos_out[t * stride + w] = x;
+      vt_out[t * stride + w] = v;
     }
   }
 }
@@ -562,13 +594,25 @@ __global__ __launch_bounds__(6 * 64) void k_reduce_partials(int nb_f,
 
 }  // namespace
 
-hipError_t launch_obs(hipStream_t s, int64_t nf, const float4 *pos4, const float4 *vel4,
-                      int axis, int nbins, float scale, double *sums,
+hipError_t launch_obs(hipStream_t s, int64_t nf, int nstates, int64_t stride, const float4 *pos4,
+                      const float4 *vel4, int axis, int nbins, float scale, double *sums,
                       unsigned long long *counts) {
-  if (nf <= 0) return hipSuccess;
-  unsigned nb = grid_a(nf);
-  if (nb > 512) nb = 512;
-  k_obs<<<nb, kBlockA, 0, s>>>(nf, pos4, vel4, axis, nbins, scale, sums, counts);
+  if (nf <= 0 || nstates <= 0) return hipSuccess;
+  // a block per 1,024 entries, at most 512 blocks
+  const int64_t total = nf * nstates;
+  const int64_t nb = std::min<int64_t>(512, (total + 1023) / 1024);
+  k_obs<<<(unsigned)nb, kBlockA, 0, s>>>(nf, total, (total + nb - 1) / nb, stride, pos4, vel4,
+                                         axis, nbins, scale, sums, counts);
+  return hipGetLastError();
+}
+
+hipError_t launch_store_walls(hipStream_t s, int64_t nrec, int nsteps, int64_t stride,
+                              const float4 *pos, const float4 *vt, float4 *pos_out,
+                              float4 *vt_out, int64_t run_stride, int32_t *slack, int32_t pad) {
+  if (nsteps <= 0) return hipSuccess;
+  const dim3 grid(grid_a(std::max<int64_t>(nrec, kIdxSlack)), (unsigned)std::min(nsteps, 64));
+  k_store_walls<<<grid, kBlockA, 0, s>>>(nrec, nsteps, stride, pos, vt, pos_out, vt_out, run_stride,
+                                         slack, pad);
   return hipGetLastError();
 }
 
