@@ -104,7 +104,7 @@ struct dpd_ctx {
   Box *boxes = nullptr;
   int ppt = 2, fblock = 256;            // launch shapes (autotuned)
   bool wide = false;      // pair forces with 16 lanes per particle (use_wide)
-  bool box_list = false;  // cell list of every box in one launch (use_box_list)
+  int box_list = 0;       // blocks per box of the one-launch cell list, 0: not used (box_parts)
   Tile *itiles = nullptr, *ftiles = nullptr;
   int n_itiles = 0, n_ftiles = 0;
   int itiles_cap = 0, ftiles_cap = 0;
@@ -427,14 +427,21 @@ int default_ppt(const dpd_ctx *c) {
 constexpr int64_t kWideMax = 65536;
 bool use_wide(const dpd_ctx *c) { return c->NF <= kWideMax; }
 
-// The cell list of every box by one block each (k_cells_box), where every box
-// fits its LDS.  Measured against the four launches (whole step, us): 24 / 31
-// at 2,000 particles in the box, 31 / 38 at 8,400, 35 / 38 at 12,000, and even
-// at 16,000, next to the largest that fits.
-bool use_box_list(const dpd_ctx *c) {
-  for (const Replica &p : c->rep)
-    if (p.ncell > dpd::kBoxCells || p.nf > dpd::kBoxFluid) return false;
-  return true;
+// Blocks per box of the one-launch cell list (k_cells_box); 0 where some box does
+// not fit its LDS, or where the brick kernel needs the separate launches' arrays.
+// 256 CUs hold one such block each, so the boxes share 256, up to 16 a box (a box of
+// at most 1,024 particles is one round of one block's threads).  Whole step, us,
+// four launches / 1 / 4 / 16 blocks per box: 29.0 / 24.4 / 22.9 / 22.9 at 2,000
+// particles, 36.1 / 31.1 / 26.9 / 24.9 at 8,400, 38.3 / 39.9 / 31.1 / 27.9 at 16,000,
+// 41.3 / 48.1 / 35.9 / 32.2 at 22,000; 64 boxes: 127 / 126 / 115 / 131.
+int box_parts(const dpd_ctx *c) {
+  if (c->nbricks > 0) return 0;
+  int64_t most = 0;
+  for (const Replica &p : c->rep) {
+    if (p.ncell > dpd::kBoxCells || p.nf > dpd::kBoxFluid) return 0;
+    most = std::max(most, p.nf);
+  }
+  return most <= 1024 ? 1 : std::max(1, std::min(16, 256 / c->R));
 }
 
 // Launch shapes: particles per thread of integrate (1, 2 or 4; at most 2
@@ -670,15 +677,19 @@ int bin_all(dpd_ctx *c, hipStream_t s) {
 // state loaded from outside) instead of by storage index; bump: the force
 // evaluation index advances in the same launches; codes = false: positions
 // elsewhere than pos[cur] (the adjoint window's), whose pair walk does not
-// read the codes.
+// read the codes; force_next: force_pass follows on the stream, which clears the
+// cell counts where the list's own launch cannot.
 int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
-                      unsigned long long *bump = nullptr, bool codes = true) {
+                      unsigned long long *bump = nullptr, bool codes = true,
+                      bool force_next = false) {
   if (c->box_list && !key4) {
     HIP_TRY(c, timed(c, s, K_SORT, [&] {
-              return dpd::launch_cells_box(s, c->boxes, c->R, c->NF, c->cell_of, c->rank_of,
-                                           c->count, c->wcstart, c->cstart, c->start_all,
-                                           c->fluid_off, c->idx, c->idx_all, c->wcell, bump);
+              return dpd::launch_cells_box(s, c->boxes, c->R, c->box_list, c->NF, c->cell_of, c->rank_of,
+                                           c->count, c->wcstart, c->start_all, c->idx,
+                                           c->idx_all, c->wcell, bump);
             }));
+    if (c->box_list > 1 && !force_next)
+      HIP_TRY(c, dpd::launch_fill_zero(s, c->count, 4 * (size_t)c->NCELL));
   } else {
     HIP_TRY(c, timed(c, s, K_SCAN_REDUCE, [&] {
               return dpd::launch_scan_reduce(s, c->NCELL, c->count, c->bsum);
@@ -708,18 +719,20 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
 // Forces at the current state in sorted order; init = 1 keeps velocities.
 int force_pass(dpd_ctx *c, hipStream_t s, int init) {
   const int a = c->cur, b = 1 - c->cur;
+  int32_t *const clear = c->box_list > 1 ? c->count : nullptr;
   if (c->n_otiles > 0)
     HIP_TRY(c, timed(c, s, K_FORCE, [&] {
               if (c->wide)
                 return dpd::launch_force_wide(s, c->boxes, c->otiles, c->n_otiles, c->NF, init,
                                               c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
                                               c->idx_all, c->start_all, c->pos[b], c->vel[b],
-                                              c->frc[b], c->dk, c->status, c->sph ? 1 : 0);
+                                              c->frc[b], c->dk, c->status, c->sph ? 1 : 0,
+                                              clear, (int32_t)c->NCELL);
               return dpd::launch_force(s, c->fblock, c->boxes, c->otiles, c->n_otiles, c->NF,
                                        (int32_t)(c->NF + c->NW), (int32_t)c->NCELL, init,
                                        c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
                                        c->idx_all, c->start_all, c->cq, c->pos[b], c->vel[b],
-                                       c->frc[b], c->dk, c->status, c->sph ? 1 : 0);
+                                       c->frc[b], c->dk, c->status, c->sph ? 1 : 0, clear);
             }));
   if (c->nbricks > 0)
     HIP_TRY(c, timed(c, s, K_FORCE, [&] {
@@ -796,7 +809,7 @@ int enqueue_step(dpd_ctx *c, hipStream_t s) {
     int rc = wall_pass(c, s, 1);
     if (rc) return rc;
   }
-  int rc = scan_scatter_sort(c, s, nullptr, c->dk);
+  int rc = scan_scatter_sort(c, s, nullptr, c->dk, true, true);
   if (rc) return rc;
   return force_pass(c, s, 0);
 }
@@ -1304,13 +1317,13 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   }
   rc = build_bricks(c);
   c->wide = use_wide(c);
-  c->box_list = use_box_list(c);
+  c->box_list = box_parts(c);
   if (!rc) rc = set_shapes(c, default_ppt(c), 256);
   if (rc) return bail(rc);
   c->cur = 0;
   c->k = 0;
   rc = bin_all(c, c->stream);
-  if (!rc) rc = scan_scatter_sort(c, c->stream);
+  if (!rc) rc = scan_scatter_sort(c, c->stream, nullptr, nullptr, true, true);
   if (!rc) rc = force_pass(c, c->stream, 1);
   if (!rc) {
     hipError_t e = hipStreamSynchronize(c->stream);
@@ -1387,7 +1400,7 @@ int load_state(dpd_ctx *c, const float4 *src) {
 // parameters and k: f = F(r, vt = v) + g (as at create).
 int refresh_forces(dpd_ctx *c) {
   int rc = bin_all(c, c->stream);
-  if (!rc) rc = scan_scatter_sort(c, c->stream);
+  if (!rc) rc = scan_scatter_sort(c, c->stream, nullptr, nullptr, true, true);
   if (rc) return rc;
   HIP_TRY(c, dpd::launch_vt_from_v(c->stream, c->NF, c->vel[c->cur], c->vt));
   return force_pass(c, c->stream, 1);
@@ -1526,7 +1539,7 @@ int stored_window_step(dpd_ctx *c, int t, bool last) {
                                            c->rank_of, c->count, c->bits, c->use_mask, c->quad,
                                            c->grid_f64, c->status, NF, c->wcstart, 0);
             }));
-    int rc = scan_scatter_sort(c, c->stream, nullptr, c->dk);
+    int rc = scan_scatter_sort(c, c->stream, nullptr, c->dk, true, true);
     return rc ? rc : force_pass(c, c->stream, 0);
   };
   const int rc = launches();

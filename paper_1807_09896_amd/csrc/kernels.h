@@ -55,14 +55,15 @@ hipError_t launch_sort_cells(hipStream_t s, int64_t ncell, const int32_t *start,
 hipError_t launch_sort_wall_cells(hipStream_t s, int64_t ncell, const int32_t *start,
                                   int32_t *idx, int32_t *cell_out);
 // The cell list of every box (scan, scatter and sort above, with the wall part
-// of the merged runs and the advance of dk) in one launch, one block per box;
-// each box has at most kBoxCells cells and kBoxFluid fluid particles.
-constexpr int kBoxCells = 14336, kBoxFluid = 18000;   // 63 KB of LDS
-hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int64_t NF,
+// of the merged runs and the advance of dk, without cstart and fluid_off) in one
+// launch, `parts` blocks per box; each box has at most kBoxCells cells and
+// kBoxFluid fluid particles.  With parts > 1 count is left as it is: the pair
+// force that follows clears it (its `clear`), or the caller.
+constexpr int kBoxCells = 16384, kBoxFluid = 24576;   // 128 KB of LDS
+hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int parts, int64_t NF,
                             const int32_t *cell_of, const int32_t *rank_of, int32_t *count,
-                            const int32_t *wcstart, int32_t *cstart, int32_t *start_all,
-                            int32_t *fluid_off, int32_t *idx, int32_t *idx_all,
-                            const int32_t *wcell, unsigned long long *dk);
+                            const int32_t *wcstart, int32_t *start_all, int32_t *idx,
+                            int32_t *idx_all, const int32_t *wcell, unsigned long long *dk);
 // Coarse position codes of the merged runs, cq[t] from pos4[idx_all[t]] for
 // t < n (one word per entry), which the pair kernel's candidate pre-test
 // reads; n = NF + NW, after the scatter and sort.
@@ -170,14 +171,15 @@ hipError_t launch_import_walls(hipStream_t s, int64_t nw, float4 *walls, const f
 // Pair forces (Eq. 3-10) + body force + velocity update over tiles of up to
 // `block` (128 or 256) fluid slots, writing the state in cell-sorted slot
 // order.  pos4 and vt4 hold NF fluid entries, the walls and the pad entry
-// (index pad).  init = 1: forces only (velocities unchanged).
+// (index pad).  init = 1: forces only (velocities unchanged).  clear: the cell
+// counts (ncell_all), cleared for the next step's binning, or null.
 hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *tiles,
                         int ntiles, int64_t NF, int32_t pad, int32_t ncell_all, int init,
                         const float4 *pos4, const float4 *vt4, const float4 *vel4,
                         const float4 *frc4, const int32_t *idx, const int32_t *idx_all,
                         const int32_t *start_all, const uint32_t *cq,
                         float4 *pos_out, float4 *vel_out, float4 *frc_out,
-                        const unsigned long long *dk, Status *st, int sph);
+                        const unsigned long long *dk, Status *st, int sph, int32_t *clear);
 
 // The same pair forces with 16 lanes per particle, for small contexts, over
 // tiles of up to kWideParts fluid slots.  It reads no coarse codes.
@@ -186,7 +188,7 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
                              const float4 *vel4, const float4 *frc4, const int32_t *idx,
                              const int32_t *idx_all, const int32_t *start_all, float4 *pos_out,
                              float4 *vel_out, float4 *frc_out, const unsigned long long *dk,
-                             Status *st, int sph);
+                             Status *st, int sph, int32_t *clear, int32_t ncell_all);
 
 // The same pair forces, body force and velocity update for the boxes cut
 // into bricks: one block per brick stages the brick's cells and a one-cell

@@ -450,40 +450,64 @@ __global__ void k_sort_wall_cells(int64_t ncell, const int32_t *__restrict__ sta
   for (int i = a; i < b; ++i) cell_out[i] = (int32_t)c;
 }
 
-// The whole cell list of small boxes in one launch, one block per box: the
-// exclusive scan of the box's cell counts, the scatter of its fluid and walls
-// and the per-cell sort, with the starts and the fluid's slots in LDS as 16-bit
-// numbers within the box.  The four separate launches (scan_reduce, scan_down,
-// scatter, sort_cells) take 4 to 5 us each, most of it the launch.  Every list
-// has one entry order (cells in order, each sorted by storage index), so the
-// result is theirs exactly.
+// The whole cell list of small boxes in one launch: the exclusive scan of a
+// box's cell counts, the scatter of its fluid and walls and the per-cell sort, in
+// LDS as 16-bit numbers within the box.  The four separate launches
+// (scan_reduce, scan_down, scatter, sort_cells) take 4 to 5 us each, most of it
+// the launch.  Every list has one entry order (cells in order, each sorted by
+// storage index), so the result is theirs exactly (cstart and fluid_off, which
+// only those launches and the brick kernel read, are not written).
+//
+// gridDim.y blocks share a box, each for an equal part of its cells: it adds up
+// the counts before its part, scans the part, and takes the particles whose cell
+// lies there from the whole box.  With one block per box the sort and the LDS
+// traffic of one CU bound it (20 us at 16,000 particles); with 16 it is the chain
+// of phases (8 us).  A single block clears the counts for the next step; blocks that
+// share a box must not (others may still read), so the pair force after them does.
 constexpr int kBoxThreads = 1024;
 
+// The 19-exchange network over 8 keys.
+__device__ __forceinline__ void sort8(uint32_t (&v)[8]) {
+  constexpr int net[19][2] = {{0, 2}, {1, 3}, {4, 6}, {5, 7}, {0, 4}, {1, 5}, {2, 6},
+                              {3, 7}, {0, 1}, {2, 3}, {4, 5}, {6, 7}, {2, 4}, {3, 5},
+                              {1, 4}, {3, 6}, {1, 2}, {3, 4}, {5, 6}};
+#pragma unroll
+  for (int q = 0; q < 19; ++q) {
+    const uint32_t x = v[net[q][0]], y = v[net[q][1]];
+    v[net[q][0]] = min(x, y);
+    v[net[q][1]] = max(x, y);
+  }
+}
+
 __global__ __launch_bounds__(kBoxThreads) void k_cells_box(
-    const Box *__restrict__ boxes, int nbox, int64_t NF, const int32_t *__restrict__ cell_of,
+    const Box *__restrict__ boxes, int64_t NF, const int32_t *__restrict__ cell_of,
     const int32_t *__restrict__ rank_of, int32_t *__restrict__ count,
-    const int32_t *__restrict__ wcstart, int32_t *__restrict__ cstart,
-    int32_t *__restrict__ start_all, int32_t *__restrict__ fluid_off, int32_t *__restrict__ idx,
-    int32_t *__restrict__ idx_all, const int32_t *__restrict__ wcell,
+    const int32_t *__restrict__ wcstart, int32_t *__restrict__ start_all,
+    int32_t *__restrict__ idx, int32_t *__restrict__ idx_all, const int32_t *__restrict__ wcell,
     unsigned long long *__restrict__ dk) {
   __shared__ uint16_t start[kBoxCells + 1];
-  __shared__ uint16_t slot[kBoxFluid];
-  __shared__ int wave_total[kBoxThreads / 64];
-  const int t = (int)threadIdx.x;
+  __shared__ uint16_t slot[kBoxFluid], cell[kBoxFluid];   // of each slot: particle and its cell
+  __shared__ int wave_sum[kBoxThreads / 64], wave_before[kBoxThreads / 64];
+  const int t = (int)threadIdx.x, parts = (int)gridDim.y, part = (int)blockIdx.y;
   const Box &B = boxes[blockIdx.x];
   const int co = (int)B.co, nc = (int)B.ncell, fo = (int)B.fo, nf = (int)B.nf;
-  const int wo = (int)B.wo, nw = (int)B.nw;
-  if (dk && blockIdx.x == 0 && t == 0) *dk += 1ull;
+  const int lo = (int)((int64_t)nc * part / parts), n = (int)((int64_t)nc * (part + 1) / parts) - lo;
+  if (dk && blockIdx.x == 0 && part == 0 && t == 0) *dk += 1ull;
+  int before = 0;   // particles in the cells before the part
 #pragma unroll 4
-  for (int c = t; c < nc; c += kBoxThreads) {
-    start[c] = (uint16_t)count[co + c];
-    count[co + c] = 0;
+  for (int c = t; c < lo; c += kBoxThreads) before += count[co + c];
+#pragma unroll 4
+  for (int c = t; c < n; c += kBoxThreads) {
+    start[c] = (uint16_t)count[co + lo + c];
+    if (parts == 1) count[co + c] = 0;
   }
+  for (int m = 32; m > 0; m >>= 1) before += __shfl_xor(before, m, 64);
+  if ((t & 63) == 0) wave_before[t >> 6] = before;
   __syncthreads();
   // each thread's run of cells (an odd number, against bank conflicts), after
   // those of the threads before it
-  const int per = ((nc + kBoxThreads - 1) / kBoxThreads) | 1;
-  const int c0 = min(t * per, nc), c1 = min(c0 + per, nc);
+  const int per = ((n + kBoxThreads - 1) / kBoxThreads) | 1;
+  const int c0 = min(t * per, n), c1 = min(c0 + per, n);
   int sum = 0;
   for (int c = c0; c < c1; ++c) sum += start[c];
   int incl = sum;
@@ -491,47 +515,68 @@ __global__ __launch_bounds__(kBoxThreads) void k_cells_box(
     const int v = __shfl_up(incl, d, 64);
     if ((t & 63) >= d) incl += v;
   }
-  if ((t & 63) == 63) wave_total[t >> 6] = incl;
+  if ((t & 63) == 63) wave_sum[t >> 6] = incl;
   __syncthreads();
-  int run = incl - sum;
-  for (int w = 0; w < (t >> 6); ++w) run += wave_total[w];
+  int run = incl - sum, own = 0;
+  before = 0;
+  for (int w = 0; w < kBoxThreads / 64; ++w) {
+    if (w < (t >> 6)) run += wave_sum[w];
+    own += wave_sum[w];
+    before += wave_before[w];
+  }
   for (int c = c0; c < c1; ++c) {
-    const int n = start[c];
+    const int k = start[c];
     start[c] = (uint16_t)run;
-    run += n;
+    run += k;
   }
-  if (t == 0) start[nc] = (uint16_t)nf;
+  if (t == 0) start[n] = (uint16_t)own;
   __syncthreads();
+  const int first = fo + before;   // the part's first slot
+  // eight rounds of the box's particles at a time (past the end: the last one
+  // again), so that one round trip to memory serves eight
+  for (int p0 = t; p0 < nf; p0 += 8 * kBoxThreads) {
+    int c[8], r[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int p = fo + min(p0 + u * kBoxThreads, nf - 1);
+      c[u] = cell_of[p] - co - lo;
+      r[u] = rank_of[p];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int p = p0 + u * kBoxThreads;
+      if (p < nf && c[u] >= 0 && c[u] < n) {
+        const int s = start[c[u]] + r[u];
+        slot[s] = (uint16_t)p;
+        cell[s] = (uint16_t)c[u];
+      }
+    }
+  }
+  const int w1 = wcstart[co + lo + n];
 #pragma unroll 4
-  for (int p = t; p < nf; p += kBoxThreads)
-    slot[start[cell_of[fo + p] - co] + rank_of[fo + p]] = (uint16_t)p;
-#pragma unroll 4
-  for (int w = wo + t; w < wo + nw; w += kBoxThreads) {
+  for (int w = wcstart[co + lo] + t; w < w1; w += kBoxThreads) {
     // entry start_all[c] + (w - wcstart[c]) of the merged runs
-    idx_all[fo + start[wcell[w] - co] + w] = (int)NF + w;
+    idx_all[first + start[wcell[w] - co - lo] + w] = (int)NF + w;
   }
+#pragma unroll 4
+  for (int c = t; c < n; c += kBoxThreads)
+    start_all[co + lo + c] = first + start[c] + wcstart[co + lo + c];
+  if (blockIdx.x == gridDim.x - 1 && part == parts - 1 && t == 0)
+    start_all[co + nc] = fo + nf + wcstart[co + nc];
   __syncthreads();
-#pragma unroll 2
-  for (int c = t; c < nc; c += kBoxThreads) {
-    const int a = start[c], n = start[c + 1] - a;
-    const int w0 = wcstart[co + c], w1 = wcstart[co + c + 1];
-    cstart[co + c] = fo + a;
-    start_all[co + c] = fo + a + w0;
-    fluid_off[co + c] = fo + a + w1;
-    int32_t *const out = idx + fo + a, *const all = idx_all + fo + a + w1;
-    if (n <= 8) {
+  for (int c = t; c < n; c += kBoxThreads) {
+    const int a = start[c], k = start[c + 1] - a;
+    if (k < 2) continue;
+    if (k <= 8) {
       uint32_t v[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = i < n ? (uint32_t)slot[a + i] : 0xffffu;
-      sort_network<8>(v);
+      for (int i = 0; i < 8; ++i) v[i] = i < k ? (uint32_t)slot[a + i] : 0xffffu;
+      sort8(v);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (i < n) {
-          out[i] = fo + (int)v[i];
-          all[i] = fo + (int)v[i];
-        }
+        if (i < k) slot[a + i] = (uint16_t)v[i];
     } else {
-      for (int i = a + 1; i < a + n; ++i) {
+      for (int i = a + 1; i < a + k; ++i) {
         const uint16_t v = slot[i];
         int j = i - 1;
         while (j >= a && slot[j] > v) {
@@ -540,15 +585,14 @@ __global__ __launch_bounds__(kBoxThreads) void k_cells_box(
         }
         slot[j + 1] = v;
       }
-      for (int i = 0; i < n; ++i) {
-        out[i] = fo + slot[a + i];
-        all[i] = fo + slot[a + i];
-      }
     }
   }
-  if ((int)blockIdx.x == nbox - 1 && t == 0) {
-    cstart[co + nc] = fo + nf;
-    start_all[co + nc] = fo + nf + wcstart[co + nc];
+  __syncthreads();
+#pragma unroll 4
+  for (int s = t; s < own; s += kBoxThreads) {
+    const int i = fo + slot[s];
+    idx[first + s] = i;
+    idx_all[first + s + wcstart[co + lo + cell[s] + 1]] = i;
   }
 }
 
@@ -1243,6 +1287,15 @@ __device__ __forceinline__ void force_tile(
   store_stream(&frc_out[s], fin.frc);
 }
 
+// The cell counts cleared for the next step's binning, by the blocks of a pair
+// force that follows a cell list whose blocks could not (clear: null where they did).
+__device__ __forceinline__ void clear_counts(int32_t *__restrict__ clear, int n) {
+  if (!clear) return;
+  for (int c = (int)(blockIdx.x * blockDim.x + threadIdx.x); c < n;
+       c += (int)(gridDim.x * blockDim.x))
+    clear[c] = 0;
+}
+
 // Six wavefronts per SIMD: at most 80 VGPRs, so the walk and the pair pass
 // run without register spills, and six blocks' lists fit in LDS.
 template <bool INIT, int BS, bool SPH>
@@ -1254,8 +1307,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_
     const int32_t *__restrict__ idx_all, const int32_t *__restrict__ start_all,
     const uint32_t *__restrict__ cq,
     float4 *__restrict__ pos_out, float4 *__restrict__ vel_out, float4 *__restrict__ frc_out,
-    const unsigned long long *__restrict__ dk, Status *st) {
+    const unsigned long long *__restrict__ dk, Status *st, int32_t *__restrict__ clear) {
   __shared__ uint32_t list[kListCap * BS];
+  clear_counts(clear, ncell_all);
   const int tid = xcd_block();
   if (tid >= ntiles) return;
   force_tile<INIT, BS, SPH>(tid, list, boxes, tiles, NF, pad, ncell_all, pos4, vt4, vel4, frc4,
@@ -1283,7 +1337,9 @@ __global__ __launch_bounds__(kBlock) void k_force_wide(
     const int32_t *__restrict__ idx, const int32_t *__restrict__ idx_all,
     const int32_t *__restrict__ start_all, float4 *__restrict__ pos_out,
     float4 *__restrict__ vel_out, float4 *__restrict__ frc_out,
-    const unsigned long long *__restrict__ dk, Status *st) {
+    const unsigned long long *__restrict__ dk, Status *st, int32_t *__restrict__ clear,
+    int ncell_all) {
+  clear_counts(clear, ncell_all);
   // padded so that the four groups of a wavefront use different banks
   __shared__ int ring[kWideParts][kWideRing + 8];
   __shared__ float4 term[kWideParts][kWideLanes + 1];
@@ -2020,14 +2076,14 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
                         const int32_t *idx, const int32_t *idx_all, const int32_t *start_all,
                         const uint32_t *cq,
                         float4 *pos_out, float4 *vel_out, float4 *frc_out,
-                        const unsigned long long *dk, Status *st, int sph) {
+                        const unsigned long long *dk, Status *st, int sph, int32_t *clear) {
   if (ntiles <= 0) return hipSuccess;
   if (!cq) return hipErrorInvalidValue;
   const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
 #define DPD_FORCE(I, BS, S)                                                                      \
   k_force<I, BS, S><<<nb, BS, 0, s>>>(boxes, tiles, ntiles, NF, pad, ncell_all, pos4, vt4, vel4, \
                                       frc4, idx, idx_all, start_all, cq, pos_out, vel_out,       \
-                                      frc_out, dk, st)
+                                      frc_out, dk, st, clear)
 #define DPD_FORCE_S(I, BS) \
   if (sph) DPD_FORCE(I, BS, true); else DPD_FORCE(I, BS, false)
   if (block == 128) {
@@ -2045,12 +2101,13 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
                              const float4 *vel4, const float4 *frc4, const int32_t *idx,
                              const int32_t *idx_all, const int32_t *start_all, float4 *pos_out,
                              float4 *vel_out, float4 *frc_out, const unsigned long long *dk,
-                             Status *st, int sph) {
+                             Status *st, int sph, int32_t *clear, int32_t ncell_all) {
   if (ntiles <= 0) return hipSuccess;
   const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
 #define DPD_WIDE(I, S)                                                                            \
   k_force_wide<I, S><<<nb, kBlock, 0, s>>>(boxes, tiles, ntiles, NF, pos4, vt4, vel4, frc4, idx, \
-                                           idx_all, start_all, pos_out, vel_out, frc_out, dk, st)
+                                           idx_all, start_all, pos_out, vel_out, frc_out, dk, st, clear, \
+                                           ncell_all)
   if (init) {
     if (sph) DPD_WIDE(true, true); else DPD_WIDE(true, false);
   } else {
@@ -2060,15 +2117,14 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
   return hipGetLastError();
 }
 
-hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int64_t NF,
+hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int parts, int64_t NF,
                             const int32_t *cell_of, const int32_t *rank_of, int32_t *count,
-                            const int32_t *wcstart, int32_t *cstart, int32_t *start_all,
-                            int32_t *fluid_off, int32_t *idx, int32_t *idx_all,
-                            const int32_t *wcell, unsigned long long *dk) {
+                            const int32_t *wcstart, int32_t *start_all, int32_t *idx,
+                            int32_t *idx_all, const int32_t *wcell, unsigned long long *dk) {
   if (nbox <= 0) return hipSuccess;
-  k_cells_box<<<(unsigned)nbox, kBoxThreads, 0, s>>>(boxes, nbox, NF, cell_of, rank_of, count,
-                                                     wcstart, cstart, start_all, fluid_off, idx,
-                                                     idx_all, wcell, dk);
+  const dim3 grid((unsigned)nbox, (unsigned)parts);
+  k_cells_box<<<grid, kBoxThreads, 0, s>>>(boxes, NF, cell_of, rank_of, count, wcstart, start_all,
+                                           idx, idx_all, wcell, dk);
   return hipGetLastError();
 }
 

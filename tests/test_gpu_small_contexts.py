@@ -41,6 +41,14 @@ def _edge_box(cells, fluid):
     return s
 
 
+def _squeezed():
+    """1,400 particles in one corner of an otherwise empty box of 1,331 cells."""
+    s = _edge_box((11, 11, 11), 1400)
+    s.pos[:] = np.mod(s.pos * np.float32(0.27), np.float32(3.0))
+    s.params = dict(s.params, a=[[0.5, 0.5], [0.5, 0.5]], dt=0.002)
+    return s
+
+
 def _sph(s):
     s.params = dict(s.params, sph=workloads.sph_force(), kBT=0.5, dt=0.005)
     return s
@@ -62,10 +70,15 @@ BOXES = {
     "couette": lambda: workloads.couette_system(L=(8.0, 6.0, 7.0), seed=15, specular=True),
     # the largest box of the one-launch cell list, in particles and in cells,
     # and one past each
-    "fluid_max": lambda: _edge_box((18, 18, 19), 18000),
-    "fluid_over": lambda: _edge_box((18, 18, 19), 18001),
-    "cells_max": lambda: _edge_box((32, 28, 16), 9000),
-    "cells_over": lambda: _edge_box((31, 31, 15), 9000),
+    "fluid_max": lambda: _edge_box((18, 18, 19), 24576),
+    "fluid_over": lambda: _edge_box((18, 18, 19), 24577),
+    "cells_max": lambda: _edge_box((32, 32, 16), 9000),
+    "cells_over": lambda: _edge_box((33, 32, 16), 9000),
+    # either side of one block per box
+    "part_one": lambda: _edge_box((7, 8, 6), 1024),
+    "part_many": lambda: _edge_box((7, 8, 6), 1025),
+    # all particles in a few cells of one block's part of the box
+    "corner": lambda: _squeezed(),
 }
 
 
@@ -86,6 +99,27 @@ def test_small_context_bits(dpd, filler, name):
     assert np.array_equal(sorted_pairs(pa), sorted_pairs(pb))
     alone.close()
     beside.close()
+
+
+@pytest.mark.parametrize("count", [3, 70, 130])
+def test_blocks_per_box(dpd, count):
+    """Batches whose boxes are shared by 16, 3 and one block each."""
+    import torch
+    boxes = [_edge_box((7, 8, 6), 1100 + 3 * r) for r in range(count)]
+    batch = dpd.Simulation(boxes)
+    batch.step(4)
+    for r in (0, count // 2, count - 1):
+        alone = dpd.Simulation(boxes[r])
+        alone.step(4)
+        a, b = alone.state(0), batch.state(r)
+        for k in a:
+            assert torch.equal(a[k], b[k]), (count, r, k)
+        alone.close()
+    # counts are clear again after calls that build a list without a force
+    assert batch.pairs(0).shape == batch.pairs(0).shape
+    batch.step(2)
+    batch.sync()
+    batch.close()
 
 
 def test_small_context_graph_replays(dpd):
