@@ -115,14 +115,18 @@ struct PItem {
 // 0xCD9E8D57 and mixes their halves with the other words and the key; the
 // key is bumped by 0x9E3779B9, 0xBB67AE85 between rounds.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);   // one instruction
+}
+
 __device__ __forceinline__ void philox10(uint32_t &c0, uint32_t &c1, uint32_t &c2,
                                          uint32_t &c3, uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
     c0 = n0;
@@ -247,12 +251,21 @@ __device__ __forceinline__ uint32_t qcode3(float x, float y, float z) {
   return qaxis(x) | (qaxis(y) << 11) | (qaxis(z) << 22) | kQGuard;
 }
 
+// v v and v v + c of a 24-bit v, one instruction each (written out, the compiler
+// makes three products and an add of three).
+__device__ __forceinline__ int mul_sq(int v) { return __mul24(v, v); }
+__device__ __forceinline__ int mad_sq(int v, int c) {
+  int r;
+  asm("v_mad_i32_i24 %0, %1, %1, %2" : "=v"(r) : "v"(v), "v"(c));
+  return r;
+}
+
 // |dq|^2 of a candidate's code w against the lane's shifted code q.
 __device__ __forceinline__ uint32_t qdist2(uint32_t w, uint32_t q) {
   const int d = (int)(w - q);
   const int dx = __builtin_amdgcn_sbfe(d, 0, 10), dy = __builtin_amdgcn_sbfe(d, 11, 10),
             dz = __builtin_amdgcn_sbfe(d, 22, 10);
-  return (uint32_t)(dx * dx + dy * dy + dz * dz);
+  return (uint32_t)mad_sq(dx, mad_sq(dy, mul_sq(dz)));
 }
 
 // Threshold of the pre-test for cutoff^2 rc2: keep a candidate iff

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 #include "kernels.h"
@@ -1169,95 +1170,96 @@ __device__ __forceinline__ void force_tile(
   const Ints4 runs(idx_all, pad + kIdxSlack);
   const Ints4 codes((const int32_t *)cq, pad + kIdxSlack);
   const Ints4 starts(start_all, ncell_all + 1 + kStartSlack);
-  const uint32_t qth = qthresh(P.rc2);
+  // (as a scalar, so that its two cases are not tested per candidate)
+  const uint32_t qth = __builtin_amdgcn_readfirstlane(qthresh(P.rc2));
   // this lane's list column as LDS byte offsets: entry q at lane0 + q * BS * 4
   char *const lds = (char *)list;
   const uint32_t lane0 = threadIdx.x * 4u;
   const uint32_t full = lane0 + (uint32_t)((kListCap - kBatch) * BS * 4);
   uint32_t tail = lane0;   // next free entry
+  const int nf32 = (int)NF;
+  // wave-uniform: some lane sees neighbour cells across an edge of the box (or
+  // the axis is so short that half of it is within two cells)
+  const bool edge = wave_any(cx == 0 || cy == 0 || cz == 0 || cx == G.nc[0] - 1 ||
+                             cy == G.nc[1] - 1 || cz == G.nc[2] - 1 || G.nc[0] < 5 ||
+                             G.nc[1] < 5 || G.nc[2] < 5);
   Acc acc = {0.f, 0.f, 0.f};
   // phase B: the listed candidates of this lane, in list (= candidate)
   // order, with the exact decision; the next candidate's data is fetched
-  // while the current one is evaluated
-  auto flush = [&]() {
-    int j = tail > lane0 ? *(const int *)(lds + lane0) : pad;
-    float4 pj = posr[j], vtj = vtr[j];
-    for (uint32_t q = lane0; q < tail; q += BS * 4u) {
-      const uint32_t qn = q + BS * 4u;
-      const int jn = qn < tail ? *(const int *)(lds + qn) : pad;
-      const float4 pjn = posr[jn], vtjn = vtr[jn];
-      const float dx = sep(pi.x, pj.x, G.L[0]);
-      const float dy = sep(pi.y, pj.y, G.L[1]);
-      const float dz = sep(pi.z, pj.z, G.L[2]);
+  // while the current one is evaluated.  Where no lane's cell is at an edge of
+  // the box the separation needs no image (sep's value in that case): 21 of
+  // about 150 instructions a pair.
+  auto pairs_of_list = [&](auto at_edge) {
+    if (tail == lane0) return;
+    const uint32_t last = tail - BS * 4u;
+    uint32_t q = lane0;
+    auto evaluate = [&](int j, const float4 &pj, const float4 &vtj) {
+      const float dx = at_edge.value ? sep(pi.x, pj.x, G.L[0]) : sub_nc(pi.x, pj.x);
+      const float dy = at_edge.value ? sep(pi.y, pj.y, G.L[1]) : sub_nc(pi.y, pj.y);
+      const float dz = at_edge.value ? sep(pi.z, pj.z, G.L[2]) : sub_nc(pi.z, pj.z);
       // the pair decision (r2 > 0 also drops coincident particles, whose
       // force is 0)
       const float r2 = pair_r2(dx, dy, dz);
       if (r2 < P.rc2 && r2 > 0.0f) {
         const PairTerm t = pair_term<SPH>(dx, dy, dz, r2, vti.x - vtj.x, vti.y - vtj.y,
-                                          vti.z - vtj.z, (int64_t)j >= NF, P, gi,
+                                          vti.z - vtj.z, j >= nf32, P, gi,
                                           __float_as_uint(pj.w), klo, khi);
         acc.x = __builtin_fmaf(t.ex, t.mag, acc.x);
         acc.y = __builtin_fmaf(t.ey, t.mag, acc.y);
         acc.z = __builtin_fmaf(t.ez, t.mag, acc.z);
       }
-      j = jn;
-      pj = pjn;
-      vtj = vtjn;
+    };
+    // two sets of registers in turn, so that the fetched pair need not be
+    // copied (8 of 122 vector instructions a pair)
+    int j = *(const int *)(lds + lane0);
+    float4 pj = posr[j], vtj = vtr[j];
+    for (;;) {
+      const int j2 = *(const int *)(lds + min(q + BS * 4u, last));
+      const float4 pj2 = posr[j2], vtj2 = vtr[j2];
+      evaluate(j, pj, vtj);
+      q += BS * 4u;
+      if (q > last) break;
+      j = *(const int *)(lds + min(q + BS * 4u, last));
+      pj = posr[j];
+      vtj = vtr[j];
+      evaluate(j2, pj2, vtj2);
+      q += BS * 4u;
+      if (q > last) break;
     }
     tail = lane0;
   };
-  // Phase A for one neighbour row: the wavefront walks the lane's runs in
-  // lockstep, kBatch run entries per lane and pass (run A, then run B where
-  // the row wraps; a lane moves to B on its own), with qa / qb the lane's
-  // code shifted by the image of run A / B.  Entries past the lane's run are
-  // read (other cells' entries, or the pad) but never listed; neither is
-  // the lane's own particle.  Phase B runs when a lane's list could
-  // overflow in the next pass.
-  auto walk = [&](int t, int t_end, int tb, int tb_end, uint32_t qa, uint32_t qb) {
-    {
-      const bool sw = t >= t_end;
-      t = sw ? tb : t;
-      t_end = sw ? tb_end : t_end;
-      tb = sw ? tb_end : tb;
-      qa = sw ? qb : qa;
-    }
-    for (;;) {
-      while (wave_any(t < t_end) && !wave_any(tail > full)) {
-        const int rem = t_end - t;
-        int jb[kBatch], w[kBatch];
-        runs.load(t, jb);
-        codes.load(t, w);
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const bool keep = qdist2((uint32_t)w[u], qa) <= qth && jb[u] != i && u < rem;
-          *(int *)(lds + tail) = jb[u];
-          tail += keep ? (uint32_t)(BS * 4) : 0u;
-        }
-        t = rem > 0 ? t + kBatch : t;
-        const bool sw = t >= t_end && tb < tb_end;
-        t = sw ? tb : t;
-        t_end = sw ? tb_end : t_end;
-        tb = sw ? tb_end : tb;
-        qa = sw ? qb : qa;
-      }
-      if (!wave_any(t < t_end)) break;
-      flush();
-    }
+  auto flush = [&]() {
+    if (edge)
+      pairs_of_list(std::true_type{});
+    else
+      pairs_of_list(std::false_type{});
   };
-
+  // Phase A: the wavefront goes through the nine neighbour rows together and
+  // walks the lane's runs of each in lockstep, kBatch run entries per lane and
+  // pass (run A [t, t_end), then run B [tb, tb_end) where the row wraps; a lane
+  // moves to B on its own), with qa / qb the lane's code shifted by the image of
+  // run A / B.  Entries past the lane's run are read (other cells' entries, or the
+  // pad) but never listed; neither is the lane's own particle.  Phase B runs when
+  // a lane's list could overflow in the next pass, and after the last row: rows
+  // and passes are one loop so that it is compiled in once.
   const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
-  for (int oz = -1; oz <= 1; ++oz) {
-    int qz = cz + oz;
-    float sz = 0.f;
-    if (qz < 0) { qz += nz; sz = -G.L[2]; }
-    else if (qz >= nz) { qz -= nz; sz = G.L[2]; }
-    const uint32_t cz_code = qshift(pi.z, sz) << 22;
-    for (int oy = -1; oy <= 1; ++oy) {
-      int qy = cy + oy;
-      float sy = 0.f;
+  int t = 0, t_end = 0, tb = 0, tb_end = 0;
+  uint32_t qa = 0, qb = 0;
+  int row = -1;   // of the nine, z outermost
+  for (;;) {
+    if (!wave_any(t < t_end)) {
+      if (++row == 9) {
+        flush();
+        break;
+      }
+      const int oz = row / 3 - 1, oy = row % 3 - 1;
+      int qz = cz + oz, qy = cy + oy;
+      float sz = 0.f, sy = 0.f;
+      if (qz < 0) { qz += nz; sz = -G.L[2]; }
+      else if (qz >= nz) { qz -= nz; sz = G.L[2]; }
       if (qy < 0) { qy += ny; sy = -G.L[1]; }
       else if (qy >= ny) { qy -= ny; sy = G.L[1]; }
-      const uint32_t cyz_code = (qshift(pi.y, sy) << 11) | cz_code;
+      const uint32_t cyz_code = (qshift(pi.y, sy) << 11) | (qshift(pi.z, sz) << 22);
       // the row's x-neighbours [cx-1, cx+1] as run A, plus run B where the
       // row wraps (cell nx-1 seen across the left edge, then cells 0 and 1;
       // or cells nx-2 and nx-1, then cell 0 seen across the right edge)
@@ -1266,19 +1268,51 @@ __device__ __forceinline__ void force_tile(
       const int a0 = left ? base + nx - 1 : (right ? base + nx - 2 : base + cx - 1);
       int v[4];
       starts.load(a0, v);
-      const int ta = v[0], ta_end = left ? v[1] : (right ? v[2] : v[3]);
-      int tb = 0, tb_end = 0;
+      t = v[0];
+      t_end = left ? v[1] : (right ? v[2] : v[3]);
+      tb = 0;
+      tb_end = 0;
       if (wave_any(left || right)) {
         int w[4];
         starts.load(base, w);
         tb = (left || right) ? w[0] : 0;
         tb_end = left ? w[2] : (right ? w[1] : 0);
       }
-      const float sxa = left ? -G.L[0] : 0.f, sxb = right ? G.L[0] : 0.f;
-      walk(ta, ta_end, tb, tb_end, qshift(pi.x, sxa) | cyz_code, qshift(pi.x, sxb) | cyz_code);
+      qa = qshift(pi.x, left ? -G.L[0] : 0.f) | cyz_code;
+      qb = qshift(pi.x, right ? G.L[0] : 0.f) | cyz_code;
+      const bool sw = t >= t_end;
+      t = sw ? tb : t;
+      t_end = sw ? tb_end : t_end;
+      tb = sw ? tb_end : tb;
+      qa = sw ? qb : qa;
+      continue;
     }
+    if (wave_any(tail > full)) flush();
+    const int rem = t_end - t;
+    int jb[kBatch], w[kBatch];
+    runs.load(t, jb);
+    codes.load(t, w);
+    // the conditions are joined as masks, by the scalar unit; the particle
+    // itself is met in the home row alone
+    unsigned long long self[kBatch] = {};
+    if (row == 4) {
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) self[u] = __ballot(jb[u] == i);
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const unsigned long long keep =
+          __ballot(qdist2((uint32_t)w[u], qa) <= qth) & __ballot(u < rem) & ~self[u];
+      *(int *)(lds + tail) = jb[u];
+      tail += __builtin_amdgcn_inverse_ballot_w64(keep) ? (uint32_t)(BS * 4) : 0u;
+    }
+    t = rem > 0 ? t + kBatch : t;
+    const bool sw = t >= t_end && tb < tb_end;
+    t = sw ? tb : t;
+    t_end = sw ? tb_end : t_end;
+    tb = sw ? tb_end : tb;
+    qa = sw ? qb : qa;
   }
-  flush();
   const Finished fin = finish_particle<INIT>(P, acc, i, vti, vel4, frc4);
   if (!(isfinite(fin.frc.x) && isfinite(fin.frc.y) && isfinite(fin.frc.z)))
     atomicAdd(&st->nonfinite, 1ull);
