@@ -105,6 +105,7 @@ struct dpd_ctx {
   int ppt = 2, fblock = 256;            // launch shapes (autotuned)
   bool wide = false;      // pair forces with 16 lanes per particle (use_wide)
   int box_list = 0;       // blocks per box of the one-launch cell list, 0: not used (box_parts)
+  bool box_codes = false; // its blocks write the runs' coarse codes as well
   Tile *itiles = nullptr, *ftiles = nullptr;
   int n_itiles = 0, n_ftiles = 0;
   int itiles_cap = 0, ftiles_cap = 0;
@@ -686,7 +687,9 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
     HIP_TRY(c, timed(c, s, K_SORT, [&] {
               return dpd::launch_cells_box(s, c->boxes, c->R, c->box_list, c->NF, c->cell_of, c->rank_of,
                                            c->count, c->wcstart, c->start_all, c->idx,
-                                           c->idx_all, c->wcell, bump);
+                                           c->idx_all, c->wcell, c->pos[c->cur],
+                                           codes && !c->wide && c->box_codes ? c->cq : nullptr,
+                                           bump);
             }));
     if (c->box_list > 1 && !force_next)
       HIP_TRY(c, dpd::launch_fill_zero(s, c->count, 4 * (size_t)c->NCELL));
@@ -709,7 +712,7 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
             }));
   }
   // the pair kernel with 16 lanes per particle reads no codes
-  if (codes && !c->wide)
+  if (codes && !c->wide && (key4 || !c->box_codes))
     HIP_TRY(c, timed(c, s, K_CODES, [&] {
               return dpd::launch_quant_runs(s, c->NF + c->NW, c->idx_all, c->pos[c->cur], c->cq);
             }));
@@ -1318,6 +1321,10 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   rc = build_bricks(c);
   c->wide = use_wide(c);
   c->box_list = box_parts(c);
+  // a box's 16 blocks write the codes too, a launch less (16 cylinder cells: 63.1 to
+  // 61.6 us a step); fewer blocks of large boxes take longer than the launch (64
+  // uneven boxes, 4 each: 110.9 to 112.1)
+  c->box_codes = c->box_list == 16;
   if (!rc) rc = set_shapes(c, default_ppt(c), 256);
   if (rc) return bail(rc);
   c->cur = 0;

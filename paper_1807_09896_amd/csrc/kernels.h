@@ -57,13 +57,15 @@ hipError_t launch_sort_wall_cells(hipStream_t s, int64_t ncell, const int32_t *s
 // The cell list of every box (scan, scatter and sort above, with the wall part
 // of the merged runs and the advance of dk, without cstart and fluid_off) in one
 // launch, `parts` blocks per box; each box has at most kBoxCells cells and
-// kBoxFluid fluid particles.  With parts > 1 count is left as it is: the pair
+// kBoxFluid fluid particles; with cq, the runs' coarse codes from pos4 too.  With
+// parts > 1 count is left as it is: the pair
 // force that follows clears it (its `clear`), or the caller.
 constexpr int kBoxCells = 16384, kBoxFluid = 24576;   // 128 KB of LDS
 hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int parts, int64_t NF,
                             const int32_t *cell_of, const int32_t *rank_of, int32_t *count,
                             const int32_t *wcstart, int32_t *start_all, int32_t *idx,
-                            int32_t *idx_all, const int32_t *wcell, unsigned long long *dk);
+                            int32_t *idx_all, const int32_t *wcell, const float4 *pos4,
+                            uint32_t *cq, unsigned long long *dk);
 // Coarse position codes of the merged runs, cq[t] from pos4[idx_all[t]] for
 // t < n (one word per entry), which the pair kernel's candidate pre-test
 // reads; n = NF + NW, after the scatter and sort.

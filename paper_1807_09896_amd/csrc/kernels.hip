@@ -485,6 +485,7 @@ __global__ __launch_bounds__(kBoxThreads) void k_cells_box(
     const int32_t *__restrict__ rank_of, int32_t *__restrict__ count,
     const int32_t *__restrict__ wcstart, int32_t *__restrict__ start_all,
     int32_t *__restrict__ idx, int32_t *__restrict__ idx_all, const int32_t *__restrict__ wcell,
+    const float4 *__restrict__ pos4, uint32_t *__restrict__ cq,
     unsigned long long *__restrict__ dk) {
   __shared__ uint16_t start[kBoxCells + 1];
   __shared__ uint16_t slot[kBoxFluid], cell[kBoxFluid];   // of each slot: particle and its cell
@@ -557,7 +558,12 @@ __global__ __launch_bounds__(kBoxThreads) void k_cells_box(
 #pragma unroll 4
   for (int w = wcstart[co + lo] + t; w < w1; w += kBoxThreads) {
     // entry start_all[c] + (w - wcstart[c]) of the merged runs
-    idx_all[first + start[wcell[w] - co - lo] + w] = (int)NF + w;
+    const int e = first + start[wcell[w] - co - lo] + w;
+    idx_all[e] = (int)NF + w;
+    if (cq) {
+      const float4 x = pos4[NF + w];
+      cq[e] = qcode3(x.x, x.y, x.z);
+    }
   }
 #pragma unroll 4
   for (int c = t; c < n; c += kBoxThreads)
@@ -591,9 +597,13 @@ __global__ __launch_bounds__(kBoxThreads) void k_cells_box(
   __syncthreads();
 #pragma unroll 4
   for (int s = t; s < own; s += kBoxThreads) {
-    const int i = fo + slot[s];
+    const int i = fo + slot[s], e = first + s + wcstart[co + lo + cell[s] + 1];
     idx[first + s] = i;
-    idx_all[first + s + wcstart[co + lo + cell[s] + 1]] = i;
+    idx_all[e] = i;
+    if (cq) {
+      const float4 x = pos4[i];
+      cq[e] = qcode3(x.x, x.y, x.z);
+    }
   }
 }
 
@@ -2154,11 +2164,12 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
 hipError_t launch_cells_box(hipStream_t s, const Box *boxes, int nbox, int parts, int64_t NF,
                             const int32_t *cell_of, const int32_t *rank_of, int32_t *count,
                             const int32_t *wcstart, int32_t *start_all, int32_t *idx,
-                            int32_t *idx_all, const int32_t *wcell, unsigned long long *dk) {
+                            int32_t *idx_all, const int32_t *wcell, const float4 *pos4,
+                            uint32_t *cq, unsigned long long *dk) {
   if (nbox <= 0) return hipSuccess;
   const dim3 grid((unsigned)nbox, (unsigned)parts);
   k_cells_box<<<grid, kBoxThreads, 0, s>>>(boxes, NF, cell_of, rank_of, count, wcstart, start_all,
-                                           idx, idx_all, wcell, dk);
+                                           idx, idx_all, wcell, pos4, cq, dk);
   return hipGetLastError();
 }
 

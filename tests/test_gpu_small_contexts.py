@@ -122,6 +122,36 @@ def test_blocks_per_box(dpd, count):
     batch.close()
 
 
+@pytest.mark.parametrize("count,walls", [(3, False), (4, True), (20, False)])
+def test_codes_of_the_box_list(dpd, count, walls):
+    """Contexts above the 16-lane pair kernel's size whose coarse codes the cell
+    list's own 16 blocks per box write, and (20 boxes, 12 blocks) a launch after it."""
+    import torch
+    boxes = []
+    for r in range(count):
+        if walls:
+            boxes.append(workloads.slab_system(L=(18.0, 26.0, 18.0 + 0.5 * r), seed_fluid=30 + r,
+                                               seed_wall=50 + r, grid_dtype=np.float32,
+                                               params=P(seed=r)))
+        else:
+            boxes.append(_edge_box((18, 18, 19), 24576 - r) if count < 16 else
+                         _edge_box((12, 11, 10), 3500 + r))
+    fluid = sum(int((s.type == 0).sum()) for s in boxes)
+    print("codes", count, walls, fluid, flush=True)
+    assert fluid > 65536
+    batch = dpd.Simulation(boxes)
+    batch.step(5)
+    for r in (0, count - 1):
+        alone = dpd.Simulation(boxes[r])
+        alone.step(5)
+        a, b = alone.state(0), batch.state(r)
+        for k in a:
+            assert torch.equal(a[k], b[k]), (count, r, k)
+        assert torch.equal(alone.forces(0), batch.forces(r)), (count, r)
+        alone.close()
+    batch.close()
+
+
 def test_small_context_graph_replays(dpd):
     """The small context's step captured and replayed, eager work between."""
     import torch
