@@ -1054,18 +1054,26 @@ __global__ __launch_bounds__(kBlock) void k_count_flagged(const KGeom G, int64_t
 // (slot-major, so the wavefront's appends fall in different banks).  Phase
 // B: each lane takes the exact FP32 decision on its listed candidates; the
 // random-number and force arithmetic runs only for pairs inside the
-// cutoff.  The wavefront runs phase B when any
-// lane's list could overflow in the next pass, and once at the end.  Lanes
+// cutoff.  The wavefront runs phase B on the first kDrain listed of every lane
+// when any lane's list could overflow in the next pass, and on all at the end.  Lanes
 // never branch apart inside a pass, so the wavefront pays for the longest
 // run of each row, not for every lane's row switches.  Sums run in
 // candidate order, so runs are deterministic.
 // ---------------------------------------------------------------------------
 // 26 entries per lane: with 256-thread blocks at six wavefronts per SIMD,
 // six blocks' lists (26 KB each) fill a CU's 160 KB of LDS, and most lanes'
-// pairs (about 16 plus the pre-test's extras) fit, so most wavefronts run
-// the pair pass once, after the walk, instead of twice.
+// pairs (about 16 plus the pre-test's extras) fit.
 constexpr int kListCap = 26;
 constexpr int kBatch = 4;   // = the width of one run-array load
+// Pairs a lane evaluates when a list could overflow: fewer than nearly every lane
+// has listed by then, so that few lanes idle; the rest stays listed.  Emptying the
+// lists costs the longest list's pairs twice: by a count over random boxes 42
+// evaluations a wavefront for the 20 candidates a lane lists at 4 particles per
+// unit volume (27 for 15 at 3), against 30 (23) with 10, 31 (23) with 12 and 34
+// (24) with 16.  Measured: 16 cylinder cells 43.1 to 40.3 us, SPH in 1.17 million
+// particles 182 to 175; the 168^3 porous box (6.3 million), which the line accesses
+// of the gathers bound, 845 before and after; 8 and 13 as 10.
+constexpr int kDrain = 10;
 
 struct Acc {
   float x, y, z;
@@ -1199,9 +1207,9 @@ __device__ __forceinline__ void force_tile(
   // while the current one is evaluated.  Where no lane's cell is at an edge of
   // the box the separation needs no image (sep's value in that case): 21 of
   // about 150 instructions a pair.
-  auto pairs_of_list = [&](auto at_edge) {
+  auto pairs_of_list = [&](auto at_edge, uint32_t upto) {
     if (tail == lane0) return;
-    const uint32_t last = tail - BS * 4u;
+    const uint32_t last = min(tail, upto) - BS * 4u;
     uint32_t q = lane0;
     auto evaluate = [&](int j, const float4 &pj, const float4 &vtj) {
       const float dx = at_edge.value ? sep(pi.x, pj.x, G.L[0]) : sub_nc(pi.x, pj.x);
@@ -1236,13 +1244,14 @@ __device__ __forceinline__ void force_tile(
       q += BS * 4u;
       if (q > last) break;
     }
-    tail = lane0;
   };
-  auto flush = [&]() {
+  // the first `count` entries of every lane's list
+  auto drain = [&](int count) {
+    const uint32_t upto = lane0 + (uint32_t)(count * BS * 4);
     if (edge)
-      pairs_of_list(std::true_type{});
+      pairs_of_list(std::true_type{}, upto);
     else
-      pairs_of_list(std::false_type{});
+      pairs_of_list(std::false_type{}, upto);
   };
   // Phase A: the wavefront goes through the nine neighbour rows together and
   // walks the lane's runs of each in lockstep, kBatch run entries per lane and
@@ -1250,8 +1259,8 @@ __device__ __forceinline__ void force_tile(
   // moves to B on its own), with qa / qb the lane's code shifted by the image of
   // run A / B.  Entries past the lane's run are read (other cells' entries, or the
   // pad) but never listed; neither is the lane's own particle.  Phase B runs when
-  // a lane's list could overflow in the next pass, and after the last row: rows
-  // and passes are one loop so that it is compiled in once.
+  // a lane's list could overflow in the next pass, and after the last row; rows
+  // and passes are one loop.
   const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
   int t = 0, t_end = 0, tb = 0, tb_end = 0;
   uint32_t qa = 0, qb = 0;
@@ -1259,7 +1268,7 @@ __device__ __forceinline__ void force_tile(
   for (;;) {
     if (!wave_any(t < t_end)) {
       if (++row == 9) {
-        flush();
+        drain(kListCap);
         break;
       }
       const int oz = row / 3 - 1, oy = row % 3 - 1;
@@ -1297,7 +1306,14 @@ __device__ __forceinline__ void force_tile(
       qa = sw ? qb : qa;
       continue;
     }
-    if (wave_any(tail > full)) flush();
+    if (wave_any(tail > full)) {
+      // kDrain pairs of every lane, the others' entries moved to the list's front
+      drain(kDrain);
+      int *const column = (int *)(lds + lane0);
+#pragma unroll
+      for (int e = 0; e + kDrain < kListCap; ++e) column[e * BS] = column[(e + kDrain) * BS];
+      tail = max(tail, lane0 + (uint32_t)(kDrain * BS * 4)) - (uint32_t)(kDrain * BS * 4);
+    }
     const int rem = t_end - t;
     int jb[kBatch], w[kBatch];
     runs.load(t, jb);
