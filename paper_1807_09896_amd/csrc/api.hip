@@ -139,6 +139,7 @@ struct dpd_ctx {
   void *quad = nullptr;         // the grids in the face layout (4 values a node)
   uint32_t *bits = nullptr;     // near-interface grid cubes, one bit each
   Status *status = nullptr;
+  Status *note = nullptr;   // pinned host memory the kernels of a getter leave the status in
   unsigned long long *dk = nullptr;  // force evaluation index on the device
   unsigned long long *pair_counter = nullptr;
 
@@ -238,6 +239,8 @@ void release_all(dpd_ctx *c) {
       (void)hipFree(p);
   }
   c->owned.clear();
+  if (c->note) (void)hipHostFree(c->note);
+  c->note = nullptr;
   for (auto &t : c->pending) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
@@ -290,15 +293,14 @@ hipError_t timed(dpd_ctx *c, hipStream_t s, int kernel, F &&launch) {
 }
 
 int read_status(dpd_ctx *c, Status &st) {
-  HIP_TRY(c, hipMemcpyAsync(&st, c->status, sizeof(Status), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, dpd::launch_note_status(c->stream, c->status, c->note));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  st = *c->note;
   return DPD_OK;
 }
 
-int latched_error(dpd_ctx *c) {
-  Status st;
-  int rc = read_status(c, st);
-  if (rc) return rc;
+// The error that a status holds.
+int status_error(dpd_ctx *c, const Status &st) {
   if (st.nonfinite)
     return fail(c, DPD_E_UNSTABLE, "non-finite positions or forces (" +
                                        std::to_string(st.nonfinite) + " events)");
@@ -310,6 +312,22 @@ int latched_error(dpd_ctx *c) {
                                      std::to_string(st.stalled) +
                                      " waits); the state after it is not valid");
   return DPD_OK;
+}
+
+int latched_error(dpd_ctx *c) {
+  Status st;
+  int rc = read_status(c, st);
+  return rc ? rc : status_error(c, st);
+}
+
+// Rows of box r by gid and, once the stream has come to it, the status.
+hipError_t export_box(dpd_ctx *c, int32_t r, float *pos, float *vel, float *frc, int32_t *events,
+                      int32_t *cell_of) {
+  const Replica &p = c->rep[r];
+  const int a = c->cur;
+  return dpd::launch_export(c->stream, p.G, p.nf, p.nw, c->pos[a] + p.fo, c->vel[a] + p.fo,
+                            c->frc[a] + p.fo, c->pos[a] + c->NF + p.wo, c->vt + c->NF + p.wo, pos,
+                            vel, frc, events, cell_of, c->status, c->note);
 }
 
 // Release a half-built context, keeping its message as the create error.
@@ -1160,6 +1178,8 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   c->bits = (uint32_t *)dalloc(c, 4 * (size_t)NWORDS);
   c->boxes = (Box *)dalloc(c, sizeof(Box) * (size_t)nbox);
   c->status = (Status *)dalloc(c, sizeof(Status));
+  if (hipHostMalloc((void **)&c->note, sizeof(Status), hipHostMallocDefault) != hipSuccess)
+    c->note = nullptr;
   c->dk = (unsigned long long *)dalloc(c, 8);
   c->pair_counter = (unsigned long long *)dalloc(c, 8);
   for (int b = 0; b < 2; ++b)
@@ -1168,7 +1188,7 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   if (!c->vt || !c->cell_of || !c->rank_of || !c->idx || !c->count || !c->cstart || !c->bsum ||
       !c->wcstart || !c->wcell || !c->idx_all || !c->cq || !c->start_all || !c->fluid_off ||
       !c->grid || !c->quad ||
-      !c->bits || !c->boxes || !c->status || !c->dk || !c->pair_counter)
+      !c->bits || !c->boxes || !c->status || !c->note || !c->dk || !c->pair_counter)
     return bail(fail(c, DPD_E_NOMEM, "device allocation failed"));
 
   int rc = DPD_OK;
@@ -1749,13 +1769,7 @@ int trace_impl(dpd_ctx *c, float *pos_log, float *vel_log, float *frc_log, int32
     float *vl = vel_log ? vel_log + (size_t)3 * p.n * st : nullptr;
     float *fl = frc_log ? frc_log + (size_t)3 * p.n * st : nullptr;
     int32_t *el = (ev_log && st > 0) ? ev_log + (size_t)p.n * (st - 1) : nullptr;
-    hipError_t e = dpd::launch_export(s, p.G, p.nf, c->pos[c->cur] + p.fo,
-                                      c->vel[c->cur] + p.fo, c->frc[c->cur] + p.fo, 0, pl, vl,
-                                      fl, el, nullptr);
-    if (e == hipSuccess)
-      e = dpd::launch_export(s, p.G, p.nw, c->pos[c->cur] + c->NF + p.wo,
-                             c->vt + c->NF + p.wo, nullptr, 1, pl, vl, fl, el, nullptr);
-    return e;
+    return export_box(c, 0, pl, vl, fl, el, nullptr);
   };
   for (int seg = 0; seg < W.nck && !rc; ++seg) {
     const int t0 = seg * W.ckpt, t1 = std::min(W.steps, t0 + W.ckpt);
@@ -1852,12 +1866,9 @@ int dpd_replica_forces(dpd_ctx *c, int32_t r, float *f_out) {
   if (!c) return DPD_E_INVAL;
   if (check_replica(c, r)) return DPD_E_INVAL;
   if (!f_out) return fail(c, DPD_E_INVAL, "f_out is NULL");
-  const Replica &p = c->rep[r];
-  HIP_TRY(c, dpd::launch_fill_zero(c->stream, f_out, 12 * (size_t)p.n));
-  HIP_TRY(c, dpd::launch_export(c->stream, p.G, p.nf, c->pos[c->cur] + p.fo,
-                                c->vel[c->cur] + p.fo, c->frc[c->cur] + p.fo, 0, nullptr,
-                                nullptr, f_out, nullptr, nullptr));
-  return latched_error(c);
+  HIP_TRY(c, export_box(c, r, nullptr, nullptr, f_out, nullptr, nullptr));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  return status_error(c, *c->note);
 }
 
 int dpd_forces(dpd_ctx *c, float *f_out) { return dpd_replica_forces(c, 0, f_out); }
@@ -1866,14 +1877,9 @@ int dpd_replica_state(dpd_ctx *c, int32_t r, float *pos, float *vel, int32_t *ev
                       int32_t *cell_of) {
   if (!c) return DPD_E_INVAL;
   if (check_replica(c, r)) return DPD_E_INVAL;
-  const Replica &p = c->rep[r];
-  HIP_TRY(c, dpd::launch_export(c->stream, p.G, p.nf, c->pos[c->cur] + p.fo,
-                                c->vel[c->cur] + p.fo, c->frc[c->cur] + p.fo, 0, pos, vel,
-                                nullptr, events, cell_of));
-  HIP_TRY(c, dpd::launch_export(c->stream, p.G, p.nw, c->pos[c->cur] + c->NF + p.wo,
-                                c->vt + c->NF + p.wo, nullptr, 1, pos, vel, nullptr, events,
-                                cell_of));
-  return latched_error(c);
+  HIP_TRY(c, export_box(c, r, pos, vel, nullptr, events, cell_of));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  return status_error(c, *c->note);
 }
 
 int dpd_get_state(dpd_ctx *c, float *pos, float *vel, int32_t *events, int32_t *cell_of) {
@@ -2270,7 +2276,6 @@ int dpd_window_trace(dpd_ctx *c, float *pos_log, float *vel_log, float *frc_log,
 
 int dpd_sync(dpd_ctx *c) {
   if (!c) return DPD_E_INVAL;
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
   return latched_error(c);
 }
 

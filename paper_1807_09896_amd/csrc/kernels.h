@@ -216,10 +216,16 @@ hipError_t launch_pair_random(hipStream_t s, uint64_t seed, uint64_t k, uint32_t
                               const uint32_t *gi, const uint32_t *gj, int64_t n, uint32_t *words,
                               float *xi);
 
-// Export rows by gid.
-hipError_t launch_export(hipStream_t s, const KGeom &G, int64_t n, const float4 *pos4,
-                         const float4 *vel4, const float4 *frc4, int wall, float *pos,
-                         float *vel, float *frc, int32_t *events, int32_t *cell_of);
+// Export rows by gid: the fluid's nf slots and the nw walls (velocities wvel4;
+// no event, no force) of one box.  With note (host memory the device
+// can write) the status st goes there too.
+hipError_t launch_export(hipStream_t s, const KGeom &G, int64_t nf, int64_t nw,
+                         const float4 *pos4, const float4 *vel4, const float4 *frc4,
+                         const float4 *wall4, const float4 *wvel4, float *pos, float *vel,
+                         float *frc, int32_t *events, int32_t *cell_of, const Status *st,
+                         Status *note);
+// The status to note, as launch_export does it.
+hipError_t launch_note_status(hipStream_t s, const Status *st, Status *note);
 
 // Import fluid rows by gid (set_state): pos4[s] = (pos[gid], gid), ...
 hipError_t launch_import(hipStream_t s, int64_t nf, float4 *pos4, float4 *vel4, float4 *frc4,

