@@ -27,6 +27,7 @@ using dpd::Box;
 using dpd::KGeom;
 using dpd::KParams;
 using dpd::Status;
+using dpd::StatusBlock;
 using dpd::Tile;
 
 namespace {
@@ -138,7 +139,7 @@ struct dpd_ctx {
   void *grid = nullptr;
   void *quad = nullptr;         // the grids in the face layout (4 values a node)
   uint32_t *bits = nullptr;     // near-interface grid cubes, one bit each
-  Status *status = nullptr;
+  Status *status = nullptr; // head of a StatusBlock
   Status *note = nullptr;   // pinned host memory the kernels of a getter leave the status in
   unsigned long long *dk = nullptr;  // force evaluation index on the device
   unsigned long long *pair_counter = nullptr;
@@ -296,6 +297,13 @@ int read_status(dpd_ctx *c, Status &st) {
   HIP_TRY(c, dpd::launch_note_status(c->stream, c->status, c->note));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   st = *c->note;
+  return DPD_OK;
+}
+
+// A status read earlier back to the device (st lives until the stream has come to it).
+int write_status(dpd_ctx *c, const Status &st) {
+  HIP_TRY(c, dpd::launch_fill_zero(c->stream, c->status, sizeof(StatusBlock)));
+  HIP_TRY(c, hipMemcpyAsync(c->status, &st, sizeof(Status), hipMemcpyHostToDevice, c->stream));
   return DPD_OK;
 }
 
@@ -1177,7 +1185,7 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   c->quad = dalloc(c, 4 * (size_t)NGRID * (size_t)grids[0].dtype);
   c->bits = (uint32_t *)dalloc(c, 4 * (size_t)NWORDS);
   c->boxes = (Box *)dalloc(c, sizeof(Box) * (size_t)nbox);
-  c->status = (Status *)dalloc(c, sizeof(Status));
+  c->status = (Status *)dalloc(c, sizeof(StatusBlock));
   if (hipHostMalloc((void **)&c->note, sizeof(Status), hipHostMallocDefault) != hipSuccess)
     c->note = nullptr;
   c->dk = (unsigned long long *)dalloc(c, 8);
@@ -1195,7 +1203,7 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   auto chk = [&](hipError_t e, const char *w) {
     if (e != hipSuccess && rc == DPD_OK) rc = hip_fail(c, e, w);
   };
-  chk(dpd::launch_fill_zero(c->stream, c->status, sizeof(Status)), "zero status");
+  chk(dpd::launch_fill_zero(c->stream, c->status, sizeof(StatusBlock)), "zero status");
   chk(dpd::launch_fill_zero(c->stream, c->count, 4 * ncell), "zero counts");
   chk(dpd::launch_fill_zero(c->stream, c->pair_counter, 8), "zero counter");
   chk(dpd::launch_fill_zero(c->stream, c->dk, 8), "zero k");
@@ -1527,7 +1535,7 @@ int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
   if (!rc && !W.acc) {
     W.acc = (double *)dalloc(c, 8 * 8);
     W.dk0 = (unsigned long long *)dalloc(c, 8);
-    W.status_save = (Status *)dalloc(c, sizeof(Status));
+    W.status_save = (Status *)dalloc(c, sizeof(StatusBlock));
     if (!W.acc || !W.dk0 || !W.status_save)
       return fail(c, DPD_E_NOMEM, "window buffer allocation failed");
   }
@@ -1669,7 +1677,8 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
     rc = save_state(c, W.save);
     if (rc) return rc;
     HIP_TRY(c,
-            hipMemcpyAsync(W.status_save, c->status, sizeof(Status), hipMemcpyDeviceToDevice, s));
+            hipMemcpyAsync(W.status_save, c->status, sizeof(StatusBlock), hipMemcpyDeviceToDevice,
+                           s));
   }
   const bool timing = c->timing;
   c->timing = false;
@@ -1731,7 +1740,8 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
     int r2 = load_state(c, W.save);
     if (!rc) rc = r2;
     HIP_TRY(c,
-            hipMemcpyAsync(c->status, W.status_save, sizeof(Status), hipMemcpyDeviceToDevice, s));
+            hipMemcpyAsync(c->status, W.status_save, sizeof(StatusBlock), hipMemcpyDeviceToDevice,
+                           s));
     HIP_TRY(c, dpd::launch_set_u64(s, c->dk, c->k));
   }
   if (rc) return rc;
@@ -1760,7 +1770,8 @@ int trace_impl(dpd_ctx *c, float *pos_log, float *vel_log, float *frc_log, int32
   const int64_t steps_save = c->steps;
   int rc = save_state(c, W.save);
   if (rc) return rc;
-  HIP_TRY(c, hipMemcpyAsync(W.status_save, c->status, sizeof(Status), hipMemcpyDeviceToDevice, s));
+  HIP_TRY(c, hipMemcpyAsync(W.status_save, c->status, sizeof(StatusBlock), hipMemcpyDeviceToDevice,
+                           s));
   const bool timing = c->timing;
   c->timing = false;
   // state `st` of the trajectory into the logs (events of step st - 1)
@@ -1790,7 +1801,8 @@ int trace_impl(dpd_ctx *c, float *pos_log, float *vel_log, float *frc_log, int32
   c->steps = steps_save;
   int r2 = load_state(c, W.save);
   if (!rc) rc = r2;
-  HIP_TRY(c, hipMemcpyAsync(c->status, W.status_save, sizeof(Status), hipMemcpyDeviceToDevice, s));
+  HIP_TRY(c, hipMemcpyAsync(c->status, W.status_save, sizeof(StatusBlock), hipMemcpyDeviceToDevice,
+                           s));
   HIP_TRY(c, dpd::launch_set_u64(s, c->dk, c->k));
   HIP_TRY(c, hipStreamSynchronize(s));
   if (rc) return rc;
@@ -2048,16 +2060,16 @@ int dpd_autotune(dpd_ctx *c, int32_t steps, int32_t *shape_out, double *ms_out) 
     const int64_t steps0 = c->steps;
     const size_t np = 16 * (size_t)(c->NF + c->NW + 1), nv = 16 * (size_t)c->NF;
     const size_t nwv = c->moving ? 16 * (size_t)c->NW : 0;   // moving walls' velocities
-    char *save = (char *)dalloc(c, np + 2 * nv + sizeof(Status) + nwv);
+    char *save = (char *)dalloc(c, np + 2 * nv + sizeof(StatusBlock) + nwv);
     if (!save) return fail(c, DPD_E_NOMEM, "autotune snapshot allocation failed");
-    char *save_wv = save + np + 2 * nv + sizeof(Status);
+    char *save_wv = save + np + 2 * nv + sizeof(StatusBlock);
     if (nwv)
       HIP_TRY(c, hipMemcpyAsync(save_wv, c->vt + c->NF, nwv, hipMemcpyDeviceToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(save, c->pos[cur0], np, hipMemcpyDeviceToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(save + np, c->vel[cur0], nv, hipMemcpyDeviceToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(save + np + nv, c->frc[cur0], nv, hipMemcpyDeviceToDevice,
                               c->stream));
-    HIP_TRY(c, hipMemcpyAsync(save + np + 2 * nv, c->status, sizeof(Status),
+    HIP_TRY(c, hipMemcpyAsync(save + np + 2 * nv, c->status, sizeof(StatusBlock),
                               hipMemcpyDeviceToDevice, c->stream));
     const bool timing = c->timing;
     c->timing = false;
@@ -2076,7 +2088,7 @@ int dpd_autotune(dpd_ctx *c, int32_t steps, int32_t *shape_out, double *ms_out) 
       HIP_TRY(c, hipMemcpyAsync(c->vel[cur0], save + np, nv, hipMemcpyDeviceToDevice, c->stream));
       HIP_TRY(c, hipMemcpyAsync(c->frc[cur0], save + np + nv, nv, hipMemcpyDeviceToDevice,
                                 c->stream));
-      HIP_TRY(c, hipMemcpyAsync(c->status, save + np + 2 * nv, sizeof(Status),
+      HIP_TRY(c, hipMemcpyAsync(c->status, save + np + 2 * nv, sizeof(StatusBlock),
                                 hipMemcpyDeviceToDevice, c->stream));
       HIP_TRY(c, hipMemcpyAsync(c->dk, &c->k, 8, hipMemcpyHostToDevice, c->stream));
       if (nwv) {
@@ -2181,8 +2193,8 @@ int dpd_set_phi(dpd_ctx *c, int32_t r, const void *data, int32_t on_device) {
   rc = read_status(c, after);
   if (rc) return rc;
   if (after.bad_grid != before.bad_grid || after.bad_phi != before.bad_phi) {
-    HIP_TRY(c, hipMemcpyAsync(c->status, &before, sizeof(Status), hipMemcpyHostToDevice,
-                              c->stream));
+    rc = write_status(c, before);
+    if (rc) return rc;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     dfree(c, stage);
     return fail(c, DPD_E_INVAL, after.bad_grid != before.bad_grid
@@ -2417,8 +2429,10 @@ int dpd_snapshot_io(dpd_ctx *c, int32_t dir, void *blob) {
   HIP_TRY(c, hipMemcpyAsync(c->frc[a], afrc, bf, hipMemcpyHostToDevice, c->stream));
   if (c->NW)
     HIP_TRY(c, hipMemcpyAsync(c->vt + c->NF, awv, bw, hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->status, &hd->status, sizeof(Status), hipMemcpyHostToDevice,
-                            c->stream));
+  {
+    int rc = write_status(c, hd->status);
+    if (rc) return rc;
+  }
   c->k = hd->k;
   c->steps = hd->steps;
   HIP_TRY(c, hipMemcpyAsync(c->dk, &c->k, 8, hipMemcpyHostToDevice, c->stream));

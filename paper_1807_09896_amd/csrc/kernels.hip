@@ -952,7 +952,7 @@ __device__ __forceinline__ void integrate_tile(
     }
   }
   // event counts: one atomic per wavefront, after the stores (a per-lane
-  // atomic on the one counter word put its latency into the step's chain)
+  // atomic put its latency into the step's chain), on the tile's line of 64
   int nbounce = 0, nfall = 0;
 #pragma unroll
   for (int u = 0; u < PPT; ++u) {
@@ -961,8 +961,9 @@ __device__ __forceinline__ void integrate_tile(
     nfall += __popcll(__ballot(ev == 2));
   }
   if (__lane_id() == 0) {
-    if (nbounce) atomicAdd(&st->bounce, (unsigned long long)nbounce);
-    if (nfall) atomicAdd(&st->fallback, (unsigned long long)nfall);
+    StatusBlock::Line &at = ((StatusBlock *)st)->lines[tid & 63];
+    if (nbounce) atomicAdd(&at.bounce, (unsigned long long)nbounce);
+    if (nfall) atomicAdd(&at.fallback, (unsigned long long)nfall);
   }
 }
 
@@ -1573,11 +1574,22 @@ __global__ void k_pair_random(uint32_t key0, uint32_t key1, uint32_t klo, uint32
 // ---------------------------------------------------------------------------
 // Getters and setters by gid
 // ---------------------------------------------------------------------------
-// Eight words of the context's status to host memory, by the first lanes of a block.
+// The context's status, with the counts of its lines, to host memory: by the first
+// wavefront of a block.
 __device__ __forceinline__ void note_status(const Status *st, Status *note) {
-  constexpr int words = (int)(sizeof(Status) / 8);
-  if (note && (int)threadIdx.x < words)
-    ((unsigned long long *)note)[threadIdx.x] = ((const unsigned long long *)st)[threadIdx.x];
+  if (!note || threadIdx.x >= 64) return;
+  const int t = (int)threadIdx.x;
+  const StatusBlock *b = (const StatusBlock *)st;
+  unsigned long long bounce = b->lines[t].bounce, fallback = b->lines[t].fallback;
+  for (int m = 32; m > 0; m >>= 1) {
+    bounce += __shfl_xor(bounce, m, 64);
+    fallback += __shfl_xor(fallback, m, 64);
+  }
+  static_assert(offsetof(Status, bounce) == 0 && offsetof(Status, fallback) == 8, "first words");
+  if (t < (int)(sizeof(Status) / 8)) {
+    const unsigned long long add = t == 0 ? bounce : (t == 1 ? fallback : 0ull);
+    ((unsigned long long *)note)[t] = ((const unsigned long long *)st)[t] + add;
+  }
 }
 
 __global__ void k_note_status(const Status *st, Status *note) { note_status(st, note); }
