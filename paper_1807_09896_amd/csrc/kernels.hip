@@ -174,107 +174,122 @@ __global__ void k_bin(const KGeom G, int64_t cell_off, int64_t n, const float4 *
   if (p < n) rank_of[p] = k;
 }
 
-__device__ __forceinline__ int block_exclusive_scan(int v, int *lds, int &total) {
-  // Hillis-Steele over the block in LDS (kScanThreads entries).
-  const int t = threadIdx.x;
-  lds[t] = v;
-  __syncthreads();
-  for (int off = 1; off < kScanThreads; off <<= 1) {
-    const int a = t >= off ? lds[t - off] : 0;
-    __syncthreads();
-    lds[t] += a;
-    __syncthreads();
+// Exclusive scan over the block's threads (kScanThreads, four wavefronts), and total.
+template <typename V>
+__device__ __forceinline__ V block_exclusive_scan(V v, V *lds, V &total) {
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  V incl = v;
+  for (int d = 1; d < 64; d <<= 1) {
+    const V o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
   }
-  total = lds[kScanThreads - 1];
-  const int incl = lds[t];
+  if (lane == 63) lds[wave] = incl;
   __syncthreads();
-  return incl - v;
-}
-
-// Sum of count over the chunk [base, min(base + kScanChunk, n)) into *out.
-__device__ __forceinline__ void scan_reduce_chunk(int64_t base, int64_t n,
-                                                  const int32_t *__restrict__ count,
-                                                  int32_t *__restrict__ out, int *lds) {
-  int acc = 0;
-  for (int k = 0; k < kScanItems; ++k) {
-    const int64_t i = base + (int64_t)k * kScanThreads + threadIdx.x;
-    if (i < n) acc += count[i];
+  V before = 0;
+  total = 0;
+  for (int w = 0; w < kScanThreads / 64; ++w) {
+    if (w < wave) before += lds[w];
+    total += lds[w];
   }
-  lds[threadIdx.x] = acc;
   __syncthreads();
-  for (int off = kScanThreads / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) lds[threadIdx.x] += lds[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = lds[0];
-  __syncthreads();
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(int64_t n,
-                                                              const int32_t *__restrict__ count,
-                                                              int32_t *__restrict__ bsum) {
-  __shared__ int lds[kScanThreads];
-  scan_reduce_chunk((int64_t)blockIdx.x * kScanChunk, n, count, bsum + blockIdx.x, lds);
+  return before + incl - v;
 }
 
 // Sum of v over the block (kScanThreads threads, four wavefronts).
-__device__ __forceinline__ int block_sum(int v, int *lds) {
+template <typename V>
+__device__ __forceinline__ V block_sum(V v, V *lds) {
   for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
   if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
   __syncthreads();
-  int t = 0;
+  V t = 0;
   for (int w = 0; w < kScanThreads / 64; ++w) t += lds[w];
   __syncthreads();
   return t;
 }
 
-// Each thread owns kScanItems consecutive cells; the block's cells are read
+// Sum of count over the chunk [base, min(base + ITEMS kScanThreads, n)) into *out.
+template <int ITEMS>
+__device__ __forceinline__ void scan_reduce_chunk(int64_t base, int64_t n,
+                                                  const int32_t *__restrict__ count,
+                                                  int32_t *__restrict__ out, int *lds) {
+  int acc = 0;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int64_t i = base + (int64_t)k * kScanThreads + threadIdx.x;
+    if (i < n) acc += count[i];
+  }
+  acc = block_sum(acc, lds);
+  if (threadIdx.x == 0) *out = acc;
+}
+
+template <int ITEMS>
+__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(int64_t n,
+                                                              const int32_t *__restrict__ count,
+                                                              int32_t *__restrict__ bsum) {
+  __shared__ int lds[kScanThreads / 64];
+  scan_reduce_chunk<ITEMS>((int64_t)blockIdx.x * ITEMS * kScanThreads, n, count,
+                           bsum + blockIdx.x, lds);
+}
+
+// Each thread owns ITEMS consecutive cells; the block's cells are read
 // through LDS so that global loads and stores stay coalesced.  The block's
-// offset is the sum of the block sums bsum[0 .. blockIdx) of k_scan_reduce.  With wall
+// offset is the sum of the block sums bsum[0 .. blockIdx) of k_scan_reduce, added up
+// (prior) while the counts are on their way.  With wall
 // offsets wstart (exclusive scan of the static wall counts) it also writes
 // the merged runs: start_all[c] = start[c] + wstart[c] begins cell c's run of
 // walls then fluid, fluid_off[c] = start_all[c] + (walls in c) its fluid part.
-// The chunk [base, min(base + kScanChunk, n)) of the exclusive scan, offset
+// The chunk [base, min(base + ITEMS kScanThreads, n)) of the exclusive scan, offset
 // by the sum of everything before it; the last chunk (last) also writes the
 // entry n after the end.  count is cleared for the next step.
-__device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, int offset, bool last,
+template <int ITEMS, typename V, typename Prior>
+__device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, bool last, Prior &&prior,
                                                 int32_t *__restrict__ count,
                                                 int32_t *__restrict__ start,
                                                 const int32_t *__restrict__ wstart,
                                                 int32_t *__restrict__ start_all,
-                                                int32_t *__restrict__ fluid_off, int *tile,
-                                                int *lds) {
-  for (int k = 0; k < kScanItems; ++k) {
-    const int local = k * kScanThreads + threadIdx.x;
-    const int64_t i = base + local;
-    int v = 0;
+                                                int32_t *__restrict__ fluid_off, V *tile, V *lds) {
+  V own[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int64_t i = base + k * kScanThreads + (int)threadIdx.x;
+    own[k] = 0;
     if (i < n) {
-      v = count[i];
+      own[k] = count[i];
+    }
+  }
+  const V offset = prior();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int local = k * kScanThreads + (int)threadIdx.x;
+    const int64_t i = base + local;
+    if (i < n) {
       count[i] = 0;
     }
-    tile[local + local / 32] = v;
+    tile[local + local / 32] = own[k];
   }
   __syncthreads();
-  int run = 0;
-  const int first = threadIdx.x * kScanItems;
-  for (int k = 0; k < kScanItems; ++k) {
+  V run = 0;
+  const int first = (int)threadIdx.x * ITEMS;
+  for (int k = 0; k < ITEMS; ++k) {
     const int local = first + k;
     run += tile[local + local / 32];
   }
-  int total;
-  int ex = block_exclusive_scan(run, lds, total) + offset;
-  for (int k = 0; k < kScanItems; ++k) {
+  V total;
+  V ex = block_exclusive_scan(run, lds, total) + offset;
+  for (int k = 0; k < ITEMS; ++k) {
     const int local = first + k;
-    const int v = tile[local + local / 32];
+    const V v = tile[local + local / 32];
     tile[local + local / 32] = ex;
     ex += v;
   }
   __syncthreads();
-  for (int k = 0; k < kScanItems; ++k) {
-    const int local = k * kScanThreads + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int local = k * kScanThreads + (int)threadIdx.x;
     const int64_t i = base + local;
     if (i < n) {
-      const int st = tile[local + local / 32];
+      const V at = tile[local + local / 32];
+      const int st = (int)at;
       start[i] = st;
       if (wstart) {
         const int w0 = wstart[i], w1 = wstart[i + 1];
@@ -284,23 +299,31 @@ __device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, int off
     }
   }
   if (last && threadIdx.x == kScanThreads - 1) {
-    start[n] = offset + total;
-    if (wstart) start_all[n] = offset + total + wstart[n];
+    const V end = offset + total;
+    start[n] = (int)end;
+    if (wstart) {
+      start_all[n] = (int)end + wstart[n];
+    }
   }
   __syncthreads();
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(
     int64_t n, int32_t *__restrict__ count, int32_t *__restrict__ start,
     const int32_t *__restrict__ bsum, const int32_t *__restrict__ wstart,
     int32_t *__restrict__ start_all, int32_t *__restrict__ fluid_off) {
-  __shared__ int tile[kScanChunk + kScanChunk / 32];
-  __shared__ int lds[kScanThreads];
-  int prior = 0;
-  for (int j = (int)threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) prior += bsum[j];
-  const int offset = block_sum(prior, lds);
-  scan_down_chunk((int64_t)blockIdx.x * kScanChunk, n, offset, blockIdx.x == gridDim.x - 1, count,
-                  start, wstart, start_all, fluid_off, tile, lds);
+  constexpr int chunk = ITEMS * kScanThreads;
+  __shared__ int tile[chunk + chunk / 32];
+  __shared__ int lds[kScanThreads / 64];
+  scan_down_chunk<ITEMS>(
+      (int64_t)blockIdx.x * chunk, n, blockIdx.x == gridDim.x - 1,
+      [&] {
+        int before = 0;
+        for (int j = (int)threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) before += bsum[j];
+        return block_sum(before, lds);
+      },
+      count, start, wstart, start_all, fluid_off, tile, lds);
 }
 
 // idx[start[cell_of[p]] + rank_of[p]] = p for the n entries.  Threads n ..
@@ -1855,7 +1878,7 @@ __device__ __attribute__((noinline)) void p_reduce(const PArgs *__restrict__ A0,
   const int box = uniform_int(box0), a = uniform_int(a0), b = uniform_int(b0);
   int *lds = lds_ptr(lds0);
   const int64_t co = A->boxes[box].co, ncell = A->boxes[box].ncell;
-  scan_reduce_chunk(co + (int64_t)a * kScanChunk, co + ncell, A->count, A->bsum + b + a, lds);
+  scan_reduce_chunk<kScanItems>(co + (int64_t)a * kScanChunk, co + ncell, A->count, A->bsum + b + a, lds);
 }
 
 // the box's fluid starts at slot fo; its chunks before this one add to it
@@ -1865,12 +1888,15 @@ __device__ __attribute__((noinline)) void p_down(const PArgs *__restrict__ A0, i
   const int box = uniform_int(box0), a = uniform_int(a0), b = uniform_int(b0);
   int *tile = lds_ptr(tile0), *lds = lds_ptr(lds0);
   const int64_t co = A->boxes[box].co, ncell = A->boxes[box].ncell, fo = A->boxes[box].fo;
-  int prior = 0;
-  for (int j = (int)threadIdx.x; j < a; j += kScanThreads) prior += A->bsum[b + j];
-  const int offset = (int)fo + block_sum(prior, lds);
   const bool last = (int64_t)(a + 1) * kScanChunk >= ncell;
-  scan_down_chunk(co + (int64_t)a * kScanChunk, co + ncell, offset, last, A->count, A->cstart,
-                  A->wcstart, A->start_all, A->fluid_off, tile, lds);
+  scan_down_chunk<kScanItems>(
+      co + (int64_t)a * kScanChunk, co + ncell, last,
+      [&] {
+        int before = 0;
+        for (int j = (int)threadIdx.x; j < a; j += kScanThreads) before += A->bsum[b + j];
+        return (int)fo + block_sum(before, lds);
+      },
+      A->count, A->cstart, A->wcstart, A->start_all, A->fluid_off, tile, lds);
 }
 
 __device__ __attribute__((noinline)) void p_scatter(const PArgs *__restrict__ A0, int a0, int b0) {
@@ -2021,15 +2047,24 @@ hipError_t launch_bin(hipStream_t s, const KGeom &G, int64_t cell_off, int64_t n
 }
 
 hipError_t launch_scan_reduce(hipStream_t s, int64_t ncell, const int32_t *count, int32_t *bsum) {
-  k_scan_reduce<<<scan_blocks(ncell), kScanThreads, 0, s>>>(ncell, count, bsum);
+  const unsigned grid = (unsigned)scan_blocks(ncell);
+  if (scan_items(ncell) == kScanItems)
+    k_scan_reduce<kScanItems><<<grid, kScanThreads, 0, s>>>(ncell, count, bsum);
+  else
+    k_scan_reduce<kScanFew><<<grid, kScanThreads, 0, s>>>(ncell, count, bsum);
   return hipGetLastError();
 }
 
 hipError_t launch_scan_down(hipStream_t s, int64_t ncell, int32_t *count, int32_t *start,
                             const int32_t *bsum, const int32_t *wstart, int32_t *start_all,
                             int32_t *fluid_off) {
-  k_scan_down<<<scan_blocks(ncell), kScanThreads, 0, s>>>(ncell, count, start, bsum, wstart,
-                                                          start_all, fluid_off);
+  const unsigned nb = (unsigned)scan_blocks(ncell);
+  if (scan_items(ncell) == kScanItems)
+    k_scan_down<kScanItems><<<nb, kScanThreads, 0, s>>>(ncell, count, start, bsum, wstart,
+                                                        start_all, fluid_off);
+  else
+    k_scan_down<kScanFew><<<nb, kScanThreads, 0, s>>>(ncell, count, start, bsum, wstart, start_all,
+                                                      fluid_off);
   return hipGetLastError();
 }
 
