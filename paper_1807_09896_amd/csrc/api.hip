@@ -133,7 +133,8 @@ struct dpd_ctx {
   bool reflect = false;   // some box has moving walls or specular reflection
   bool sph = false;       // some box uses the attractive-repulsive conservative force
   float4 *wtmp = nullptr, *wvtmp = nullptr;
-  int32_t *wcell_tmp = nullptr, *wrank = nullptr, *wcount = nullptr;
+  int32_t *wcell_tmp = nullptr, *wrank = nullptr, *wcount = nullptr, *widx = nullptr,
+          *wsum = nullptr;
   int32_t *start_all = nullptr; // start of each cell's merged run
   int32_t *fluid_off = nullptr; // start of each cell's fluid part in the merged run
   void *grid = nullptr;
@@ -455,14 +456,15 @@ constexpr int64_t kWideMax = 65536;
 bool use_wide(const dpd_ctx *c) { return c->NF <= kWideMax; }
 
 // Blocks per box of the one-launch cell list (k_cells_box); 0 where some box does
-// not fit its LDS, or where the brick kernel needs the separate launches' arrays.
+// not fit its LDS, where the brick kernel needs the separate launches' arrays, and
+// where walls move (list_both lists them with the fluid in four launches).
 // 256 CUs hold one such block each, so the boxes share 256, up to 16 a box (a box of
 // at most 1,024 particles is one round of one block's threads).  Whole step, us,
 // four launches / 1 / 4 / 16 blocks per box: 29.0 / 24.4 / 22.9 / 22.9 at 2,000
 // particles, 36.1 / 31.1 / 26.9 / 24.9 at 8,400, 38.3 / 39.9 / 31.1 / 27.9 at 16,000,
 // 41.3 / 48.1 / 35.9 / 32.2 at 22,000; 64 boxes: 127 / 126 / 115 / 131.
 int box_parts(const dpd_ctx *c) {
-  if (c->nbricks > 0) return 0;
+  if (c->nbricks > 0 || c->moving) return 0;
   int64_t most = 0;
   for (const Replica &p : c->rep) {
     if (p.ncell > dpd::kBoxCells || p.nf > dpd::kBoxFluid) return 0;
@@ -776,15 +778,11 @@ int force_pass(dpd_ctx *c, hipStream_t s, int init) {
 }
 
 // The launches of one step on stream s (swaps cur).
-// Walls re-sorted by cell after their positions changed; with `move` the
-// walls of every box whose solid moves first advance by dt v.  Reads the
-// walls at pos[cur] + NF (velocities at vt + NF), writes them back in cell
-// order (within a cell by storage index) to both position buffers and vt,
-// and rebuilds wcell and wcstart.
-int wall_pass(dpd_ctx *c, hipStream_t s, int move) {
-  if (c->NW == 0) return DPD_OK;
-  const int a = c->cur, b = 1 - a;
-  float4 *wp = c->pos[a] + c->NF, *wv = c->vt + c->NF;
+// The walls of every box binned at their positions into wcell_tmp, wrank and wcount, with
+// copies in wtmp and wvtmp; with move, those of every box whose solid moves first
+// advance by dt v.
+int bin_walls(dpd_ctx *c, hipStream_t s, int move) {
+  float4 *wp = c->pos[c->cur] + c->NF, *wv = c->vt + c->NF;
   for (int r = 0; r < c->R; ++r) {
     const Replica &p = c->rep[r];
     if (p.nw == 0) continue;
@@ -795,6 +793,51 @@ int wall_pass(dpd_ctx *c, hipStream_t s, int move) {
                                                c->wrank + p.wo, c->wcount);
             }));
   }
+  return DPD_OK;
+}
+
+// The binned walls in the order idx, into both position buffers and vt.
+int order_walls(dpd_ctx *c, hipStream_t s, const int32_t *idx) {
+  const int a = c->cur, b = 1 - a;
+  HIP_TRY(c, timed(c, s, K_OTHER, [&] {
+            return dpd::launch_permute(s, c->NW, idx, c->wtmp, c->pos[a] + c->NF, c->wvtmp,
+                                       c->vt + c->NF, c->wtmp, c->pos[b] + c->NF);
+          }));
+  return DPD_OK;
+}
+
+// A step's cell list where walls move: as scan_scatter_sort with the walls
+// advanced by dt v and put back in cell order on the way.
+int list_both(dpd_ctx *c, hipStream_t s) {
+  int rc = bin_walls(c, s, 1);
+  if (rc) return rc;
+  const dpd::BothLists L = {c->NCELL, c->NF, c->NW, c->count, c->cstart, c->bsum, c->wcount,
+                            c->wcstart, c->wsum, c->start_all, c->fluid_off, c->cell_of,
+                            c->rank_of, c->wcell_tmp, c->wrank, c->idx, c->widx, c->idx_all,
+                            c->wcell, c->dk};
+  HIP_TRY(c, timed(c, s, K_SCAN_REDUCE, [&] {
+            return dpd::launch_scan_reduce(s, c->NCELL, c->count, c->bsum, c->wcount, c->wsum);
+          }));
+  HIP_TRY(c, timed(c, s, K_SCAN_DOWN, [&] { return dpd::launch_scan_both(s, L); }));
+  HIP_TRY(c, timed(c, s, K_SCATTER, [&] { return dpd::launch_scatter_both(s, L); }));
+  HIP_TRY(c, timed(c, s, K_SORT, [&] { return dpd::launch_sort_both(s, L); }));
+  rc = order_walls(c, s, c->widx);
+  if (rc) return rc;
+  if (!c->wide)
+    HIP_TRY(c, timed(c, s, K_CODES, [&] {
+              return dpd::launch_quant_runs(s, c->NF + c->NW, c->idx_all, c->pos[c->cur], c->cq);
+            }));
+  return DPD_OK;
+}
+
+// Walls re-sorted by cell after their positions changed outside a step.  Reads the
+// walls at pos[cur] + NF (velocities at vt + NF), writes them back in cell
+// order (within a cell by storage index) to both position buffers and vt,
+// and rebuilds wcell and wcstart.
+int wall_pass(dpd_ctx *c, hipStream_t s) {
+  if (c->NW == 0) return DPD_OK;
+  const int rc = bin_walls(c, s, 0);
+  if (rc) return rc;
   HIP_TRY(c, timed(c, s, K_SCAN_REDUCE, [&] {
             return dpd::launch_scan_reduce(s, c->NCELL, c->wcount, c->bsum);
           }));
@@ -809,12 +852,7 @@ int wall_pass(dpd_ctx *c, hipStream_t s, int move) {
   HIP_TRY(c, timed(c, s, K_SORT, [&] {
             return dpd::launch_sort_wall_cells(s, c->NCELL, c->wcstart, c->idx, c->wcell);
           }));
-  // the sorted walls into both position buffers at once
-  HIP_TRY(c, timed(c, s, K_OTHER, [&] {
-            return dpd::launch_permute(s, c->NW, c->idx, c->wtmp, wp, c->wvtmp, wv, c->wtmp,
-                                       c->pos[b] + c->NF);
-          }));
-  return DPD_OK;
+  return order_walls(c, s, c->idx);
 }
 
 int enqueue_step(dpd_ctx *c, hipStream_t s) {
@@ -834,11 +872,7 @@ int enqueue_step(dpd_ctx *c, hipStream_t s) {
                                          c->count, c->bits, c->use_mask, c->quad, c->grid_f64,
                                          c->status, c->NF, c->wcstart, c->reflect ? 1 : 0);
           }));
-  if (c->moving) {
-    int rc = wall_pass(c, s, 1);
-    if (rc) return rc;
-  }
-  int rc = scan_scatter_sort(c, s, nullptr, c->dk, true, true);
+  const int rc = c->moving ? list_both(c, s) : scan_scatter_sort(c, s, nullptr, c->dk, true, true);
   if (rc) return rc;
   return force_pass(c, s, 0);
 }
@@ -888,7 +922,7 @@ int one_step(dpd_ctx *c) {
 // it every later summation order) depends only on the state, not on how the
 // context stored its particles before.
 int resort(dpd_ctx *c) {
-  int rc = c->moving ? wall_pass(c, c->stream, 0) : DPD_OK;
+  int rc = c->moving ? wall_pass(c, c->stream) : DPD_OK;
   if (!rc) rc = bin_all(c, c->stream);
   if (!rc) rc = scan_scatter_sort(c, c->stream, c->pos[c->cur]);
   if (rc) return rc;
@@ -1176,7 +1210,9 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
     c->wcell_tmp = (int32_t *)dalloc(c, 4 * nw);
     c->wrank = (int32_t *)dalloc(c, 4 * nw);
     c->wcount = (int32_t *)dalloc(c, 4 * ncell);
-    if (!c->wtmp || !c->wvtmp || !c->wcell_tmp || !c->wrank || !c->wcount)
+    c->widx = (int32_t *)dalloc(c, 4 * std::max<size_t>((size_t)NW, 1));
+    c->wsum = (int32_t *)dalloc(c, 4 * (size_t)c->nscan);
+    if (!c->wtmp || !c->wvtmp || !c->wcell_tmp || !c->wrank || !c->wcount || !c->widx || !c->wsum)
       return bail(fail(c, DPD_E_NOMEM, "device allocation failed"));
   }
   c->start_all = (int32_t *)dalloc(c, 4 * (ncell + 1 + dpd::kStartSlack));
@@ -2096,7 +2132,7 @@ int dpd_autotune(dpd_ctx *c, int32_t steps, int32_t *shape_out, double *ms_out) 
         // velocities, and the cell list of that order
         HIP_TRY(c, hipMemcpyAsync(c->vt + c->NF, save_wv, nwv, hipMemcpyDeviceToDevice,
                                   c->stream));
-        const int wrc = wall_pass(c, c->stream, 0);
+        const int wrc = wall_pass(c, c->stream);
         if (wrc && !rc) rc = wrc;
       }
       return DPD_OK;
@@ -2439,7 +2475,7 @@ int dpd_snapshot_io(dpd_ctx *c, int32_t dir, void *blob) {
   // moving walls: their cell runs follow the restored positions (the sort
   // within cells keeps the restored order)
   if (c->moving) {
-    int rc = wall_pass(c, c->stream, 0);
+    int rc = wall_pass(c, c->stream);
     if (rc) return rc;
   }
   c->gen += 1;

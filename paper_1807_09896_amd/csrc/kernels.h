@@ -42,10 +42,25 @@ hipError_t launch_bin(hipStream_t s, const KGeom &G, int64_t cell_off, int64_t n
 // Exclusive scan of count[0..ncell) into start[0..ncell] (start[ncell] =
 // total), count reset to 0, in two launches: per-block sums, then the
 // per-block scans, each block adding the sum of the block sums before it.
-hipError_t launch_scan_reduce(hipStream_t s, int64_t ncell, const int32_t *count, int32_t *bsum);
+hipError_t launch_scan_reduce(hipStream_t s, int64_t ncell, const int32_t *count, int32_t *bsum,
+                              const int32_t *wcount = nullptr, int32_t *wsum = nullptr);
 hipError_t launch_scan_down(hipStream_t s, int64_t ncell, int32_t *count, int32_t *start,
                             const int32_t *bsum, const int32_t *wstart, int32_t *start_all,
                             int32_t *fluid_off);
+
+// Fluid (n, binned into count) and moving walls (nw, binned into wcount) listed
+// together after launch_scan_reduce of both: starts, merged runs, the walls' order
+// (widx) and their cells in it (wcell).  launch_scatter_both also advances dk.
+struct BothLists {
+  int64_t ncell, n, nw;
+  int32_t *count, *start, *bsum, *wcount, *wstart, *wsum, *start_all, *fluid_off;
+  const int32_t *cell_of, *rank_of, *wcell_of, *wrank_of;
+  int32_t *idx, *widx, *idx_all, *wcell;
+  unsigned long long *dk;
+};
+hipError_t launch_scan_both(hipStream_t s, const BothLists &L);
+hipError_t launch_scatter_both(hipStream_t s, const BothLists &L);
+hipError_t launch_sort_both(hipStream_t s, const BothLists &L);
 
 // idx[start[cell_of[p]] + rank_of[p]] = p, then each cell's run sorted by p
 // (by the gid bits of key4[p].w when key4 is given), and copied to the fluid

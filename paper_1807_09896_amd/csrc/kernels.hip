@@ -222,13 +222,17 @@ __device__ __forceinline__ void scan_reduce_chunk(int64_t base, int64_t n,
   if (threadIdx.x == 0) *out = acc;
 }
 
+// With gridDim.y = 2 of the walls' counts too.
 template <int ITEMS>
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(int64_t n,
                                                               const int32_t *__restrict__ count,
-                                                              int32_t *__restrict__ bsum) {
+                                                              int32_t *__restrict__ bsum,
+                                                              const int32_t *__restrict__ wcount,
+                                                              int32_t *__restrict__ wsum) {
   __shared__ int lds[kScanThreads / 64];
-  scan_reduce_chunk<ITEMS>((int64_t)blockIdx.x * ITEMS * kScanThreads, n, count,
-                           bsum + blockIdx.x, lds);
+  scan_reduce_chunk<ITEMS>((int64_t)blockIdx.x * ITEMS * kScanThreads, n,
+                           blockIdx.y ? wcount : count, (blockIdx.y ? wsum : bsum) + blockIdx.x,
+                           lds);
 }
 
 // Each thread owns ITEMS consecutive cells; the block's cells are read
@@ -241,11 +245,15 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(int64_t n,
 // The chunk [base, min(base + ITEMS kScanThreads, n)) of the exclusive scan, offset
 // by the sum of everything before it; the last chunk (last) also writes the
 // entry n after the end.  count is cleared for the next step.
-template <int ITEMS, typename V, typename Prior>
+// BOTH: the walls' counts too, scanned into wstart in the upper halves of 64-bit
+// sums.
+template <int ITEMS, bool BOTH, typename V, typename Prior>
 __device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, bool last, Prior &&prior,
                                                 int32_t *__restrict__ count,
+                                                int32_t *__restrict__ wcount,
                                                 int32_t *__restrict__ start,
-                                                const int32_t *__restrict__ wstart,
+                                                std::conditional_t<BOTH, int32_t, const int32_t>
+                                                    *__restrict__ wstart,
                                                 int32_t *__restrict__ start_all,
                                                 int32_t *__restrict__ fluid_off, V *tile, V *lds) {
   V own[ITEMS];
@@ -255,6 +263,7 @@ __device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, bool la
     own[k] = 0;
     if (i < n) {
       own[k] = count[i];
+      if constexpr (BOTH) own[k] += (V)wcount[i] << 32;
     }
   }
   const V offset = prior();
@@ -264,6 +273,7 @@ __device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, bool la
     const int64_t i = base + local;
     if (i < n) {
       count[i] = 0;
+      if constexpr (BOTH) wcount[i] = 0;
     }
     tile[local + local / 32] = own[k];
   }
@@ -291,7 +301,12 @@ __device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, bool la
       const V at = tile[local + local / 32];
       const int st = (int)at;
       start[i] = st;
-      if (wstart) {
+      if constexpr (BOTH) {
+        const int w0 = (int)(at >> 32);
+        wstart[i] = w0;
+        start_all[i] = st + w0;
+        fluid_off[i] = st + w0 + (int)(own[k] >> 32);
+      } else if (wstart) {
         const int w0 = wstart[i], w1 = wstart[i + 1];
         start_all[i] = st + w0;
         fluid_off[i] = st + w1;
@@ -301,7 +316,10 @@ __device__ __forceinline__ void scan_down_chunk(int64_t base, int64_t n, bool la
   if (last && threadIdx.x == kScanThreads - 1) {
     const V end = offset + total;
     start[n] = (int)end;
-    if (wstart) {
+    if constexpr (BOTH) {
+      wstart[n] = (int)(end >> 32);
+      start_all[n] = (int)end + (int)(end >> 32);
+    } else if (wstart) {
       start_all[n] = (int)end + wstart[n];
     }
   }
@@ -316,14 +334,40 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(
   constexpr int chunk = ITEMS * kScanThreads;
   __shared__ int tile[chunk + chunk / 32];
   __shared__ int lds[kScanThreads / 64];
-  scan_down_chunk<ITEMS>(
+  scan_down_chunk<ITEMS, false>(
       (int64_t)blockIdx.x * chunk, n, blockIdx.x == gridDim.x - 1,
       [&] {
         int before = 0;
         for (int j = (int)threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) before += bsum[j];
         return block_sum(before, lds);
       },
-      count, start, wstart, start_all, fluid_off, tile, lds);
+      count, nullptr, start, wstart, start_all, fluid_off, tile, lds);
+}
+
+// Moving walls: the walls' counts scanned into wstart in the same pass.
+//
+// The five launches that list fluid and moving walls together (k_scan_reduce, this
+// one, k_scatter_both, k_sort_both, k_permute) take the place of nine of 5 to 8 us
+// each, most of it the launch: a step of 746,000 fluid and 304,000 wall particles
+// 178 to 167 us.
+template <int ITEMS>
+__global__ __launch_bounds__(kScanThreads) void k_scan_down_both(
+    int64_t n, int32_t *__restrict__ count, int32_t *__restrict__ start,
+    const int32_t *__restrict__ bsum, int32_t *__restrict__ wcount, int32_t *__restrict__ wstart,
+    const int32_t *__restrict__ wsum, int32_t *__restrict__ start_all,
+    int32_t *__restrict__ fluid_off) {
+  constexpr int chunk = ITEMS * kScanThreads;
+  __shared__ long long tile[chunk + chunk / 32];
+  __shared__ long long lds[kScanThreads / 64];
+  scan_down_chunk<ITEMS, true>(
+      (int64_t)blockIdx.x * chunk, n, blockIdx.x == gridDim.x - 1,
+      [&] {
+        long long before = 0;
+        for (int j = (int)threadIdx.x; j < (int)blockIdx.x; j += kScanThreads)
+          before += (long long)bsum[j] + ((long long)wsum[j] << 32);
+        return block_sum(before, lds);
+      },
+      count, wcount, start, wstart, start_all, fluid_off, tile, lds);
 }
 
 // idx[start[cell_of[p]] + rank_of[p]] = p for the n entries.  Threads n ..
@@ -358,6 +402,22 @@ __global__ void k_scatter(int64_t n, const int32_t *__restrict__ cell_of,
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (dk && p == 0) *dk += 1ull;
   scatter_one(p, n, cell_of, rank_of, start, idx, nw, wcell, wstart, start_all, idx_all);
+}
+
+// The same for n fluid particles and nw walls, each in an index array of its own.
+__global__ void k_scatter_both(int64_t n, const int32_t *__restrict__ cell_of,
+                               const int32_t *__restrict__ rank_of,
+                               const int32_t *__restrict__ start, int32_t *__restrict__ idx,
+                               int64_t nw, const int32_t *__restrict__ wcell_of,
+                               const int32_t *__restrict__ wrank_of,
+                               const int32_t *__restrict__ wstart, int32_t *__restrict__ widx,
+                               unsigned long long *__restrict__ dk) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (dk && p == 0) *dk += 1ull;
+  if (p < n)
+    idx[start[cell_of[p]] + rank_of[p]] = (int32_t)p;
+  else if (p - n < nw)
+    widx[wstart[wcell_of[p - n]] + wrank_of[p - n]] = (int32_t)(p - n);
 }
 
 // Insertion network of compare-exchanges over K registers.
@@ -472,6 +532,30 @@ __global__ void k_sort_wall_cells(int64_t ncell, const int32_t *__restrict__ sta
   sort_cell<false>(c, start, idx, nullptr, nullptr, nullptr);
   const int a = start[c], b = start[c + 1];
   for (int i = a; i < b; ++i) cell_out[i] = (int32_t)c;
+}
+
+// Fluid and moving walls: each cell's runs sorted by storage index, its merged run
+// written, and the cell of each sorted wall.  The first half of the threads take the
+// cells' fluid, the second (whole blocks) their walls.  (Moving the walls' records in
+// the same launch held a thread for two more dependent loads per wall: 20 us instead of
+// 8 and a launch of k_permute, 6.)
+__global__ __launch_bounds__(kBlock) void k_sort_both(
+    int64_t ncell, int64_t n, const int32_t *__restrict__ start, int32_t *__restrict__ idx,
+    const int32_t *__restrict__ wstart, int32_t *__restrict__ widx,
+    const int32_t *__restrict__ start_all, const int32_t *__restrict__ fluid_off,
+    int32_t *__restrict__ idx_all, int32_t *__restrict__ wcell) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= ncell) return;
+  if (blockIdx.y == 0) {
+    sort_run(idx, start[c], start[c + 1], idx_all + fluid_off[c]);
+    return;
+  }
+  const int a = wstart[c], b = wstart[c + 1], out = start_all[c] - a;
+  sort_run(widx, a, b, nullptr);
+  for (int w = a; w < b; ++w) {
+    wcell[w] = (int32_t)c;
+    idx_all[out + w] = (int32_t)(n + w);
+  }
 }
 
 // The whole cell list of small boxes in one launch: the exclusive scan of a
@@ -1889,14 +1973,14 @@ __device__ __attribute__((noinline)) void p_down(const PArgs *__restrict__ A0, i
   int *tile = lds_ptr(tile0), *lds = lds_ptr(lds0);
   const int64_t co = A->boxes[box].co, ncell = A->boxes[box].ncell, fo = A->boxes[box].fo;
   const bool last = (int64_t)(a + 1) * kScanChunk >= ncell;
-  scan_down_chunk<kScanItems>(
+  scan_down_chunk<kScanItems, false>(
       co + (int64_t)a * kScanChunk, co + ncell, last,
       [&] {
         int before = 0;
         for (int j = (int)threadIdx.x; j < a; j += kScanThreads) before += A->bsum[b + j];
         return (int)fo + block_sum(before, lds);
       },
-      A->count, A->cstart, A->wcstart, A->start_all, A->fluid_off, tile, lds);
+      A->count, nullptr, A->cstart, A->wcstart, A->start_all, A->fluid_off, tile, lds);
 }
 
 __device__ __attribute__((noinline)) void p_scatter(const PArgs *__restrict__ A0, int a0, int b0) {
@@ -2046,12 +2130,40 @@ hipError_t launch_bin(hipStream_t s, const KGeom &G, int64_t cell_off, int64_t n
   return hipGetLastError();
 }
 
-hipError_t launch_scan_reduce(hipStream_t s, int64_t ncell, const int32_t *count, int32_t *bsum) {
-  const unsigned grid = (unsigned)scan_blocks(ncell);
+hipError_t launch_scan_reduce(hipStream_t s, int64_t ncell, const int32_t *count, int32_t *bsum,
+                              const int32_t *wcount, int32_t *wsum) {
+  const dim3 grid((unsigned)scan_blocks(ncell), wcount ? 2 : 1);
   if (scan_items(ncell) == kScanItems)
-    k_scan_reduce<kScanItems><<<grid, kScanThreads, 0, s>>>(ncell, count, bsum);
+    k_scan_reduce<kScanItems><<<grid, kScanThreads, 0, s>>>(ncell, count, bsum, wcount, wsum);
   else
-    k_scan_reduce<kScanFew><<<grid, kScanThreads, 0, s>>>(ncell, count, bsum);
+    k_scan_reduce<kScanFew><<<grid, kScanThreads, 0, s>>>(ncell, count, bsum, wcount, wsum);
+  return hipGetLastError();
+}
+
+hipError_t launch_scan_both(hipStream_t s, const BothLists &L) {
+  const unsigned nb = (unsigned)scan_blocks(L.ncell);
+  if (scan_items(L.ncell) == kScanItems)
+    k_scan_down_both<kScanItems><<<nb, kScanThreads, 0, s>>>(L.ncell, L.count, L.start, L.bsum,
+                                                             L.wcount, L.wstart, L.wsum,
+                                                             L.start_all, L.fluid_off);
+  else
+    k_scan_down_both<kScanFew><<<nb, kScanThreads, 0, s>>>(L.ncell, L.count, L.start, L.bsum,
+                                                           L.wcount, L.wstart, L.wsum,
+                                                           L.start_all, L.fluid_off);
+  return hipGetLastError();
+}
+
+hipError_t launch_scatter_both(hipStream_t s, const BothLists &L) {
+  k_scatter_both<<<grid_for(std::max<int64_t>(L.n + L.nw, 1)), kBlock, 0, s>>>(
+      L.n, L.cell_of, L.rank_of, L.start, L.idx, L.nw, L.wcell_of, L.wrank_of, L.wstart, L.widx,
+      L.dk);
+  return hipGetLastError();
+}
+
+hipError_t launch_sort_both(hipStream_t s, const BothLists &L) {
+  k_sort_both<<<dim3(grid_for(L.ncell), 2), kBlock, 0, s>>>(L.ncell, L.n, L.start, L.idx, L.wstart,
+                                                            L.widx, L.start_all, L.fluid_off,
+                                                            L.idx_all, L.wcell);
   return hipGetLastError();
 }
 
