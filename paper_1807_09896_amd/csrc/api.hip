@@ -1656,23 +1656,48 @@ int stored_window(dpd_ctx *c) {
   return DPD_OK;
 }
 
-// The VJP kernels of step t from its arrays st: A holds the adjoints of X_{t+1}
-// (slot order), B receives those of X_t.
-int step_vjp(dpd_ctx *c, const StoredStep &st, uint64_t t, const float4 *A, float4 *B,
-             double *dphi) {
+// The preparation of step t's VJP from the arrays st, velocities' adjoints to vn.
+dpd::AdjPrep adj_prep(dpd_ctx *c, const StoredStep &st, float4 *vn) {
+  Window &W = c->win;
+  const int64_t NF = c->NF;
+  return {st.idx, st.D,  st.V, W.lw,       W.axis, W.nbins, W.scale, W.adj + 6 * NF,
+          vn,     W.adj + 8 * NF, W.part_g};
+}
+
+// The VJP kernels of step t from its arrays st, prepared with the velocities' adjoints vn.
+// With next, the preparation of the step before follows in the same launch, else B
+// receives the adjoints of X_t.
+int step_vjp(dpd_ctx *c, const StoredStep &st, uint64_t t, const float4 *vn, float4 *B,
+             const dpd::AdjPrep *next, double *dphi) {
   Window &W = c->win;
   const int64_t NF = c->NF;
   hipStream_t s = c->stream;
-  float4 *rn = W.adj + 6 * NF, *vn = W.adj + 7 * NF, *fbar = W.adj + 8 * NF;
+  float4 *rn = W.adj + 6 * NF, *fbar = W.adj + 8 * NF;
   float4 *rt = W.adj + 9 * NF, *vtb = W.adj + 10 * NF;
-  HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 0, st.idx, st.D, st.V, A, A + NF, A + 2 * NF,
-                                  W.lw, W.axis, W.nbins, W.scale, rn, vn, fbar, W.part_g));
   HIP_TRY(c, dpd::launch_force_vjp(s, c->wide ? 0 : c->fblock, c->boxes, c->ftiles, c->n_ftiles,
                                    NF, (int32_t)(NF + c->NW), st.D, st.V, st.idx, st.idx_all,
                                    st.start_all, fbar, rn, rt, vtb, W.dk0, t + 1, W.part_f));
   HIP_TRY(c, dpd::launch_integrate_vjp(s, c->boxes, NF, st.X, st.X + NF, st.X + 2 * NF, st.V, rt,
                                        vtb, vn, c->grid, c->grid_f64, dphi, B, B + NF,
-                                       B + 2 * NF));
+                                       B + 2 * NF, next));
+  return DPD_OK;
+}
+
+// The backward sweep of a window kept whole: A holds the adjoints of the last state (slot
+// order; its memory is used), B receives those of the first.
+int stored_sweep(dpd_ctx *c, float4 *A, float4 *B, double *dphi) {
+  Window &W = c->win;
+  const int64_t NF = c->NF;
+  float4 *vn = W.adj + 7 * NF, *other = A;
+  HIP_TRY(c, dpd::launch_adj_prep(c->stream, c->boxes, NF, 0, A, A + NF, A + 2 * NF,
+                                  adj_prep(c, stored_step(c, W.steps - 1), vn)));
+  for (int t = W.steps - 1; t >= 0; --t) {
+    dpd::AdjPrep next{};
+    if (t > 0) next = adj_prep(c, stored_step(c, t - 1), other);
+    const int rc = step_vjp(c, stored_step(c, t), (uint64_t)t, vn, B, t > 0 ? &next : nullptr, dphi);
+    if (rc) return rc;
+    std::swap(vn, other);
+  }
   return DPD_OK;
 }
 
@@ -1692,8 +1717,11 @@ int backward_step(dpd_ctx *c, const float4 *x, uint64_t t, const float4 *A, floa
                                    0));
   int rc = scan_scatter_sort(c, s, nullptr, nullptr, false);
   if (rc) return rc;
-  return step_vjp(c, {const_cast<float4 *>(x), W.wpos, c->vt, c->idx, c->idx_all, c->start_all}, t,
-                  A, B, dphi);
+  const StoredStep st = {const_cast<float4 *>(x), W.wpos,     c->vt,
+                         c->idx,                  c->idx_all, c->start_all};
+  float4 *vn = W.adj + 7 * NF;
+  HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 0, A, A + NF, A + 2 * NF, adj_prep(c, st, vn)));
+  return step_vjp(c, st, t, vn, B, nullptr, dphi);
 }
 
 int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
@@ -1728,8 +1756,8 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
   // walls and the pad of the sweep's position array
   HIP_TRY(c, hipMemcpyAsync(W.wpos + NF, c->pos[c->cur] + NF, 16 * (size_t)(c->NW + 1),
                             hipMemcpyDeviceToDevice, s));
-  for (int t = W.steps - 1; t >= 0 && !rc && !recompute; --t) {
-    rc = step_vjp(c, stored_step(c, t), (uint64_t)t, A, B, dphi);
+  if (!recompute) {
+    rc = stored_sweep(c, A, B, dphi);
     std::swap(A, B);
   }
   for (int seg = W.nck - 1; seg >= 0 && !rc && recompute; --seg) {
@@ -1758,9 +1786,8 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
     HIP_TRY(c, dpd::launch_bin(s, p.G, p.co, NF, W.wpos, c->cell_of, c->rank_of, c->count));
     rc = scan_scatter_sort(c, s, nullptr, nullptr, false);
     if (!rc) {
-      HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 1, c->idx, W.wpos, c->vt, A, A + NF,
-                                      A + 2 * NF, W.lw, W.axis, W.nbins, W.scale, nullptr,
-                                      nullptr, fbar, W.part_g));
+      HIP_TRY(c, dpd::launch_adj_prep(s, c->boxes, NF, 1, A, A + NF, A + 2 * NF,
+                                      adj_prep(c, {}, nullptr)));
       HIP_TRY(c, dpd::launch_force_vjp(s, c->wide ? 0 : c->fblock, c->boxes, c->ftiles, c->n_ftiles, NF,
                                        (int32_t)(NF + c->NW), W.wpos, c->vt, c->idx, c->idx_all,
                                        c->start_all, fbar, nullptr, rt, vtb, W.dk0, 0, W.part_f));

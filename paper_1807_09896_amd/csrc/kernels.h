@@ -297,11 +297,18 @@ hipError_t launch_vt_from_v(hipStream_t s, int64_t nf, const float4 *vel4, float
 hipError_t launch_set_u64(hipStream_t s, unsigned long long *p, unsigned long long v);
 
 int adj_prep_blocks(int64_t nf);
+struct AdjPrep {
+  const int32_t *idx;
+  const float4 *pos4, *vt4;
+  const float *lw;
+  int axis, nbins;
+  float scale;
+  float4 *rn, *vn, *fbar;
+  double *part_g;
+};
 hipError_t launch_adj_prep(hipStream_t s, const Box *boxes, int64_t nf, int initial,
-                           const int32_t *idx, const float4 *pos4, const float4 *vt4,
                            const float4 *rb_s, const float4 *vb_s, const float4 *fb_s,
-                           const float *lw, int axis, int nbins, float scale, float4 *rn,
-                           float4 *vn, float4 *fbar, double *part_g);
+                           const AdjPrep &N);
 int force_vjp_blocks(int ntiles);
 // block 0: the kernel with 16 lanes per particle, over tiles of kWideParts.
 hipError_t launch_force_vjp(hipStream_t s, int block, const Box *boxes, const Tile *tiles,
@@ -314,7 +321,7 @@ hipError_t launch_integrate_vjp(hipStream_t s, const Box *boxes, int64_t nf, con
                                 const float4 *vel_t, const float4 *frc_t, const float4 *vt4,
                                 const float4 *rt, const float4 *vtb, const float4 *vn,
                                 const void *grid, int grid_f64, double *dphi, float4 *rb_out,
-                                float4 *vb_out, float4 *fb_out);
+                                float4 *vb_out, float4 *fb_out, const AdjPrep *next = nullptr);
 hipError_t launch_reduce_partials(hipStream_t s, int nb_f, const double *part_f, int nb_g,
                                   const double *part_g, double *out);
 
