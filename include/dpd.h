@@ -337,7 +337,9 @@ int dpd_set_phi(dpd_ctx *ctx, int32_t r, const void *data, int32_t on_device);
  * number of such terms and the bin the FP32 decision
  * clamp(floor(fl(x_axis * fl32(nbins / L_axis))), 0, nbins - 1).
  * profile (device, nbins float64) and counts (device, nbins int64: N_b) may
- * be NULL.  A checkpoint of the fluid state is stored every ckpt steps
+ * be NULL.  A window whose steps' states and cell lists fit 2 GiB of device
+ * memory (and can be allocated) is kept whole; otherwise a checkpoint of the
+ * fluid state is stored every ckpt steps
  * (1 <= ckpt <= steps, nbins <= 1024); the context ends at the window's last
  * state.  DPD_E_STATE for a batch context; DPD_E_INVAL for moving walls,
  * DPD_FLAG_SPECULAR or DPD_FLAG_SPH (the adjoint covers the a_ij w force and
@@ -347,7 +349,8 @@ int dpd_set_phi(dpd_ctx *ctx, int32_t r, const void *data, int32_t on_device);
  * nbins float64) by the hand-written adjoint of every step of the window
  * (pair force of Eq. 3-10, the Groot-Warren update and the bounce-back of
  * Eq. 16-17 with the recorded events held fixed, and the starting force),
- * recomputing each ckpt-step segment from its checkpoint.  The bins, pair
+ * from the steps kept or recomputing each ckpt-step segment from its checkpoint.
+ * The bins, pair
  * sets and events are those of the forward window.  grads (host, 6 float64)
  * receives dL/d{a_ff, a_fw, gamma, g_x, g_y, g_z} (gamma through both the
  * dissipative amplitude and sigma = sqrt(2 gamma kBT); the sigma path is

@@ -427,11 +427,11 @@ int build_tiles(dpd_ctx *c, int size, Tile **dst, int *n, int *cap, bool without
 int build_persistent(dpd_ctx *c);
 
 // The context's wider integrate shape: 4 particles per thread
-// (86 VGPRs, five wavefronts per SIMD, four particles' loads in flight per
+// (80 VGPRs, six wavefronts per SIMD, four particles' loads in flight per
 // lane) for contexts of at least 2^20 fluid particles whose boxes all use
 // the plain instance; 2 otherwise.  The instance with moving walls and
-// specular reflection needs 118 VGPRs at 4 (Couette channel: integrate 0.051
-// -> 0.073 ms).
+// specular reflection needs 112 VGPRs at 4 and took longer (Couette channel:
+// integrate 0.051 -> 0.073 ms).
 int wide_ppt(const dpd_ctx *c) { return !c->reflect && c->NF >= ((int64_t)1 << 20) ? 4 : 2; }
 
 // The shape a context starts with: 1 particle per thread below 2^20, where a

@@ -841,7 +841,7 @@ __global__ void k_check_phi(const KGeom G, const T *__restrict__ grid, int64_t n
 // ---------------------------------------------------------------------------
 // Integrate + reflect + bin (Groot-Warren drift, Sec. II.C bounce-back)
 //
-// Each thread advances two particles (p and p + kBlock of a 2 kBlock tile),
+// Each thread advances PPT particles (p, p + kBlock, ... of a tile of PPT kBlock),
 // so that their loads and atomics are in flight together.  Ranks within a
 // cell come from one atomic per run of equal cells in a wavefront: the
 // particles arrive sorted by their previous cell and most keep it, so runs
@@ -2021,7 +2021,7 @@ __device__ __attribute__((noinline)) void p_force(const PArgs *__restrict__ A0, 
 template <typename T, int PPT, bool REFLECT, bool SPH>
 // Six wavefronts per SIMD, as the pair kernel: the pair list (26 KB per
 // block) limits a CU to six blocks anyway, and the phase functions are
-// allocated separately, the largest (the pair force, 74 VGPRs in its own
+// allocated separately, the largest (the pair force, 73 VGPRs in its own
 // kernel) with a few more registers as a callee.
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void
 k_step_persistent(const PArgs *__restrict__ A) {
