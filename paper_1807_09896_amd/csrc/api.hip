@@ -157,6 +157,10 @@ struct dpd_ctx {
   bool use_graph = false;
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
+  // steps in a row (step_run): second prediction and cell counts, in turn with vt and
+  // count (null: not used)
+  float4 *vt2 = nullptr;
+  int32_t *count2 = nullptr;
 
   // persistent step (dpd_use_persistent): work items, per-(box, phase) item
   // counts and arrivals, the queue counter, per-box scan chunk sums, 256-particle
@@ -203,6 +207,7 @@ void *dalloc(dpd_ctx *c, size_t bytes) {
     p = c->al.alloc(bytes, (void *)c->stream, c->al.user);
   } else if (hipMalloc(&p, bytes) != hipSuccess) {
     p = nullptr;
+    (void)hipGetLastError();   // reported by the caller, or done without
   }
   if (p) c->owned.push_back(p);
   return p;
@@ -454,6 +459,13 @@ int default_ppt(const dpd_ctx *c) {
 // 97,000 (86 / 74 at 129,000).  The bits are the same either way.
 constexpr int64_t kWideMax = 65536;
 bool use_wide(const dpd_ctx *c) { return c->NF <= kWideMax; }
+
+// Steps in a row (step_run) in contexts whose pair kernel's blocks, of 16 particles, are
+// all on the chip at once (five on each of 256 CUs): where they are not, one lane of 16
+// drifting costs as much as the launch it saves.  Step, us, without / with: 19.6 /
+// 16.2 at 2,400 particles, 20.5 / 17.2 at 7,400, 24.1 / 21.9 at 16,500, 25.4 / 24.4 at
+// 20,000; 32.8 / 33.1 at 27,000, 37.9 / 40.4 at 61,000.
+constexpr int kRunTiles = 1280;
 
 // Blocks per box of the one-launch cell list (k_cells_box); 0 where some box does
 // not fit its LDS, where the brick kernel needs the separate launches' arrays, and
@@ -748,7 +760,7 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
 }
 
 // Forces at the current state in sorted order; init = 1 keeps velocities.
-int force_pass(dpd_ctx *c, hipStream_t s, int init) {
+int force_pass(dpd_ctx *c, hipStream_t s, int init, const dpd::NextStep *next = nullptr) {
   const int a = c->cur, b = 1 - c->cur;
   int32_t *const clear = c->box_list > 1 ? c->count : nullptr;
   if (c->n_otiles > 0)
@@ -758,7 +770,7 @@ int force_pass(dpd_ctx *c, hipStream_t s, int init) {
                                               c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
                                               c->idx_all, c->start_all, c->pos[b], c->vel[b],
                                               c->frc[b], c->dk, c->status, c->sph ? 1 : 0,
-                                              clear, (int32_t)c->NCELL);
+                                              clear, (int32_t)c->NCELL, next);
               return dpd::launch_force(s, c->fblock, c->boxes, c->otiles, c->n_otiles, c->NF,
                                        (int32_t)(c->NF + c->NW), (int32_t)c->NCELL, init,
                                        c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
@@ -855,6 +867,17 @@ int wall_pass(dpd_ctx *c, hipStream_t s) {
   return order_walls(c, s, c->idx);
 }
 
+int drift(dpd_ctx *c, hipStream_t s) {
+  const int a = c->cur;
+  HIP_TRY(c, timed(c, s, K_INTEGRATE, [&] {
+            return dpd::launch_integrate(s, c->ppt, c->boxes, c->itiles, c->n_itiles, c->pos[a],
+                                         c->pos[a], c->vel[a], c->frc[a], c->vt, c->cell_of, c->rank_of,
+                                         c->count, c->bits, c->use_mask, c->quad, c->grid_f64,
+                                         c->status, c->NF, c->wcstart, c->reflect ? 1 : 0);
+          }));
+  return DPD_OK;
+}
+
 int enqueue_step(dpd_ctx *c, hipStream_t s) {
   const int a = c->cur;
   if (c->persistent) {
@@ -866,13 +889,9 @@ int enqueue_step(dpd_ctx *c, hipStream_t s) {
     c->cur = 1 - a;
     return DPD_OK;
   }
-  HIP_TRY(c, timed(c, s, K_INTEGRATE, [&] {
-            return dpd::launch_integrate(s, c->ppt, c->boxes, c->itiles, c->n_itiles, c->pos[a],
-                                         c->pos[a], c->vel[a], c->frc[a], c->vt, c->cell_of, c->rank_of,
-                                         c->count, c->bits, c->use_mask, c->quad, c->grid_f64,
-                                         c->status, c->NF, c->wcstart, c->reflect ? 1 : 0);
-          }));
-  const int rc = c->moving ? list_both(c, s) : scan_scatter_sort(c, s, nullptr, c->dk, true, true);
+  int rc = drift(c, s);
+  if (rc) return rc;
+  rc = c->moving ? list_both(c, s) : scan_scatter_sort(c, s, nullptr, c->dk, true, true);
   if (rc) return rc;
   return force_pass(c, s, 0);
 }
@@ -914,6 +933,30 @@ int one_step(dpd_ctx *c) {
   c->k += 1;
   c->steps += 1;
   return DPD_OK;
+}
+
+// n >= 2 steps in a row of a small context (kRunTiles): the pair kernel with 16 lanes per
+// particle goes on to the next step's drift, so only the first step has a launch for
+// it.  The results are those of n steps one by one, and the launches are direct with
+// use_graph too: two a step keep the GPU busier than a replay a step (16.2 against 20.5
+// us at 2,400 particles, 21.8 against 26.2 at 16,500).
+int step_run(dpd_ctx *c, int64_t n) {
+  int rc = drift(c, c->stream);
+  for (int64_t s = 0; s < n && !rc; ++s) {
+    const bool last = s + 1 == n;
+    rc = scan_scatter_sort(c, c->stream, nullptr, c->dk, true, true);
+    if (rc) break;
+    const dpd::NextStep next = {c->bits, c->use_mask, c->grid_f64, c->quad,
+                                c->vt2,  c->cell_of,  c->rank_of,  c->count2};
+    rc = force_pass(c, c->stream, 0, last ? nullptr : &next);
+    if (!last) {
+      std::swap(c->vt, c->vt2);
+      std::swap(c->count, c->count2);
+    }
+    c->k += 1;
+    c->steps += 1;
+  }
+  return rc;
 }
 
 // Re-sort the fluid state into cell order after positions changed outside a
@@ -1390,6 +1433,21 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   // uneven boxes, 4 each: 110.9 to 112.1)
   c->box_codes = c->box_list == 16;
   if (!rc) rc = set_shapes(c, default_ppt(c), 256);
+  // steps in a row (step_run), where the buffers can be had
+  if (!rc && c->wide && c->box_list && c->n_otiles <= kRunTiles) {
+    const size_t vt_bytes = 16 * (size_t)(c->NF + c->NW + 1), count_bytes = 4 * (size_t)c->NCELL;
+    c->vt2 = (float4 *)dalloc(c, vt_bytes);
+    c->count2 = (int32_t *)dalloc(c, count_bytes);
+    if (c->vt2 && c->count2) {
+      chk(dpd::launch_fill_zero(c->stream, c->vt2, vt_bytes), "zero predictions");
+      chk(dpd::launch_fill_zero(c->stream, c->count2, count_bytes), "zero counts");
+    } else {
+      if (c->vt2) dfree(c, c->vt2);
+      if (c->count2) dfree(c, c->count2);
+      c->vt2 = nullptr;
+      c->count2 = nullptr;
+    }
+  }
   if (rc) return bail(rc);
   c->cur = 0;
   c->k = 0;
@@ -1902,6 +1960,8 @@ int dpd_replica_count(const dpd_ctx *c) { return c ? c->R : DPD_E_INVAL; }
 int dpd_step(dpd_ctx *c, int64_t nsteps) {
   if (!c) return DPD_E_INVAL;
   if (nsteps < 0) return fail(c, DPD_E_INVAL, "negative step count");
+  if (nsteps > 1 && c->vt2 && !c->reflect && !c->persistent && !c->timing)
+    return step_run(c, nsteps);
   for (int64_t s = 0; s < nsteps; ++s) {
     int rc = one_step(c);
     if (rc) return rc;

@@ -209,12 +209,22 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
 
 // The same pair forces with 16 lanes per particle, for small contexts, over
 // tiles of up to kWideParts fluid slots.  It reads no coarse codes.
+// With next the launch also does what launch_integrate would do next (plain bounce-back
+// off resting walls): pos_out receives the drifted positions, next the rest.
+struct NextStep {
+  const uint32_t *bits;
+  int use_mask, grid_f64;
+  const void *quad;
+  float4 *vt;
+  int32_t *cell_of, *rank_of, *count;
+};
 hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,
                              int64_t NF, int init, const float4 *pos4, const float4 *vt4,
                              const float4 *vel4, const float4 *frc4, const int32_t *idx,
                              const int32_t *idx_all, const int32_t *start_all, float4 *pos_out,
                              float4 *vel_out, float4 *frc_out, const unsigned long long *dk,
-                             Status *st, int sph, int32_t *clear, int32_t ncell_all);
+                             Status *st, int sph, int32_t *clear, int32_t ncell_all,
+                             const NextStep *next = nullptr);
 
 // The same pair forces, body force and velocity update for the boxes cut
 // into bricks: one block per brick stages the brick's cells and a one-cell

@@ -1,0 +1,78 @@
+"""Steps that follow one another in a call (two launches each in small contexts) against
+the same steps one call each, bit for bit."""
+import numpy as np
+import pytest
+
+import workloads
+from gpu_helpers import require_gpu
+from test_gpu_small_contexts import _edge_box, _sph
+
+pytestmark = pytest.mark.gpu
+
+P = workloads.default_params
+
+
+@pytest.fixture(scope="module")
+def dpd():
+    require_gpu()
+    import paper_1807_09896_amd as dpd
+    dpd.load_library()
+    return dpd
+
+
+def _slab(dtype, seed):
+    return workloads.slab_system(L=(9.0, 8.0, 9.0), seed_fluid=seed, seed_wall=seed + 1,
+                                 grid_dtype=dtype, params=P(seed=seed))
+
+
+CASES = {
+    # 16 blocks per box, float32 and float64 grids
+    "float32": lambda: [_slab(np.float32, 31)],
+    "float64": lambda: [_slab(np.float64, 33)],
+    "sph": lambda: [_sph(workloads.sinusoid_slit_system(L=(12.0, 8.0, 12.0), base=3.0, amp=1.0))],
+    # one block per box, whose launch clears the counts itself
+    "one_block": lambda: [_edge_box((7, 8, 6), 900 + 37 * r) for r in range(3)],
+    "uneven": lambda: [_edge_box((4, 4, 4), 1), _slab(np.float32, 35), _edge_box((6, 5, 4), 1300)],
+    # not eligible: reflections with the normal's component only
+    "specular": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=0.0, seed=36, specular=True)],
+}
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("name", list(CASES))
+def test_same_bits(dpd, name, graph):
+    import torch
+    boxes = CASES[name]()
+    print("steps in a row", name, graph, [s.n for s in boxes], flush=True)
+    one, row = dpd.Simulation(boxes), dpd.Simulation(boxes, graph=graph)
+
+    def same(what):
+        assert one.counters() == row.counters(), what
+        for r in range(len(boxes)):
+            a, b = one.state(r), row.state(r)
+            for k in a:
+                assert torch.equal(a[k], b[k]), (what, r, k)
+            assert torch.equal(one.forces(r), row.forces(r)), (what, r)
+            assert one.pairs(r).shape == row.pairs(r).shape, (what, r)
+
+    for n in (2, 3, 1, 4, 7, 2):
+        for _ in range(n):
+            one.step(1)
+        row.step(n)
+        same(n)
+    # a restored state goes on alike, and so does one after set_params
+    blob = row.snapshot()
+    row.step(5)
+    row.restore(blob)
+    one.step(1)
+    one.step(1)
+    row.step(2)
+    same("restored")
+    row.kernel_times(1)
+    row.step(3)
+    row.kernel_times(0)
+    for _ in range(3):
+        one.step(1)
+    same("timed")
+    one.close()
+    row.close()
