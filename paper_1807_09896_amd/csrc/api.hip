@@ -759,6 +759,11 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
   return DPD_OK;
 }
 
+// The next drift in the pair kernel's launch, to pos and vt, binned into count2.
+dpd::NextStep next_step(dpd_ctx *c, float4 *pos, float4 *vt) {
+  return {c->bits, c->use_mask, c->grid_f64, c->quad, pos, vt, c->cell_of, c->rank_of, c->count2};
+}
+
 // Forces at the current state in sorted order; init = 1 keeps velocities.
 int force_pass(dpd_ctx *c, hipStream_t s, int init, const dpd::NextStep *next = nullptr) {
   const int a = c->cur, b = 1 - c->cur;
@@ -946,8 +951,7 @@ int step_run(dpd_ctx *c, int64_t n) {
     const bool last = s + 1 == n;
     rc = scan_scatter_sort(c, c->stream, nullptr, c->dk, true, true);
     if (rc) break;
-    const dpd::NextStep next = {c->bits, c->use_mask, c->grid_f64, c->quad,
-                                c->vt2,  c->cell_of,  c->rank_of,  c->count2};
+    const dpd::NextStep next = next_step(c, c->pos[1 - c->cur], c->vt2);
     rc = force_pass(c, c->stream, 0, last ? nullptr : &next);
     if (!last) {
       std::swap(c->vt, c->vt2);
@@ -1644,6 +1648,7 @@ int stored_window_step(dpd_ctx *c, int t, bool last) {
   const int64_t NF = c->NF;
   const int a = c->cur, b = 1 - a;
   float4 *const next = last ? nullptr : stored_step(c, t + 1).X;
+  const bool row = c->vt2 && !c->timing;   // as step_run: the drifts in the pair kernel
   struct Saved {
     float4 *pos[2], *vel[2], *frc[2], *vt;
     int32_t *idx, *idx_all, *start_all;
@@ -1662,14 +1667,19 @@ int stored_window_step(dpd_ctx *c, int t, bool last) {
     c->frc[b] = next + 2 * NF;
   }
   auto launches = [&]() -> int {
-    HIP_TRY(c, timed(c, c->stream, K_INTEGRATE, [&] {
+    if (t == 0 || !row)
+      HIP_TRY(c, timed(c, c->stream, K_INTEGRATE, [&] {
               return dpd::launch_integrate(c->stream, c->ppt, c->boxes, c->itiles, c->n_itiles,
                                            st.X, st.D, st.X + NF, st.X + 2 * NF, st.V, c->cell_of,
                                            c->rank_of, c->count, c->bits, c->use_mask, c->quad,
                                            c->grid_f64, c->status, NF, c->wcstart, 0);
             }));
     int rc = scan_scatter_sort(c, c->stream, nullptr, c->dk, true, true);
-    return rc ? rc : force_pass(c, c->stream, 0);
+    if (rc || !row || last) return rc ? rc : force_pass(c, c->stream, 0);
+    const dpd::NextStep drifted = next_step(c, stored_step(c, t + 1).D, stored_step(c, t + 1).V);
+    rc = force_pass(c, c->stream, 0, &drifted);
+    std::swap(c->count, c->count2);
+    return rc;
   };
   const int rc = launches();
   for (int q = 0; q < 2; ++q) {

@@ -210,12 +210,12 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
 // The same pair forces with 16 lanes per particle, for small contexts, over
 // tiles of up to kWideParts fluid slots.  It reads no coarse codes.
 // With next the launch also does what launch_integrate would do next (plain bounce-back
-// off resting walls): pos_out receives the drifted positions, next the rest.
+// off resting walls), into next; the drifted positions may take pos_out's place.
 struct NextStep {
   const uint32_t *bits;
   int use_mask, grid_f64;
   const void *quad;
-  float4 *vt;
+  float4 *pos, *vt;
   int32_t *cell_of, *rank_of, *count;
 };
 hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,

@@ -1638,9 +1638,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
       atomicAdd(&st->nonfinite, 1ull);
     vel_out[s] = fin.vel;
     frc_out[s] = fin.frc;
-    if constexpr (std::is_void_v<T>) {
-      pos_out[s] = pi;
-    } else {
+    if (std::is_void_v<T> || next.pos != pos_out) pos_out[s] = pi;
+    if constexpr (!std::is_void_v<T>) {
       const int co = (int)B.co;
       const Moved m = integrate_one<T, false>(
           G, P, true, pi, fin.vel, fin.frc, next.bits + B.bo, next.use_mask,
@@ -1648,7 +1647,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
           nullptr);
       const int cell = co + m.cell;
       const int rank = atomicAdd(&next.count[cell], 1);
-      pos_out[s] = m.pos;
+      next.pos[s] = m.pos;
       next.vt[s] = m.vt;
       next.cell_of[s] = cell;
       next.rank_of[s] = rank;
