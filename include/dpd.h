@@ -273,8 +273,8 @@ int dpd_replica_profile(dpd_ctx *ctx, int32_t r, int32_t axis, int32_t nbins, do
 
 /* enable != 0: dpd_step replays one captured HIP graph per step (the launch
  * sequence of a step, captured on first use on a private stream and replayed
- * on the context stream; calls of several steps of a small context launch
- * directly, which is faster there; the random-number index k lives on the device
+ * on the context stream; calls of several steps launch directly where the
+ * pair kernel goes on to the next step's drift, which is faster; the random-number index k lives on the device
  * and is
  * advanced inside the graph, so replays draw fresh numbers).  Results are
  * bit-identical to direct launches.  Per-kernel timing, when enabled, uses

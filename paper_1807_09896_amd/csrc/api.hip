@@ -460,11 +460,12 @@ int default_ppt(const dpd_ctx *c) {
 constexpr int64_t kWideMax = 65536;
 bool use_wide(const dpd_ctx *c) { return c->NF <= kWideMax; }
 
-// Steps in a row (step_run) in contexts whose pair kernel's blocks, of 16 particles, are
-// all on the chip at once (five on each of 256 CUs): where they are not, one lane of 16
-// drifting costs as much as the launch it saves.  Step, us, without / with: 19.6 /
-// 16.2 at 2,400 particles, 20.5 / 17.2 at 7,400, 24.1 / 21.9 at 16,500, 25.4 / 24.4 at
-// 20,000; 32.8 / 33.1 at 27,000, 37.9 / 40.4 at 61,000.
+// Steps in a row (step_run) where the pair kernel has 16 lanes per particle: up to this
+// many blocks, of 16 particles, which are all on the chip at once (five on each of
+// 256 CUs); where they are not, one lane of 16 drifting costs as much as the launch it
+// saves.  Step, us, without / with: 19.6 / 16.2 at 2,400 particles, 20.5 / 17.2 at
+// 7,400, 24.1 / 21.9 at 16,500, 25.4 / 24.4 at 20,000; 32.8 / 33.1 at 27,000, 37.9 /
+// 40.4 at 61,000.  With one lane per particle it pays at every size (force_tile).
 constexpr int kRunTiles = 1280;
 
 // Blocks per box of the one-launch cell list (k_cells_box); 0 where some box does
@@ -761,7 +762,9 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
 
 // The next drift in the pair kernel's launch, to pos and vt, binned into count2.
 dpd::NextStep next_step(dpd_ctx *c, float4 *pos, float4 *vt) {
-  return {c->bits, c->use_mask, c->grid_f64, c->quad, pos, vt, c->cell_of, c->rank_of, c->count2};
+  return {c->bits,    c->use_mask, c->grid_f64, c->quad,
+          pos,        vt,          c->cell_of,  c->rank_of,
+          c->count2 ? c->count2 : c->count};
 }
 
 // Forces at the current state in sorted order; init = 1 keeps velocities.
@@ -780,7 +783,7 @@ int force_pass(dpd_ctx *c, hipStream_t s, int init, const dpd::NextStep *next = 
                                        (int32_t)(c->NF + c->NW), (int32_t)c->NCELL, init,
                                        c->pos[a], c->vt, c->vel[a], c->frc[a], c->idx,
                                        c->idx_all, c->start_all, c->cq, c->pos[b], c->vel[b],
-                                       c->frc[b], c->dk, c->status, c->sph ? 1 : 0, clear);
+                                       c->frc[b], c->dk, c->status, c->sph ? 1 : 0, clear, next);
             }));
   if (c->nbricks > 0)
     HIP_TRY(c, timed(c, s, K_FORCE, [&] {
@@ -940,11 +943,10 @@ int one_step(dpd_ctx *c) {
   return DPD_OK;
 }
 
-// n >= 2 steps in a row of a small context (kRunTiles): the pair kernel with 16 lanes per
-// particle goes on to the next step's drift, so only the first step has a launch for
-// it.  The results are those of n steps one by one, and the launches are direct with
-// use_graph too: two a step keep the GPU busier than a replay a step (16.2 against 20.5
-// us at 2,400 particles, 21.8 against 26.2 at 16,500).
+// n >= 2 steps in a row: the pair kernel goes on to the next step's drift, so only the
+// first step has a launch for it.  The results are those of n steps one by one, and the
+// launches are direct with use_graph too: they keep the GPU busier than a replay a
+// step (16.2 against 20.5 us at 2,400 particles, 21.8 against 26.2 at 16,500).
 int step_run(dpd_ctx *c, int64_t n) {
   int rc = drift(c, c->stream);
   for (int64_t s = 0; s < n && !rc; ++s) {
@@ -955,7 +957,7 @@ int step_run(dpd_ctx *c, int64_t n) {
     rc = force_pass(c, c->stream, 0, last ? nullptr : &next);
     if (!last) {
       std::swap(c->vt, c->vt2);
-      std::swap(c->count, c->count2);
+      if (c->count2) std::swap(c->count, c->count2);
     }
     c->k += 1;
     c->steps += 1;
@@ -1438,13 +1440,13 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   c->box_codes = c->box_list == 16;
   if (!rc) rc = set_shapes(c, default_ppt(c), 256);
   // steps in a row (step_run), where the buffers can be had
-  if (!rc && c->wide && c->box_list && c->n_otiles <= kRunTiles) {
+  if (!rc && !c->moving && c->nbricks == 0 && (!c->wide || c->n_otiles <= kRunTiles)) {
     const size_t vt_bytes = 16 * (size_t)(c->NF + c->NW + 1), count_bytes = 4 * (size_t)c->NCELL;
     c->vt2 = (float4 *)dalloc(c, vt_bytes);
-    c->count2 = (int32_t *)dalloc(c, count_bytes);
-    if (c->vt2 && c->count2) {
+    if (c->box_list) c->count2 = (int32_t *)dalloc(c, count_bytes);
+    if (c->vt2 && (c->count2 || !c->box_list)) {
       chk(dpd::launch_fill_zero(c->stream, c->vt2, vt_bytes), "zero predictions");
-      chk(dpd::launch_fill_zero(c->stream, c->count2, count_bytes), "zero counts");
+      if (c->count2) chk(dpd::launch_fill_zero(c->stream, c->count2, count_bytes), "zero counts");
     } else {
       if (c->vt2) dfree(c, c->vt2);
       if (c->count2) dfree(c, c->count2);
@@ -1678,7 +1680,7 @@ int stored_window_step(dpd_ctx *c, int t, bool last) {
     if (rc || !row || last) return rc ? rc : force_pass(c, c->stream, 0);
     const dpd::NextStep drifted = next_step(c, stored_step(c, t + 1).D, stored_step(c, t + 1).V);
     rc = force_pass(c, c->stream, 0, &drifted);
-    std::swap(c->count, c->count2);
+    if (c->count2) std::swap(c->count, c->count2);
     return rc;
   };
   const int rc = launches();

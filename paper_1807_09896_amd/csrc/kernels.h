@@ -194,6 +194,16 @@ hipError_t launch_wall_move_bin(hipStream_t s, const KGeom &G, float hdt, float 
 // Wall positions replaced from gid-ordered float32 rows (device memory).
 hipError_t launch_import_walls(hipStream_t s, int64_t nw, float4 *walls, const float *pos);
 
+// What launch_integrate would do next (plain bounce-back off resting walls), done by the
+// pair force's launch; the drifted positions may take pos_out's place.
+struct NextStep {
+  const uint32_t *bits;
+  int use_mask, grid_f64;
+  const void *quad;
+  float4 *pos, *vt;
+  int32_t *cell_of, *rank_of, *count;
+};
+
 // Pair forces (Eq. 3-10) + body force + velocity update over tiles of up to
 // `block` (128 or 256) fluid slots, writing the state in cell-sorted slot
 // order.  pos4 and vt4 hold NF fluid entries, the walls and the pad entry
@@ -205,19 +215,11 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
                         const float4 *frc4, const int32_t *idx, const int32_t *idx_all,
                         const int32_t *start_all, const uint32_t *cq,
                         float4 *pos_out, float4 *vel_out, float4 *frc_out,
-                        const unsigned long long *dk, Status *st, int sph, int32_t *clear);
+                        const unsigned long long *dk, Status *st, int sph, int32_t *clear,
+                        const NextStep *next = nullptr);
 
 // The same pair forces with 16 lanes per particle, for small contexts, over
 // tiles of up to kWideParts fluid slots.  It reads no coarse codes.
-// With next the launch also does what launch_integrate would do next (plain bounce-back
-// off resting walls), into next; the drifted positions may take pos_out's place.
-struct NextStep {
-  const uint32_t *bits;
-  int use_mask, grid_f64;
-  const void *quad;
-  float4 *pos, *vt;
-  int32_t *cell_of, *rank_of, *count;
-};
 hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles, int ntiles,
                              int64_t NF, int init, const float4 *pos4, const float4 *vt4,
                              const float4 *vel4, const float4 *frc4, const int32_t *idx,

@@ -1,5 +1,5 @@
-"""Steps that follow one another in a call (two launches each in small contexts) against
-the same steps one call each, bit for bit."""
+"""Steps that follow one another in a call (the pair kernel goes on to the next drift)
+against the same steps one call each, bit for bit."""
 import numpy as np
 import pytest
 
@@ -20,9 +20,13 @@ def dpd():
     return dpd
 
 
+def _slab_of(L, dtype, seed):
+    return workloads.slab_system(L=L, seed_fluid=seed, seed_wall=seed + 1, grid_dtype=dtype,
+                                 params=P(seed=seed))
+
+
 def _slab(dtype, seed):
-    return workloads.slab_system(L=(9.0, 8.0, 9.0), seed_fluid=seed, seed_wall=seed + 1,
-                                 grid_dtype=dtype, params=P(seed=seed))
+    return _slab_of((9.0, 8.0, 9.0), dtype, seed)
 
 
 CASES = {
@@ -33,6 +37,15 @@ CASES = {
     # one block per box, whose launch clears the counts itself
     "one_block": lambda: [_edge_box((7, 8, 6), 900 + 37 * r) for r in range(3)],
     "uneven": lambda: [_edge_box((4, 4, 4), 1), _slab(np.float32, 35), _edge_box((6, 5, 4), 1300)],
+    # one lane per particle: the four launches of the cell list, its one launch (16 and 12
+    # blocks a box), a box of part-filled wavefronts, float64
+    "large": lambda: [_slab_of((36.0, 36.0, 24.0), np.float32, 41)],
+    "large64": lambda: [_slab_of((36.0, 36.0, 24.0), np.float64, 43)],
+    "large_sph": lambda: [_sph(workloads.sinusoid_slit_system(L=(36.0, 36.0, 24.0), base=3.0,
+                                                              amp=1.0))],
+    "batch16": lambda: [_slab_of((18.0, 26.0, 18.0 + 0.5 * r), np.float32, 45 + r)
+                        for r in range(4)],
+    "batch12": lambda: [_edge_box((12, 11, 10), 3400 + 13 * r) for r in range(20)],
     # not eligible: reflections with the normal's component only
     "specular": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=0.0, seed=36, specular=True)],
 }
