@@ -764,7 +764,8 @@ int scan_scatter_sort(dpd_ctx *c, hipStream_t s, const float4 *key4 = nullptr,
 dpd::NextStep next_step(dpd_ctx *c, float4 *pos, float4 *vt) {
   return {c->bits,    c->use_mask, c->grid_f64, c->quad,
           pos,        vt,          c->cell_of,  c->rank_of,
-          c->count2 ? c->count2 : c->count};
+          c->count2 ? c->count2 : c->count,
+          c->reflect ? 1 : 0, c->wcstart};
 }
 
 // Forces at the current state in sorted order; init = 1 keeps velocities.
@@ -816,12 +817,14 @@ int bin_walls(dpd_ctx *c, hipStream_t s, int move) {
   return DPD_OK;
 }
 
-// The binned walls in the order idx, into both position buffers and vt.
+// The binned walls in the order idx, into both position buffers and both predictions.
 int order_walls(dpd_ctx *c, hipStream_t s, const int32_t *idx) {
   const int a = c->cur, b = 1 - a;
   HIP_TRY(c, timed(c, s, K_OTHER, [&] {
             return dpd::launch_permute(s, c->NW, idx, c->wtmp, c->pos[a] + c->NF, c->wvtmp,
-                                       c->vt + c->NF, c->wtmp, c->pos[b] + c->NF);
+                                       c->vt + c->NF, c->wtmp, c->pos[b] + c->NF,
+                                       c->vt2 ? c->wvtmp : nullptr,
+                                       c->vt2 ? c->vt2 + c->NF : nullptr);
           }));
   return DPD_OK;
 }
@@ -951,7 +954,8 @@ int step_run(dpd_ctx *c, int64_t n) {
   int rc = drift(c, c->stream);
   for (int64_t s = 0; s < n && !rc; ++s) {
     const bool last = s + 1 == n;
-    rc = scan_scatter_sort(c, c->stream, nullptr, c->dk, true, true);
+    rc = c->moving ? list_both(c, c->stream)
+                   : scan_scatter_sort(c, c->stream, nullptr, c->dk, true, true);
     if (rc) break;
     const dpd::NextStep next = next_step(c, c->pos[1 - c->cur], c->vt2);
     rc = force_pass(c, c->stream, 0, last ? nullptr : &next);
@@ -1440,12 +1444,13 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   c->box_codes = c->box_list == 16;
   if (!rc) rc = set_shapes(c, default_ppt(c), 256);
   // steps in a row (step_run), where the buffers can be had
-  if (!rc && !c->moving && c->nbricks == 0 && (!c->wide || c->n_otiles <= kRunTiles)) {
+  if (!rc && c->nbricks == 0 && (!c->wide || (!c->moving && c->n_otiles <= kRunTiles))) {
     const size_t vt_bytes = 16 * (size_t)(c->NF + c->NW + 1), count_bytes = 4 * (size_t)c->NCELL;
     c->vt2 = (float4 *)dalloc(c, vt_bytes);
     if (c->box_list) c->count2 = (int32_t *)dalloc(c, count_bytes);
     if (c->vt2 && (c->count2 || !c->box_list)) {
-      chk(dpd::launch_fill_zero(c->stream, c->vt2, vt_bytes), "zero predictions");
+      chk(hipMemcpyAsync(c->vt2, c->vt, vt_bytes, hipMemcpyDeviceToDevice, c->stream),
+          "copy predictions");   // the walls' velocities
       if (c->count2) chk(dpd::launch_fill_zero(c->stream, c->count2, count_bytes), "zero counts");
     } else {
       if (c->vt2) dfree(c, c->vt2);
@@ -1972,7 +1977,7 @@ int dpd_replica_count(const dpd_ctx *c) { return c ? c->R : DPD_E_INVAL; }
 int dpd_step(dpd_ctx *c, int64_t nsteps) {
   if (!c) return DPD_E_INVAL;
   if (nsteps < 0) return fail(c, DPD_E_INVAL, "negative step count");
-  if (nsteps > 1 && c->vt2 && !c->reflect && !c->persistent && !c->timing)
+  if (nsteps > 1 && c->vt2 && !(c->wide && c->reflect) && !c->persistent && !c->timing)
     return step_run(c, nsteps);
   for (int64_t s = 0; s < nsteps; ++s) {
     int rc = one_step(c);

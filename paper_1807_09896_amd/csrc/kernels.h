@@ -105,10 +105,11 @@ hipError_t launch_set_pad(hipStream_t s, float4 *pos4, float4 *vt4, int32_t *sla
 hipError_t launch_cells(hipStream_t s, const KGeom &G, int64_t cell_off, int64_t n,
                         const float4 *pos4, int32_t *cell);
 
-// out[s] = in[idx[s]] for up to three float4 arrays (NULL skipped).
+// out[s] = in[idx[s]] for up to four float4 arrays (NULL skipped).
 hipError_t launch_permute(hipStream_t s, int64_t n, const int32_t *idx, const float4 *a_in,
                           float4 *a_out, const float4 *b_in, float4 *b_out, const float4 *c_in,
-                          float4 *c_out);
+                          float4 *c_out,
+                          const float4 *d_in = nullptr, float4 *d_out = nullptr);
 
 // Near-interface mask: one bit per grid cube, set when a corner is negative
 // (nwords = ceil(cubes / 32)).
@@ -194,14 +195,15 @@ hipError_t launch_wall_move_bin(hipStream_t s, const KGeom &G, float hdt, float 
 // Wall positions replaced from gid-ordered float32 rows (device memory).
 hipError_t launch_import_walls(hipStream_t s, int64_t nw, float4 *walls, const float *pos);
 
-// What launch_integrate would do next (plain bounce-back off resting walls), done by the
-// pair force's launch; the drifted positions may take pos_out's place.
+// What launch_integrate would do next, done by the pair force's launch; the drifted positions may take pos_out's place.
 struct NextStep {
   const uint32_t *bits;
   int use_mask, grid_f64;
   const void *quad;
   float4 *pos, *vt;
   int32_t *cell_of, *rank_of, *count;
+  int reflect;              // moving walls or specular reflection (launch_force alone)
+  const int32_t *wcstart;   // the walls' runs
 };
 
 // Pair forces (Eq. 3-10) + body force + velocity update over tiles of up to

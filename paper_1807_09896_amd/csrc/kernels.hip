@@ -745,13 +745,14 @@ __global__ void k_cells(const KGeom G, int64_t cell_off, int64_t n,
 
 __global__ void k_permute(int64_t n, const int32_t *__restrict__ idx, const float4 *a_in,
                           float4 *a_out, const float4 *b_in, float4 *b_out, const float4 *c_in,
-                          float4 *c_out) {
+                          float4 *c_out, const float4 *d_in, float4 *d_out) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const int i = idx[s];
   if (a_in) a_out[s] = a_in[i];
   if (b_in) b_out[s] = b_in[i];
   if (c_in) c_out[s] = c_in[i];
+  if (d_in) d_out[s] = d_in[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -971,10 +972,7 @@ __device__ __forceinline__ Moved integrate_one(const KGeom &G, const KParams &P,
                 dz = P.dt * (v.z + P.hdt * f.z);
     const float d2 = dx * dx + dy * dy + dz * dz;
     if (!(d2 <= P.max_disp2)) {
-      if (d2 != d2 || isinf(d2))
-        atomicAdd(&st->nonfinite, 1ull);
-      else
-        atomicAdd(&st->unstable, 1ull);
+      if (act) atomicAdd(d2 != d2 || isinf(d2) ? &st->nonfinite : &st->unstable, 1ull);
       // keep indices in range for the rest of the step
       if (!(xs >= 0.f && xs <= G.L[0])) xs = x.x;
       if (!(ys >= 0.f && ys <= G.L[1])) ys = x.y;
@@ -1307,7 +1305,8 @@ __device__ __forceinline__ Finished finish_particle(const KParams &P, const Acc 
 // (77 VGPRs).  A step of steps in a row, us: 16 cylinder cells 58.1 to 50.2, 64 uneven
 // boxes 106 to 93.4, 330,000 particles in a cylinder 76.1 to 71.4, porous SPH with
 // 1.17 million 227 to 214, the 168^3 porous box (6.3 million) 1,129 to 1,097.
-template <bool INIT, int BS, bool SPH, typename T>
+// REFLECT: integrate_one's moving walls and specular reflection.
+template <bool INIT, int BS, bool SPH, typename T, bool REFLECT>
 __device__ __forceinline__ void force_tile(
     int tid, uint32_t *list, const Box *__restrict__ boxes, const Tile *__restrict__ tiles,
     int64_t NF, int32_t pad, int32_t ncell_all, const float4 *__restrict__ pos4,
@@ -1319,7 +1318,8 @@ __device__ __forceinline__ void force_tile(
     const unsigned long long *__restrict__ dk, Status *st,
     const NextStep &next) {
   const Tile tile = tiles[tid];
-  if ((int)threadIdx.x >= tile.count) return;
+  if (((int)threadIdx.x & ~63) >= tile.count) return;
+  const bool act = (int)threadIdx.x < tile.count;   // the others follow the last particle
   const Box &B = boxes[tile.box];
   const KGeom G = B.G;
   const KParams P = B.P;
@@ -1329,7 +1329,7 @@ __device__ __forceinline__ void force_tile(
   const unsigned long long kk = *dk;
   const uint32_t klo = (uint32_t)kk;
   const uint32_t khi = ((uint32_t)(kk >> 32) & 0xFFFFu) | (P.replica << 16);
-  const int64_t s = (int64_t)tile.first + threadIdx.x;
+  const int64_t s = (int64_t)tile.first + min((int)threadIdx.x, tile.count - 1);
   const int i = idx[s];
   const float4 pi = pos4[i];
   const float4 vti = vt4[i];
@@ -1496,24 +1496,26 @@ __device__ __forceinline__ void force_tile(
     qa = sw ? qb : qa;
   }
   const Finished fin = finish_particle<INIT>(P, acc, i, vti, vel4, frc4);
-  if (!(isfinite(fin.frc.x) && isfinite(fin.frc.y) && isfinite(fin.frc.z)))
-    atomicAdd(&st->nonfinite, 1ull);
-  if (std::is_void_v<T> || next.pos != pos_out) store_stream(&pos_out[s], pi);
-  store_stream(&vel_out[s], fin.vel);
-  store_stream(&frc_out[s], fin.frc);
+  if (act) {
+    if (!(isfinite(fin.frc.x) && isfinite(fin.frc.y) && isfinite(fin.frc.z)))
+      atomicAdd(&st->nonfinite, 1ull);
+    if (std::is_void_v<T> || next.pos != pos_out) store_stream(&pos_out[s], pi);
+    store_stream(&vel_out[s], fin.vel);
+    store_stream(&frc_out[s], fin.frc);
+  }
   if constexpr (!std::is_void_v<T>) {
-    const Moved m = integrate_one<T, false>(
-        G, P, true, pi, fin.vel, fin.frc, next.bits + B.bo, next.use_mask,
-        (const typename PhiQuad<T>::type *)next.quad + B.go, st, co, NF, nullptr, nullptr, nullptr);
-    const int cell = co + m.cell;
-    // (the last wavefront of a box may be a part of one)
-    const int rank = __ballot(true) == ~0ull ? rank_in_cell(cell, next.count)
-                                             : atomicAdd(&next.count[cell], 1);
-    store_stream(&next.pos[s], m.pos);
-    store_stream(&next.vt[s], m.vt);
-    store_stream(&next.cell_of[s], cell);
-    store_stream(&next.rank_of[s], rank);
-    const int ev = __float_as_int(m.vt.w);
+    const Moved m = integrate_one<T, REFLECT>(
+        G, P, act, pi, fin.vel, fin.frc, next.bits + B.bo, next.use_mask,
+        (const typename PhiQuad<T>::type *)next.quad + B.go, st, co, NF, next.wcstart, pos4, vt4);
+    const int cell = act ? co + m.cell : -1;
+    const int rank = rank_in_cell(cell, next.count);
+    if (act) {
+      store_stream(&next.pos[s], m.pos);
+      store_stream(&next.vt[s], m.vt);
+      store_stream(&next.cell_of[s], cell);
+      store_stream(&next.rank_of[s], rank);
+    }
+    const int ev = act ? __float_as_int(m.vt.w) : 0;
     const int nbounce = (int)__popcll(__ballot(ev == 1)), nfall = (int)__popcll(__ballot(ev == 2));
     if (__lane_id() == 0) {
       StatusBlock::Line &at = ((StatusBlock *)st)->lines[tid & 63];
@@ -1534,7 +1536,7 @@ __device__ __forceinline__ void clear_counts(int32_t *__restrict__ clear, int n)
 
 // Six wavefronts per SIMD: at most 80 VGPRs, so the walk and the pair pass
 // run without register spills, and six blocks' lists fit in LDS.
-template <bool INIT, int BS, bool SPH, typename T>
+template <bool INIT, int BS, bool SPH, typename T, bool REFLECT>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_force(
     const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles, int64_t NF,
     int32_t pad, int32_t ncell_all, const float4 *__restrict__ pos4,
@@ -1549,7 +1551,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_
   clear_counts(clear, ncell_all);
   const int tid = xcd_block();
   if (tid >= ntiles) return;
-  force_tile<INIT, BS, SPH, T>(tid, list, boxes, tiles, NF, pad, ncell_all, pos4, vt4, vel4, frc4,
+  force_tile<INIT, BS, SPH, T, REFLECT>(tid, list, boxes, tiles, NF, pad, ncell_all, pos4, vt4, vel4, frc4,
                             idx, idx_all, start_all, cq, pos_out, vel_out, frc_out, dk, st, next);
 }
 
@@ -2063,7 +2065,7 @@ __device__ __attribute__((noinline)) void p_force(const PArgs *__restrict__ A0, 
   const ArgsPtr A = uniform_args(A0);
   const int tile = uniform_int(tile0);
   uint32_t *list = lds_ptr(list0);
-  force_tile<false, kBlock, SPH, void>(tile, list, A->boxes, A->ftiles, A->NF, A->pad,
+  force_tile<false, kBlock, SPH, void, false>(tile, list, A->boxes, A->ftiles, A->NF, A->pad,
                                        A->ncell_all, A->pos4, A->vt4, A->vel4, A->frc4, A->idx,
                                        A->idx_all, A->start_all, A->cq, A->pos_out, A->vel_out,
                                        A->frc_out, A->dk, A->st, NextStep{});
@@ -2300,9 +2302,10 @@ hipError_t launch_cells(hipStream_t s, const KGeom &G, int64_t cell_off, int64_t
 
 hipError_t launch_permute(hipStream_t s, int64_t n, const int32_t *idx, const float4 *a_in,
                           float4 *a_out, const float4 *b_in, float4 *b_out, const float4 *c_in,
-                          float4 *c_out) {
+                          float4 *c_out, const float4 *d_in, float4 *d_out) {
   if (n <= 0) return hipSuccess;
-  k_permute<<<grid_for(n), kBlock, 0, s>>>(n, idx, a_in, a_out, b_in, b_out, c_in, c_out);
+  k_permute<<<grid_for(n), kBlock, 0, s>>>(n, idx, a_in, a_out, b_in, b_out, c_in, c_out, d_in,
+                                           d_out);
   return hipGetLastError();
 }
 
@@ -2411,23 +2414,26 @@ hipError_t launch_force(hipStream_t s, int block, const Box *boxes, const Tile *
   const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
   const NextStep N = next ? *next : NextStep{};
   if (init && next) return hipErrorInvalidValue;
-#define DPD_FORCE(I, BS, S, T)                                                                   \
-  k_force<I, BS, S, T><<<nb, BS, 0, s>>>(boxes, tiles, ntiles, NF, pad, ncell_all, pos4, vt4,    \
-                                         vel4, frc4, idx, idx_all, start_all, cq, pos_out,       \
-                                         vel_out, frc_out, dk, st, clear, N)
-#define DPD_FORCE_S(I, BS, T) \
-  if (sph) DPD_FORCE(I, BS, true, T); else DPD_FORCE(I, BS, false, T)
-#define DPD_FORCE_B(I, T) \
-  if (block == 128) { DPD_FORCE_S(I, 128, T); } else { DPD_FORCE_S(I, 256, T); }
+#define DPD_FORCE(I, BS, S, T, R)                                                                \
+  k_force<I, BS, S, T, R><<<nb, BS, 0, s>>>(boxes, tiles, ntiles, NF, pad, ncell_all, pos4, vt4, \
+                                            vel4, frc4, idx, idx_all, start_all, cq, pos_out,    \
+                                            vel_out, frc_out, dk, st, clear, N)
+#define DPD_FORCE_S(I, BS, T, R) \
+  if (sph) DPD_FORCE(I, BS, true, T, R); else DPD_FORCE(I, BS, false, T, R)
+#define DPD_FORCE_B(I, T, R) \
+  if (block == 128) { DPD_FORCE_S(I, 128, T, R); } else { DPD_FORCE_S(I, 256, T, R); }
+#define DPD_FORCE_R(T) \
+  if (N.reflect) { DPD_FORCE_B(false, T, true); } else { DPD_FORCE_B(false, T, false); }
   if (init) {
-    DPD_FORCE_B(true, void);
+    DPD_FORCE_B(true, void, false);
   } else if (!next) {
-    DPD_FORCE_B(false, void);
+    DPD_FORCE_B(false, void, false);
   } else if (next->grid_f64) {
-    DPD_FORCE_B(false, double);
+    DPD_FORCE_R(double);
   } else {
-    DPD_FORCE_B(false, float);
+    DPD_FORCE_R(float);
   }
+#undef DPD_FORCE_R
 #undef DPD_FORCE_B
 #undef DPD_FORCE_S
 #undef DPD_FORCE
@@ -2442,7 +2448,7 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
                              Status *st, int sph, int32_t *clear, int32_t ncell_all,
                              const NextStep *next) {
   if (ntiles <= 0) return hipSuccess;
-  if (init && next) return hipErrorInvalidValue;
+  if (next && (init || next->reflect)) return hipErrorInvalidValue;
   const NextStep N = next ? *next : NextStep{};
   const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
 #define DPD_WIDE(I, S, T)                                                                         \

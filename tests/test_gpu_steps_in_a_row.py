@@ -46,7 +46,16 @@ CASES = {
     "batch16": lambda: [_slab_of((18.0, 26.0, 18.0 + 0.5 * r), np.float32, 45 + r)
                         for r in range(4)],
     "batch12": lambda: [_edge_box((12, 11, 10), 3400 + 13 * r) for r in range(20)],
-    # not eligible: reflections with the normal's component only
+    # moving walls (listed with the fluid on the way) alone and beside resting ones, and
+    # specular reflection
+    "large_moving": lambda: [workloads.couette_system(L=(41.0, 40.0, 17.5), U=4.0, seed=61)],
+    "mixed_moving": lambda: [workloads.couette_system(L=(41.0, 40.0, 12.0), U=4.0, seed=62),
+                             _slab_of((30.0, 29.0, 24.0), np.float32, 63)],
+    "large_specular": lambda: [workloads.couette_system(L=(41.0, 40.0, 17.5), U=0.0, seed=64,
+                                                        specular=True)],
+    "moving_specular": lambda: [workloads.couette_system(L=(41.0, 40.0, 17.5), U=4.0, seed=65,
+                                                         specular=True)],
+    # not eligible: small, with reflections of the normal's component only
     "specular": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=0.0, seed=36, specular=True)],
 }
 
