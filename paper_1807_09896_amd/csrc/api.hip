@@ -2005,7 +2005,8 @@ int dpd_use_persistent(dpd_ctx *c, int32_t enable) {
   if (c->moving) return fail(c, DPD_E_INVAL, "the persistent step does not move walls");
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->persistent = true;
-  int rc = c->ppt > 2 ? set_shapes(c, 2, c->fblock) : build_persistent(c);
+  // (one particle per thread, the default of small contexts, takes longer there)
+  int rc = c->ppt != 2 ? set_shapes(c, 2, c->fblock) : build_persistent(c);
   if (rc) {
     c->persistent = false;
     return rc;

@@ -1305,8 +1305,11 @@ __device__ __forceinline__ Finished finish_particle(const KParams &P, const Acc 
 // (77 VGPRs).  A step of steps in a row, us: 16 cylinder cells 58.1 to 50.2, 64 uneven
 // boxes 106 to 93.4, 330,000 particles in a cylinder 76.1 to 71.4, porous SPH with
 // 1.17 million 227 to 214, the 168^3 porous box (6.3 million) 1,129 to 1,097.
-// REFLECT: integrate_one's moving walls and specular reflection.
-template <bool INIT, int BS, bool SPH, typename T, bool REFLECT>
+// REFLECT: integrate_one's moving walls and specular reflection.  SPLIT: the pair pass
+// is compiled apart for interior wavefronts and for the end of the walk (1 % of a step); as a
+// callee, whose registers are fewer, the function spills then (a persistent step of 200
+// boxes with 1.56 million particles: 1,139 us against 1,054).
+template <bool INIT, int BS, bool SPH, typename T, bool REFLECT, bool SPLIT = true>
 __device__ __forceinline__ void force_tile(
     int tid, uint32_t *list, const Box *__restrict__ boxes, const Tile *__restrict__ tiles,
     int64_t NF, int32_t pad, int32_t ncell_all, const float4 *__restrict__ pos4,
@@ -1404,7 +1407,7 @@ __device__ __forceinline__ void force_tile(
   // the first `count` entries of every lane's list
   auto drain = [&](int count) {
     const uint32_t upto = lane0 + (uint32_t)(count * BS * 4);
-    if (edge)
+    if (!SPLIT || edge)
       pairs_of_list(std::true_type{}, upto);
     else
       pairs_of_list(std::false_type{}, upto);
@@ -1424,47 +1427,51 @@ __device__ __forceinline__ void force_tile(
   for (;;) {
     if (!wave_any(t < t_end)) {
       if (++row == 9) {
-        drain(kListCap);
-        break;
+        if constexpr (SPLIT) {
+          drain(kListCap);
+          break;
+        }
+      } else {
+        const int oz = row / 3 - 1, oy = row % 3 - 1;
+        int qz = cz + oz, qy = cy + oy;
+        float sz = 0.f, sy = 0.f;
+        if (qz < 0) { qz += nz; sz = -G.L[2]; }
+        else if (qz >= nz) { qz -= nz; sz = G.L[2]; }
+        if (qy < 0) { qy += ny; sy = -G.L[1]; }
+        else if (qy >= ny) { qy -= ny; sy = G.L[1]; }
+        const uint32_t cyz_code = (qshift(pi.y, sy) << 11) | (qshift(pi.z, sz) << 22);
+        // the row's x-neighbours [cx-1, cx+1] as run A, plus run B where the
+        // row wraps (cell nx-1 seen across the left edge, then cells 0 and 1;
+        // or cells nx-2 and nx-1, then cell 0 seen across the right edge)
+        const int base = co + (qz * ny + qy) * nx;
+        const bool left = cx == 0, right = cx == nx - 1;
+        const int a0 = left ? base + nx - 1 : (right ? base + nx - 2 : base + cx - 1);
+        int v[4];
+        starts.load(a0, v);
+        t = v[0];
+        t_end = left ? v[1] : (right ? v[2] : v[3]);
+        tb = 0;
+        tb_end = 0;
+        if (wave_any(left || right)) {
+          int w[4];
+          starts.load(base, w);
+          tb = (left || right) ? w[0] : 0;
+          tb_end = left ? w[2] : (right ? w[1] : 0);
+        }
+        qa = qshift(pi.x, left ? -G.L[0] : 0.f) | cyz_code;
+        qb = qshift(pi.x, right ? G.L[0] : 0.f) | cyz_code;
+        const bool sw = t >= t_end;
+        t = sw ? tb : t;
+        t_end = sw ? tb_end : t_end;
+        tb = sw ? tb_end : tb;
+        qa = sw ? qb : qa;
+        continue;
       }
-      const int oz = row / 3 - 1, oy = row % 3 - 1;
-      int qz = cz + oz, qy = cy + oy;
-      float sz = 0.f, sy = 0.f;
-      if (qz < 0) { qz += nz; sz = -G.L[2]; }
-      else if (qz >= nz) { qz -= nz; sz = G.L[2]; }
-      if (qy < 0) { qy += ny; sy = -G.L[1]; }
-      else if (qy >= ny) { qy -= ny; sy = G.L[1]; }
-      const uint32_t cyz_code = (qshift(pi.y, sy) << 11) | (qshift(pi.z, sz) << 22);
-      // the row's x-neighbours [cx-1, cx+1] as run A, plus run B where the
-      // row wraps (cell nx-1 seen across the left edge, then cells 0 and 1;
-      // or cells nx-2 and nx-1, then cell 0 seen across the right edge)
-      const int base = co + (qz * ny + qy) * nx;
-      const bool left = cx == 0, right = cx == nx - 1;
-      const int a0 = left ? base + nx - 1 : (right ? base + nx - 2 : base + cx - 1);
-      int v[4];
-      starts.load(a0, v);
-      t = v[0];
-      t_end = left ? v[1] : (right ? v[2] : v[3]);
-      tb = 0;
-      tb_end = 0;
-      if (wave_any(left || right)) {
-        int w[4];
-        starts.load(base, w);
-        tb = (left || right) ? w[0] : 0;
-        tb_end = left ? w[2] : (right ? w[1] : 0);
-      }
-      qa = qshift(pi.x, left ? -G.L[0] : 0.f) | cyz_code;
-      qb = qshift(pi.x, right ? G.L[0] : 0.f) | cyz_code;
-      const bool sw = t >= t_end;
-      t = sw ? tb : t;
-      t_end = sw ? tb_end : t_end;
-      tb = sw ? tb_end : tb;
-      qa = sw ? qb : qa;
-      continue;
     }
-    if (wave_any(tail > full)) {
-      // kDrain pairs of every lane, the others' entries moved to the list's front
-      drain(kDrain);
+    if ((!SPLIT && row == 9) || wave_any(tail > full)) {
+      drain(!SPLIT && row == 9 ? kListCap : kDrain);
+      if (!SPLIT && row == 9) break;
+      // the entries that are left, to the list's front
       int *const column = (int *)(lds + lane0);
 #pragma unroll
       for (int e = 0; e + kDrain < kListCap; ++e) column[e * BS] = column[(e + kDrain) * BS];
@@ -2065,7 +2072,7 @@ __device__ __attribute__((noinline)) void p_force(const PArgs *__restrict__ A0, 
   const ArgsPtr A = uniform_args(A0);
   const int tile = uniform_int(tile0);
   uint32_t *list = lds_ptr(list0);
-  force_tile<false, kBlock, SPH, void, false>(tile, list, A->boxes, A->ftiles, A->NF, A->pad,
+  force_tile<false, kBlock, SPH, void, false, false>(tile, list, A->boxes, A->ftiles, A->NF, A->pad,
                                        A->ncell_all, A->pos4, A->vt4, A->vel4, A->frc4, A->idx,
                                        A->idx_all, A->start_all, A->cq, A->pos_out, A->vel_out,
                                        A->frc_out, A->dk, A->st, NextStep{});
