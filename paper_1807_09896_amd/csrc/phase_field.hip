@@ -75,19 +75,19 @@ __device__ __forceinline__ void lengths(float s2, float delta2, float, float &le
   inv = __builtin_amdgcn_rsqf(fmaxf(s2, delta2));
 }
 
-// double: both from one reciprocal square root y of s2 (kept off zero, where
-// |u| is s2 y = 0), by the hardware's estimate and two Newton steps (y += y (1 -
-// v y^2) / 2, each squaring the relative error, the last residual fused).  With the
-// correctly rounded sqrt and division in their place a step of a 187 x 130 x 201
-// grid took 100 us instead of 71 (64 planes per block); the error of phi against
-// plain 64-bit torch is 2.2e-17 (relative 2-norm, 20 steps) either way.
+// double: both from one reciprocal square root y of s2 (kept off zero, where |u| is
+// s2 y = 0): the hardware's estimate and a Newton step, then |u| = s2 y and 1 / |u| = y
+// corrected by their fused residuals, which leaves each within a rounding of the
+// exact value, as the correctly rounded sqrt and division do.  With those in their place a
+// step of a 187 x 130 x 201 grid took 100 us instead of 71 (64 planes per block).
 __device__ __forceinline__ void lengths(double s2, double delta2, double inv_delta, double &len,
                                         double &inv) {
   const double v = fmax(s2, 1e-200);
   double y = __builtin_amdgcn_rsq(v);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) y = __builtin_fma(0.5 * y, __builtin_fma(-(v * y), y, 1.0), y);
+  y = __builtin_fma(0.5 * y, __builtin_fma(-(v * y), y, 1.0), y);
   len = s2 * y;
+  len = __builtin_fma(__builtin_fma(-len, len, s2), 0.5 * y, len);
+  y = __builtin_fma(__builtin_fma(-len, y, 1.0), y, y);
   inv = s2 > delta2 ? y : inv_delta;
 }
 
