@@ -1444,7 +1444,7 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   c->box_codes = c->box_list == 16;
   if (!rc) rc = set_shapes(c, default_ppt(c), 256);
   // steps in a row (step_run), where the buffers can be had
-  if (!rc && c->nbricks == 0 && (!c->wide || (!c->moving && c->n_otiles <= kRunTiles))) {
+  if (!rc && c->nbricks == 0 && (!c->wide || c->n_otiles <= kRunTiles)) {
     const size_t vt_bytes = 16 * (size_t)(c->NF + c->NW + 1), count_bytes = 4 * (size_t)c->NCELL;
     c->vt2 = (float4 *)dalloc(c, vt_bytes);
     if (c->box_list) c->count2 = (int32_t *)dalloc(c, count_bytes);
@@ -1977,7 +1977,7 @@ int dpd_replica_count(const dpd_ctx *c) { return c ? c->R : DPD_E_INVAL; }
 int dpd_step(dpd_ctx *c, int64_t nsteps) {
   if (!c) return DPD_E_INVAL;
   if (nsteps < 0) return fail(c, DPD_E_INVAL, "negative step count");
-  if (nsteps > 1 && c->vt2 && !(c->wide && c->reflect) && !c->persistent && !c->timing)
+  if (nsteps > 1 && c->vt2 && !c->persistent && !c->timing)
     return step_run(c, nsteps);
   for (int64_t s = 0; s < nsteps; ++s) {
     int rc = one_step(c);

@@ -202,7 +202,7 @@ struct NextStep {
   const void *quad;
   float4 *pos, *vt;
   int32_t *cell_of, *rank_of, *count;
-  int reflect;              // moving walls or specular reflection (launch_force alone)
+  int reflect;              // moving walls or specular reflection
   const int32_t *wcstart;   // the walls' runs
 };
 

@@ -1581,7 +1581,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_
 // 24.1 to 21.9 at 16,500.  Five wavefronts per SIMD (96 VGPRs): with four the blocks of
 // 16,500 particles took a second round, 24.4 us.
 // ---------------------------------------------------------------------------
-template <bool INIT, bool SPH, typename T>
+template <bool INIT, bool SPH, typename T, bool REFLECT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_force_wide(
     const Box *__restrict__ boxes, const Tile *__restrict__ tiles, int ntiles, int64_t NF,
     const float4 *__restrict__ pos4, const float4 *__restrict__ vt4,
@@ -1676,22 +1676,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     vel_out[s] = fin.vel;
     frc_out[s] = fin.frc;
     if (std::is_void_v<T> || next.pos != pos_out) pos_out[s] = pi;
-    if constexpr (!std::is_void_v<T>) {
+  }
+  if constexpr (!std::is_void_v<T>) {
+    // one lane's work; with REFLECT by all lanes, which search a reflection's wall
+    // together (groups leave from the last on, and there are no more reflections than
+    // groups)
+    if (REFLECT || g == 0) {
       const int co = (int)B.co;
-      const Moved m = integrate_one<T, false>(
-          G, P, true, pi, fin.vel, fin.frc, next.bits + B.bo, next.use_mask,
-          (const typename PhiQuad<T>::type *)next.quad + B.go, st, co, NF, nullptr, nullptr,
-          nullptr);
-      const int cell = co + m.cell;
-      const int rank = atomicAdd(&next.count[cell], 1);
-      next.pos[s] = m.pos;
-      next.vt[s] = m.vt;
-      next.cell_of[s] = cell;
-      next.rank_of[s] = rank;
-      const int ev = __float_as_int(m.vt.w);
-      StatusBlock::Line &at = ((StatusBlock *)st)->lines[tid & 63];
-      if (ev == 1) atomicAdd(&at.bounce, 1ull);
-      if (ev == 2) atomicAdd(&at.fallback, 1ull);
+      const Moved m = integrate_one<T, REFLECT>(
+          G, P, g == 0, pi, fin.vel, fin.frc, next.bits + B.bo, next.use_mask,
+          (const typename PhiQuad<T>::type *)next.quad + B.go, st, co, NF, next.wcstart, pos4,
+          vt4);
+      if (g == 0) {
+        const int cell = co + m.cell;
+        const int rank = atomicAdd(&next.count[cell], 1);
+        next.pos[s] = m.pos;
+        next.vt[s] = m.vt;
+        next.cell_of[s] = cell;
+        next.rank_of[s] = rank;
+        const int ev = __float_as_int(m.vt.w);
+        StatusBlock::Line &at = ((StatusBlock *)st)->lines[tid & 63];
+        if (ev == 1) atomicAdd(&at.bounce, 1ull);
+        if (ev == 2) atomicAdd(&at.fallback, 1ull);
+      }
     }
   }
 }
@@ -2455,24 +2462,27 @@ hipError_t launch_force_wide(hipStream_t s, const Box *boxes, const Tile *tiles,
                              Status *st, int sph, int32_t *clear, int32_t ncell_all,
                              const NextStep *next) {
   if (ntiles <= 0) return hipSuccess;
-  if (next && (init || next->reflect)) return hipErrorInvalidValue;
+  if (next && init) return hipErrorInvalidValue;
   const NextStep N = next ? *next : NextStep{};
   const unsigned nb = (unsigned)(((ntiles + 7) / 8) * 8);
-#define DPD_WIDE(I, S, T)                                                                         \
-  k_force_wide<I, S, T><<<nb, kBlock, 0, s>>>(boxes, tiles, ntiles, NF, pos4, vt4, vel4, frc4, idx, \
-                                              idx_all, start_all, pos_out, vel_out, frc_out, dk,  \
-                                              st, clear, ncell_all, N)
-#define DPD_WIDE_S(I, T) \
-  if (sph) DPD_WIDE(I, true, T); else DPD_WIDE(I, false, T)
+#define DPD_WIDE(I, S, T, R)                                                                      \
+  k_force_wide<I, S, T, R><<<nb, kBlock, 0, s>>>(boxes, tiles, ntiles, NF, pos4, vt4, vel4, frc4, \
+                                                 idx, idx_all, start_all, pos_out, vel_out,       \
+                                                 frc_out, dk, st, clear, ncell_all, N)
+#define DPD_WIDE_S(I, T, R) \
+  if (sph) DPD_WIDE(I, true, T, R); else DPD_WIDE(I, false, T, R)
+#define DPD_WIDE_R(T) \
+  if (N.reflect) { DPD_WIDE_S(false, T, true); } else { DPD_WIDE_S(false, T, false); }
   if (init) {
-    DPD_WIDE_S(true, void);
+    DPD_WIDE_S(true, void, false);
   } else if (!next) {
-    DPD_WIDE_S(false, void);
+    DPD_WIDE_S(false, void, false);
   } else if (next->grid_f64) {
-    DPD_WIDE_S(false, double);
+    DPD_WIDE_R(double);
   } else {
-    DPD_WIDE_S(false, float);
+    DPD_WIDE_R(float);
   }
+#undef DPD_WIDE_R
 #undef DPD_WIDE_S
 #undef DPD_WIDE
   return hipGetLastError();

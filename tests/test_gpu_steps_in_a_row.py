@@ -6,6 +6,7 @@ import pytest
 import workloads
 from gpu_helpers import require_gpu
 from test_gpu_small_contexts import _edge_box, _sph
+from test_gpu_walls import _aimed_couette
 
 pytestmark = pytest.mark.gpu
 
@@ -55,7 +56,12 @@ CASES = {
                                                         specular=True)],
     "moving_specular": lambda: [workloads.couette_system(L=(41.0, 40.0, 17.5), U=4.0, seed=65,
                                                          specular=True)],
-    # not eligible: small, with reflections of the normal's component only
+    # the same in small contexts: a part-filled last wavefront, many reflections
+    "moving": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=4.0, seed=66)],
+    "moving_aimed": lambda: [_aimed_couette(False, seed=67, speed=45.0, band=0.5)],
+    "moving_batch": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0 + 0.5 * r), U=4.0,
+                                                      seed=68 + r, specular=r == 1)
+                             for r in range(3)] + [_slab(np.float32, 72)],
     "specular": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=0.0, seed=36, specular=True)],
 }
 
