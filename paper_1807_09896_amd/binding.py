@@ -197,10 +197,16 @@ class TorchAllocator:
         self.struct = dpd_allocator(self._alloc, self._free, None)
 
     def _do_alloc(self, nbytes, stream, user):
-        t = self._torch.empty(int(nbytes), dtype=self._torch.uint8, device=self.device)
-        p = t.data_ptr()
-        self.live[p] = t
-        return p
+        # An exception must not leave the callback: C would read whatever the result slot
+        # held before.  NULL is the library's "no memory", reported as DPD_E_NOMEM or done
+        # without.
+        try:
+            t = self._torch.empty(int(nbytes), dtype=self._torch.uint8, device=self.device)
+            p = t.data_ptr()
+            self.live[p] = t
+            return p
+        except BaseException:
+            return None
 
     def _do_free(self, ptr, stream, user):
         self.live.pop(int(ptr or 0), None)

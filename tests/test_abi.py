@@ -96,3 +96,29 @@ def test_null_handles_are_rejected(lib):
     assert lib.dpd_step(None, 1) != 0
     assert lib.dpd_sync(None) != 0
     lib.dpd_destroy(None)
+
+
+@pytest.mark.parametrize("error", [RuntimeError("out of memory"), KeyboardInterrupt()])
+def test_allocator_callback_returns_null_on_failure(monkeypatch, error):
+    """torch raises where the allocator's contract is to return NULL; nothing may leave the
+    callback, or C takes what its result slot held before for the memory."""
+    import sys
+    import types
+    import torch
+    from paper_1807_09896_amd import binding
+    alloc = binding.TorchAllocator(torch.device("cpu"))
+    # the callback as C has it
+    entry = binding.ALLOC_FN(C.cast(alloc.struct.alloc, C.c_void_p).value)
+    free = binding.FREE_FN(C.cast(alloc.struct.free, C.c_void_p).value)
+    p = entry(4096, None, None)
+    assert p and list(alloc.live) == [p]
+    left = []
+    monkeypatch.setattr(sys, "unraisablehook", lambda u: left.append(u.exc_value))
+
+    def empty(*a, **k):
+        raise error
+    monkeypatch.setattr(alloc, "_torch", types.SimpleNamespace(empty=empty, uint8=torch.uint8))
+    assert entry(1 << 20, None, None) is None
+    assert not left and list(alloc.live) == [p]
+    free(p, None, None)
+    assert not alloc.live

@@ -25,7 +25,9 @@ def dpd():
 
 
 def _window(dpd, s, steps, ckpt, monkeypatch, refuse):
-    """refuse: allocations of at least so many bytes fail once the simulation exists."""
+    """refuse: allocations of at least so many bytes fail once the simulation exists, as
+    torch's fail: with an exception."""
+    import types
     import torch
     from paper_1807_09896_amd import binding
     from paper_1807_09896_amd.adjoint import Window
@@ -36,13 +38,14 @@ def _window(dpd, s, steps, ckpt, monkeypatch, refuse):
 
         def __init__(self, device):
             super().__init__(device)
+            self._torch = types.SimpleNamespace(empty=self._empty, uint8=torch.uint8)
             made.append(self)
 
-        def _do_alloc(self, nbytes, stream, user):
+        def _empty(self, nbytes, **kw):
             if self.limit is not None and nbytes >= self.limit:
                 self.refused += 1
-                return None
-            return super()._do_alloc(nbytes, stream, user)
+                raise torch.cuda.OutOfMemoryError("refused")
+            return torch.empty(nbytes, **kw)
 
     monkeypatch.setattr(binding, "TorchAllocator", Allocator)
     sim = dpd.Simulation(s, graph=True)
