@@ -470,14 +470,25 @@ constexpr int kRunTiles = 1280;
 
 // Blocks per box of the one-launch cell list (k_cells_box); 0 where some box does
 // not fit its LDS, where the brick kernel needs the separate launches' arrays, and
-// where walls move (list_both lists them with the fluid in four launches).
+// where walls move (list_both lists them with the fluid).
 // 256 CUs hold one such block each, so the boxes share 256, up to 16 a box (a box of
 // at most 1,024 particles is one round of one block's threads).  Whole step, us,
 // four launches / 1 / 4 / 16 blocks per box: 29.0 / 24.4 / 22.9 / 22.9 at 2,000
 // particles, 36.1 / 31.1 / 26.9 / 24.9 at 8,400, 38.3 / 39.9 / 31.1 / 27.9 at 16,000,
 // 41.3 / 48.1 / 35.9 / 32.2 at 22,000; 64 boxes: 127 / 126 / 115 / 131.
+// More boxes than CUs take turns, each block's chain of phases after another's.  From
+// the third turn on that costs more than the launches save, unless the boxes are large
+// enough for the blocks to work through them about as fast as the launches do (step of
+// steps in a row, us, four launches / one: 300 particles a box 57.7 / 54.1 at 512
+// boxes, 63.5 / 63.9 at 576, 88 / 93 at 1,024, 150 / 174 at 2,048; 1,000 a box 107 /
+// 103 at 512, 116 / 118 at 576, 179 / 184 at 1,024, 325 / 345 at 2,048; 1,500 a box
+// 176 / 174 at 768, 223 / 225 at 1,024, 423 / 431 at 2,048; 2,200 a box 247 / 244 at
+// 768, 318 / 317 at 1,024, 617 / 622 at 2,048; 8,200 a box 1,124 / 1,100 at 1,024,
+// 2,240 / 2,200 at 2,048).
+constexpr int kBoxTurns = 2 * 256, kBoxLarge = 1536;
 int box_parts(const dpd_ctx *c) {
   if (c->nbricks > 0 || c->moving) return 0;
+  if (c->R > kBoxTurns && c->NF < (int64_t)kBoxLarge * c->R) return 0;
   int64_t most = 0;
   for (const Replica &p : c->rep) {
     if (p.ncell > dpd::kBoxCells || p.nf > dpd::kBoxFluid) return 0;

@@ -101,13 +101,21 @@ def test_small_context_bits(dpd, filler, name):
     beside.close()
 
 
-@pytest.mark.parametrize("count", [3, 70, 130])
-def test_blocks_per_box(dpd, count):
-    """Batches whose boxes are shared by 16, 3 and one block each."""
+@pytest.mark.parametrize("count,fluid", [(3, 1100), (70, 1100), (130, 1100), (512, 200),
+                                         (513, 200), (513, 1536)])
+def test_blocks_per_box(dpd, count, fluid):
+    """Batches whose boxes are shared by 16, 3 and one block each; above 512 boxes only
+    large ones take the one launch."""
     import torch
-    boxes = [_edge_box((7, 8, 6), 1100 + 3 * r) for r in range(count)]
+    cells = (7, 8, 6) if fluid < 1500 else (8, 8, 8)
+    boxes = [_edge_box(cells, fluid + 3 * (r % 140)) for r in range(count)]
+    print("blocks per box", count, fluid, flush=True)
     batch = dpd.Simulation(boxes)
-    batch.step(4)
+    batch.kernel_times(1)
+    batch.step(1)
+    scans = batch.kernel_times(0)["scan_down"][1]
+    assert scans == (1 if count > 512 and fluid < 1500 else 0)
+    batch.step(3)
     for r in (0, count // 2, count - 1):
         alone = dpd.Simulation(boxes[r])
         alone.step(4)
