@@ -21,7 +21,10 @@
  * valid once the stream has reached that point (dpd_sync() or any stream
  * synchronisation).  Device memory of a context comes from the caller's
  * allocator when one is given (e.g. PyTorch's caching allocator), from
- * hipMalloc otherwise, and is released by dpd_destroy().
+ * hipMalloc otherwise, and is released by dpd_destroy().  An allocator returns
+ * NULL where it has no memory, or declines: DPD_E_NOMEM, or the call does
+ * without where it can (what only saves time: 16 bytes a particle and 4 a cell
+ * for steps in a row, a window kept whole).
  */
 #ifndef DPD_H
 #define DPD_H
@@ -339,11 +342,13 @@ int dpd_set_phi(dpd_ctx *ctx, int32_t r, const void *data, int32_t on_device);
  * number of such terms and the bin the FP32 decision
  * clamp(floor(fl(x_axis * fl32(nbins / L_axis))), 0, nbins - 1).
  * profile (device, nbins float64) and counts (device, nbins int64: N_b) may
- * be NULL.  A window whose steps' states and cell lists fit 2 GiB of device
- * memory (and can be allocated) is kept whole; otherwise a checkpoint of the
- * fluid state is stored every ckpt steps
- * (1 <= ckpt <= steps, nbins <= 1024); the context ends at the window's last
- * state.  DPD_E_STATE for a batch context; DPD_E_INVAL for moving walls,
+ * be NULL.  A window whose steps' states and cell lists (about 100 bytes a
+ * particle and step) fit 2 GiB of device memory is kept whole in one block,
+ * which the context holds until a window does not use it or its memory is
+ * needed; otherwise, and where the allocator returns NULL for that block, a
+ * checkpoint of the fluid state is stored every ckpt steps (1 <= ckpt <=
+ * steps, nbins <= 1024).  The context ends at the window's last state.
+ * DPD_E_STATE for a batch context; DPD_E_INVAL for moving walls,
  * DPD_FLAG_SPECULAR or DPD_FLAG_SPH (the adjoint covers the a_ij w force and
  * resting walls with bounce-back).
  *

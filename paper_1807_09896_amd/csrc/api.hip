@@ -161,6 +161,7 @@ struct dpd_ctx {
   // count (null: not used)
   float4 *vt2 = nullptr;
   int32_t *count2 = nullptr;
+  bool captured = false;   // a caller's own graph may hold them
 
   // persistent step (dpd_use_persistent): work items, per-(box, phase) item
   // counts and arrivals, the queue counter, per-box scan chunk sums, 256-particle
@@ -199,16 +200,22 @@ int hip_fail(dpd_ctx *c, hipError_t e, const char *where) {
     if (e_ != hipSuccess) return hip_fail((ctx), e_, #expr);    \
   } while (0)
 
-void *dalloc(dpd_ctx *c, size_t bytes) {
+bool give_back(dpd_ctx *c);
+
+// spare: memory that the caller can do without.  For any other, what the context holds
+// of such memory makes room where there is none.
+void *dalloc(dpd_ctx *c, size_t bytes, bool spare = false) {
   bytes = (bytes + 255) & ~(size_t)255;
   if (bytes == 0) bytes = 256;
   void *p = nullptr;
-  if (c->has_al) {
-    p = c->al.alloc(bytes, (void *)c->stream, c->al.user);
-  } else if (hipMalloc(&p, bytes) != hipSuccess) {
-    p = nullptr;
-    (void)hipGetLastError();   // reported by the caller, or done without
-  }
+  do {
+    if (c->has_al) {
+      p = c->al.alloc(bytes, (void *)c->stream, c->al.user);
+    } else if (hipMalloc(&p, bytes) != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();   // reported by the caller, or done without
+    }
+  } while (!p && !spare && give_back(c));
   if (p) c->owned.push_back(p);
   return p;
 }
@@ -231,6 +238,38 @@ void drop_graphs(dpd_ctx *c) {
       (void)hipGraphExecDestroy(c->graph[g]);
       c->graph[g] = nullptr;
     }
+}
+
+hipError_t write_persistent_args(dpd_ctx *c);
+
+void free_store(Window &W, dpd_ctx *c) {
+  if (W.store) dfree(c, W.store);
+  W.store = nullptr;
+  W.store_cap = 0;
+}
+
+// Memory that only saves time, back to the allocator: the store of a window that can
+// no longer be swept, and the second prediction and counts of steps in a row (both
+// counts are clear between calls, and the walls' part of both predictions is the same).
+// False where the context holds none.
+bool give_back(dpd_ctx *c) {
+  Window &W = c->win;
+  const bool store = W.store && !(W.valid && W.gen == c->gen), row = c->vt2 && !c->captured;
+  if (!store && !row) return false;
+  (void)hipStreamSynchronize(c->stream);
+  if (store) {
+    free_store(W, c);
+    W.full = false;
+  }
+  if (row) {
+    drop_graphs(c);   // a captured step holds one of each pair
+    dfree(c, c->vt2);
+    if (c->count2) dfree(c, c->count2);
+    c->vt2 = nullptr;
+    c->count2 = nullptr;
+    if (c->persistent) (void)write_persistent_args(c);
+  }
+  return true;
 }
 
 void release_all(dpd_ctx *c) {
@@ -594,6 +633,7 @@ int build_persistent(dpd_ctx *c) {
   for (void *q : {(void *)c->pitems, (void *)c->pneed, (void *)c->parrive, (void *)c->phead,
                   (void *)c->pbsum, (void *)c->pargs[0], (void *)c->pargs[1]})
     if (q) dfree(c, q);
+  c->pargs[0] = c->pargs[1] = nullptr;
   c->pitems = (PItem *)dalloc(c, sizeof(PItem) * std::max<size_t>(items.size(), 1));
   c->pneed = (int32_t *)dalloc(c, 4 * need.size());
   c->parrive = (int32_t *)dalloc(c, 4 * need.size());
@@ -609,7 +649,13 @@ int build_persistent(dpd_ctx *c) {
     HIP_TRY(c, hipMemcpy(c->pitems, items.data(), sizeof(PItem) * items.size(),
                          hipMemcpyHostToDevice));
   HIP_TRY(c, hipMemcpy(c->pneed, need.data(), 4 * need.size(), hipMemcpyHostToDevice));
-  for (int a = 0; a < 2; ++a) {
+  HIP_TRY(c, write_persistent_args(c));
+  return DPD_OK;
+}
+
+// The persistent step's arguments for either buffer set, with the context's buffers of now.
+hipError_t write_persistent_args(dpd_ctx *c) {
+  for (int a = 0; a < 2 && c->pargs[1]; ++a) {
     const int b = 1 - a;
     dpd::PArgs A{};
     A.boxes = c->boxes;
@@ -649,9 +695,10 @@ int build_persistent(dpd_ctx *c) {
     A.vel_out = c->vel[b];
     A.frc_out = c->frc[b];
     A.dk = c->dk;
-    HIP_TRY(c, hipMemcpy(c->pargs[a], &A, sizeof(A), hipMemcpyHostToDevice));
+    const hipError_t e = hipMemcpy(c->pargs[a], &A, sizeof(A), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return e;
   }
-  return DPD_OK;
+  return hipSuccess;
 }
 
 // Cuts of one axis of n cells into bricks of at most B cells.  The brick at
@@ -1457,17 +1504,15 @@ int create_impl(int32_t nbox, const dpd_box *boxes, const dpd_particles *parts,
   // steps in a row (step_run), where the buffers can be had
   if (!rc && c->nbricks == 0 && (!c->wide || c->n_otiles <= kRunTiles)) {
     const size_t vt_bytes = 16 * (size_t)(c->NF + c->NW + 1), count_bytes = 4 * (size_t)c->NCELL;
-    c->vt2 = (float4 *)dalloc(c, vt_bytes);
-    if (c->box_list) c->count2 = (int32_t *)dalloc(c, count_bytes);
+    c->vt2 = (float4 *)dalloc(c, vt_bytes, true);
+    if (c->vt2 && c->box_list) c->count2 = (int32_t *)dalloc(c, count_bytes, true);
     if (c->vt2 && (c->count2 || !c->box_list)) {
       chk(hipMemcpyAsync(c->vt2, c->vt, vt_bytes, hipMemcpyDeviceToDevice, c->stream),
           "copy predictions");   // the walls' velocities
       if (c->count2) chk(dpd::launch_fill_zero(c->stream, c->count2, count_bytes), "zero counts");
     } else {
       if (c->vt2) dfree(c, c->vt2);
-      if (c->count2) dfree(c, c->count2);
       c->vt2 = nullptr;
-      c->count2 = nullptr;
     }
   }
   if (rc) return bail(rc);
@@ -1596,17 +1641,27 @@ StoredStep stored_step(const dpd_ctx *c, int t) {
           (int32_t *)(p + l.idx), (int32_t *)(p + l.idx_all), (int32_t *)(p + l.start_all)};
 }
 
-// Windows of up to this many bytes are kept whole.  A step of the 20^3 slit
-// (19,700 particles) takes 1.9 MB; keeping its 24-step window, the sweep
-// launches three kernels per step instead of recomputing the segment and then
-// each step's drift and cell list.  Larger windows keep a state every ckpt
-// steps, as do those whose store cannot be allocated.
+// Windows of up to this many bytes are kept whole, whatever their ckpt.  A step of the
+// 20^3 slit (19,700 particles) takes 1.9 MB; keeping its 24-step window, the sweep
+// launches two kernels per step, and one before the first, instead of recomputing the
+// segment and then each step's drift and cell list.  Larger windows keep a state every
+// ckpt steps, as do those whose store cannot be allocated.  The store stays for the
+// windows to come, until one does not use it (window_alloc) or its memory is
+// needed (give_back).
 constexpr size_t kWindowStore = (size_t)2 << 30;
 
 // The state a segment starts from.
 const float4 *segment_start(const dpd_ctx *c, int seg) {
   const Window &W = c->win;
   return W.full ? stored_step(c, seg * W.ckpt).X : W.ck + (size_t)seg * 3 * c->NF;
+}
+
+// Per-block partial sums of the backward sweep's kernels.
+int window_partials(dpd_ctx *c) {
+  Window &W = c->win;
+  const int nb_f = dpd::force_vjp_blocks(c->n_ftiles), nb_g = dpd::adj_prep_blocks(c->NF);
+  const int rc = grow(c, &W.part_f, 3 * (size_t)std::max(nb_f, 1), &W.cap_f, nb_f);
+  return rc ? rc : grow(c, &W.part_g, 3 * (size_t)std::max(nb_g, 1), &W.cap_g, nb_g);
 }
 
 int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
@@ -1623,17 +1678,7 @@ int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
   }
   int dummy = 0;
   int rc = DPD_OK;
-  const size_t want = StoreLayout(c).stride * (size_t)steps;
-  W.full = c->NF > 0 && c->nbricks == 0 && want <= kWindowStore;
-  if (W.full && W.store_cap < want) {
-    if (W.store) dfree(c, W.store);
-    W.store = (char *)dalloc(c, want);
-    W.store_cap = W.store ? want : 0;
-    W.full = W.store != nullptr;
-  }
-  if (!W.full) rc = grow(c, &W.ck, 3 * nf * (size_t)nck, &W.cap_nck, nck);
-  if (!rc && !W.full) rc = grow(c, &W.seg, 3 * nf * (size_t)ckpt, &W.cap_ckpt, ckpt);
-  if (!rc && !W.save) rc = grow(c, &W.save, 3 * nf, &dummy, 1);
+  if (!W.save) rc = grow(c, &W.save, 3 * nf, &dummy, 1);
   if (!rc && !W.wpos) rc = grow(c, &W.wpos, (size_t)(c->NF + c->NW + 1), &dummy, 1);
   if (!rc && !W.adj) rc = grow(c, &W.adj, 11 * nf, &dummy, 1);
   if (!rc && W.cap_nbins < nbins) {
@@ -1655,6 +1700,19 @@ int window_alloc(dpd_ctx *c, int steps, int ckpt, int nbins) {
     if (!W.acc || !W.dk0 || !W.status_save)
       return fail(c, DPD_E_NOMEM, "window buffer allocation failed");
   }
+  if (!rc) rc = window_partials(c);
+  // the store last, so that it takes nothing that a window has to have; one that does not
+  // serve this window goes back
+  const size_t want = StoreLayout(c).stride * (size_t)steps;
+  const bool fits = c->NF > 0 && c->nbricks == 0 && want <= kWindowStore;
+  if (!fits || W.store_cap < want) free_store(W, c);
+  if (!rc && fits && !W.store) {
+    W.store = (char *)dalloc(c, want, true);
+    W.store_cap = W.store ? want : 0;
+  }
+  W.full = W.store != nullptr;
+  if (!rc && !W.full) rc = grow(c, &W.ck, 3 * nf * (size_t)nck, &W.cap_nck, nck);
+  if (!rc && !W.full) rc = grow(c, &W.seg, 3 * nf * (size_t)ckpt, &W.cap_ckpt, ckpt);
   return rc;
 }
 
@@ -1815,8 +1873,7 @@ int backward_impl(dpd_ctx *c, const double *dldp, double *grads, double *dphi) {
   const int64_t NF = c->NF;
   hipStream_t s = c->stream;
   const int nb_f = dpd::force_vjp_blocks(c->n_ftiles), nb_g = dpd::adj_prep_blocks(NF);
-  int rc = grow(c, &W.part_f, 3 * (size_t)std::max(nb_f, 1), &W.cap_f, nb_f);
-  if (!rc) rc = grow(c, &W.part_g, 3 * (size_t)std::max(nb_g, 1), &W.cap_g, nb_g);
+  int rc = window_partials(c);
   if (rc) return rc;
   // keep the context's state; the sweep reuses the step buffers
   const int cur0 = c->cur;
@@ -1988,6 +2045,11 @@ int dpd_replica_count(const dpd_ctx *c) { return c ? c->R : DPD_E_INVAL; }
 int dpd_step(dpd_ctx *c, int64_t nsteps) {
   if (!c) return DPD_E_INVAL;
   if (nsteps < 0) return fail(c, DPD_E_INVAL, "negative step count");
+  if (c->vt2 && !c->captured) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    c->captured = st != hipStreamCaptureStatusNone;
+  }
   if (nsteps > 1 && c->vt2 && !c->persistent && !c->timing)
     return step_run(c, nsteps);
   for (int64_t s = 0; s < nsteps; ++s) {
