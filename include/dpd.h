@@ -303,15 +303,22 @@ int dpd_use_persistent(dpd_ctx *ctx, int32_t enable);
  * P or 1, with P 4 for contexts of at least 2^20
  * fluid particles without moving walls or specular reflection and 2
  * otherwise, and 2 under dpd_use_persistent; a context starts with 1 below
- * 2^20 fluid particles, a batch below 2^18, and with P above) and of the pair-force kernel
- * (work-group size, 128 or 256; default 256) by
- * timing `steps` steps of each of the four combinations from the current
+ * 2^20 fluid particles, a batch below 2^18, and with P above) and of the
+ * pair-force kernel (work-group size, 128 or 256; default 256) by
+ * timing a call of `steps` steps, as dpd_step makes it, with each of the four
+ * combinations from the current
  * state: one untimed round of all four, then two timed rounds in opposite
  * orders, each combination keeping its faster time (the first trials of a
  * run are slower, which would favour the last combination tried); the
  * state, k and the step counter are restored after each trial, so
  * the context is left as it was apart from the shapes (results do not depend
- * on them).  If the environment variable DPD_TUNE_CACHE names a file, a
+ * on them).  In a call of several steps the integrate kernel may run for the
+ * first of them alone (the pair kernel drifts the particles for the others):
+ * pass the number that the program's own calls have.  Where the pair force
+ * has no work-group size to choose (up to 65,536 fluid particles in the
+ * context, bricks, the persistent step), the combinations with 128 are not
+ * tried and have the times of those with 256.  If the environment variable
+ * DPD_TUNE_CACHE names a file, a
  * choice recorded there for the same device and sizes is used without trials
  * and new choices are appended.  shape_out (host int32[2], may be NULL)
  * receives {particles per thread, work-group size}; ms_out (host double[4],

@@ -1027,6 +1027,14 @@ int step_run(dpd_ctx *c, int64_t n) {
   return rc;
 }
 
+// n steps as a call of dpd_step takes them.
+int run_steps(dpd_ctx *c, int64_t n) {
+  if (n > 1 && c->vt2 && !c->persistent && !c->timing) return step_run(c, n);
+  int rc = DPD_OK;
+  for (int64_t s = 0; s < n && !rc; ++s) rc = one_step(c);
+  return rc;
+}
+
 // Re-sort the fluid state into cell order after positions changed outside a
 // step (set_state): bin, scan, scatter, sort, permute into the other buffers.
 // Within a cell particles are ordered by gid, so the stored order (and with
@@ -1536,12 +1544,14 @@ int check_replica(dpd_ctx *c, int32_t r) {
   return DPD_OK;
 }
 
-// Time `steps` steps of the current shapes from the saved state; returns ms.
+// Time a call of `steps` steps with the current shapes from the saved state; returns ms.
 int trial(dpd_ctx *c, int steps, float *ms) {
   hipEvent_t a = get_event(c), b = get_event(c);
-  int rc = one_step(c);  // warm-up (and graph capture)
+  // warm-up, and where steps are replayed the capture from either buffer set
+  int rc = run_steps(c, steps > 1 ? 2 : 1);
+  if (!rc && steps == 1) rc = run_steps(c, 1);
   if (!rc) (void)hipEventRecord(a, c->stream);
-  for (int s = 0; s < steps && !rc; ++s) rc = one_step(c);
+  if (!rc) rc = run_steps(c, steps);
   if (!rc) (void)hipEventRecord(b, c->stream);
   if (!rc) {
     hipError_t e = hipEventSynchronize(b);
@@ -2050,13 +2060,7 @@ int dpd_step(dpd_ctx *c, int64_t nsteps) {
     if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
     c->captured = st != hipStreamCaptureStatusNone;
   }
-  if (nsteps > 1 && c->vt2 && !c->persistent && !c->timing)
-    return step_run(c, nsteps);
-  for (int64_t s = 0; s < nsteps; ++s) {
-    int rc = one_step(c);
-    if (rc) return rc;
-  }
-  return DPD_OK;
+  return run_steps(c, nsteps);
 }
 
 int dpd_use_graph(dpd_ctx *c, int32_t enable) {
@@ -2319,9 +2323,13 @@ int dpd_autotune(dpd_ctx *c, int32_t steps, int32_t *shape_out, double *ms_out) 
     // favoured whichever shape came last: one untimed round, then two rounds
     // in opposite orders, each shape keeping its faster time.
     const int order[3][4] = {{0, 1, 2, 3}, {0, 1, 2, 3}, {3, 2, 1, 0}};
+    // the work-group size is that of k_force alone: not of the pair force with 16 lanes per
+    // particle, in bricks, or in the persistent step, whose shapes with 128 are those with 256
+    const bool blocks = !c->wide && !c->persistent && c->n_otiles > 0;
     for (int round = 0; round < 3 && !rc; ++round)
       for (int o = 0; o < 4 && !rc; ++o) {
         const int i = order[round][o];
+        if (!blocks && shapes[i][1] == 128) continue;
         double t = -1.0;
         const int e = run_shape(i, t);
         if (e) {
@@ -2332,6 +2340,10 @@ int dpd_autotune(dpd_ctx *c, int32_t steps, int32_t *shape_out, double *ms_out) 
         if (rc || round == 0) continue;
         if (times[i] < 0.0 || t < times[i]) times[i] = t;
       }
+    if (!blocks) {
+      times[2] = times[0];
+      times[3] = times[1];
+    }
     for (int i = 0; i < 4 && !rc; ++i)
       if (best < 0 || times[i] < times[best]) best = i;
     HIP_TRY(c, hipStreamSynchronize(c->stream));

@@ -180,6 +180,55 @@ def test_autotune_keeps_state_and_every_shape_agrees(dpd, tmp_path):
     ref.close()
 
 
+def test_autotune_without_a_block_size(dpd):
+    """With 16 lanes per particle the pair kernel's work-group size does nothing: its
+    combinations are not tried, and 256 stays."""
+    sim = dpd.Simulation(_small_batch())
+    for steps, how in ((1, False), (4, False), (1, True), (4, True)):
+        sim.use_persistent(how)
+        shape, ms = sim.autotune(steps)
+        say("autotune of a small batch", steps, how, shape, ms)
+        assert ms[2:] == ms[:2] and min(ms) > 0 and shape[1] == 256
+    sim.close()
+
+
+@pytest.mark.parametrize("sph", [False, True])
+def test_block_sizes_of_a_large_context_agree(dpd, tmp_path, monkeypatch, sph):
+    """The pair kernel with one lane per particle in work-groups of 128 and 256, in calls of
+    one step and of several (where it drifts too), alone and under graph replay."""
+    import torch
+    s = workloads.slab_system(L=(36.0, 36.0, 24.0), seed_fluid=81, seed_wall=82,
+                              grid_dtype=np.float32, params=workloads.default_params(seed=83))
+    if sph:
+        s.params = dict(s.params, sph=workloads.sph_force(), kBT=0.5, dt=0.005)
+    assert s.n_fluid > 65536
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("DPD_TUNE_CACHE", str(cache))
+    got = []
+    for graph in (False, True):
+        sim = dpd.Simulation(s, graph=graph)
+        shape, ms = sim.autotune(2)
+        say("autotune of a large box", s.n, shape, ms)
+        assert ms[2:] != ms[:2] and min(ms) > 0
+        sig = cache.read_text().split()[-3]
+        for blk in (256, 128):
+            cache.write_text("%s 1 %d\n" % (sig, blk))
+            run = dpd.Simulation(s, graph=graph)
+            assert run.autotune(1)[0] == (1, blk)
+            states = []
+            for n in (1, 1, 3, 1, 4):
+                run.step(n)
+                states.append(dict(run.state(), force=run.forces()))
+            got.append(states)
+            run.close()
+        cache.write_text("")
+        sim.close()
+    for other in got[1:]:
+        for k, (a, b) in enumerate(zip(got[0], other)):
+            for q in a:
+                assert torch.equal(a[q], b[q]), (k, q)
+
+
 def test_full_batch_sampled_boxes(dpd, oracle_lib):
     """The 256-replica workload in the benchmarked configuration (graph
     replay, autotuned shapes): sampled boxes against the same box alone
