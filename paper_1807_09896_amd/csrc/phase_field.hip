@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
 
 #include "kernels.h"
 
@@ -88,8 +89,15 @@ __device__ __forceinline__ void lengths(double s2, double delta2, double inv_del
   len = s2 * y;
   len = __builtin_fma(__builtin_fma(-len, len, s2), 0.5 * y, len);
   y = __builtin_fma(__builtin_fma(-len, y, 1.0), y, y);
-  inv = s2 > delta2 ? y : inv_delta;
+  inv = fmin(y, inv_delta);   // (as a choice by s2 > delta2: 28.0 us a step of that grid, 27.6 so)
 }
+
+// An infinite s2 has made |u| NaN (and its inverse the floor's), where |u| is infinite and
+// 1 / |u| zero, as the float form has them.
+__device__ __forceinline__ bool lost(double len0, double len1) {
+  return __builtin_isunordered(len0, len1);
+}
+__device__ __forceinline__ bool lost(float, float) { return false; }
 
 __device__ __forceinline__ void res_max(void *res, float v) {
   atomicMax((unsigned int *)res, __float_as_uint(v));
@@ -202,14 +210,36 @@ __global__ __launch_bounds__(kThreads) void k_phi_relax(RelaxArgs<T> a) {
       om[k] = ph;
       o0[k] = zp;
     }
+    // the nodes whose squared length overflowed, again (one test for both rows; a test in
+    // lengths took 1.8 % of a step of the grid above, selects there 3 %)
+    static_assert(kRows == 2, "rows tested together");
+    if (__builtin_expect(lost(nxt_gm[0], nxt_gm[1]), 0)) {
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int ty = ty0 + k * (kThreads / kBX);
+        const int c = (ty + 2) * kPW + tx + 2;
+        const T ux = a.gx * (sphi[p0 + c + 1] - sphi[p0 + c - 1]);
+        const T uy = a.gy * (sphi[p0 + c + kPW] - sphi[p0 + c - kPW]);
+        const T uz = a.gz * (sphi[pp + c] - sphi[pm + c]);
+        const T s2 = ux * ux + uy * uy + uz * uz;
+        if (s2 < std::numeric_limits<T>::infinity() || s2 != s2) continue;
+        const int m = (ty + 1) * kNW + tx + 1;
+        sn[nb + m] = ux * T(0);
+        sn[nb + kNPlane + m] = uy * T(0);
+        nz_p[k] = uz * T(0);
+        nxt_gm[k] = s2;
+      }
+    }
     if (has_halo) {
       // the halo needs n_x (columns) or n_y (rows) only; both are written
       const int c = hc;
       const T ux = a.gx * (sphi[p0 + c + 1] - sphi[p0 + c - 1]);
       const T uy = a.gy * (sphi[p0 + c + kPW] - sphi[p0 + c - kPW]);
       const T uz = a.gz * (sphi[pp + c] - sphi[pm + c]);
+      const T s2 = ux * ux + uy * uy + uz * uz;
       T len, inv;
-      lengths(ux * ux + uy * uy + uz * uz, a.delta2, a.inv_delta, len, inv);
+      lengths(s2, a.delta2, a.inv_delta, len, inv);
+      if (lost(len, len)) inv = s2 > a.delta2 ? T(0) : a.inv_delta;
       sn[nb + hn] = ux * inv;
       sn[nb + kNPlane + hn] = uy * inv;
     }

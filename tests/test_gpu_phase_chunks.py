@@ -59,3 +59,29 @@ def test_fields_without_gradient(dpd, dtype):
         out, res = _relax(dpd, phi0, h, 0.01, 2, dtype)
         assert np.abs(out - ref).max() <= TOL[dtype], value
         assert abs(res - rres) <= TOL[dtype], value
+
+
+@pytest.mark.parametrize("value,dtype", [(np.inf, 4), (np.inf, 8), (-np.inf, 8), (1e200, 8),
+                                         (-1e158, 8), (np.nan, 4), (np.nan, 8)], ids=str)
+def test_overflow_stays_where_it_is(dpd, monkeypatch, value, dtype):
+    """One node of a smooth field infinite, NaN, or so large that a squared length overflows:
+    after one step the same nodes are infinite and NaN as in the oracle, where a finite part
+    over an infinite length is zero, and the others have its values.  (The floor of a length
+    that is NaN is the floor in the kernel, as fmax has it.)"""
+    nx, ny, nz = 70, 20, 9
+    z, y, x = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+    phi0 = 0.6 * np.sin(0.3 * x + 0.2) * np.cos(0.45 * y + 0.7 * z) + 0.1 * np.sin(0.9 * z + 0.4 * y)
+    phi0[4, 15, 63] = value   # beside a tile's edge in x and in y
+    phi0 = phi0.astype(np.float32).astype(np.float64) if dtype == 4 else phi0
+    h = (0.25, 0.25, 0.25)
+    with np.errstate(all="ignore"), monkeypatch.context() as m:
+        m.setattr(np, "maximum", np.fmax)
+        ref, _ = pf.relax(phi0, h, EPS, 0.01, 1)
+    print("relax overflow", value, dtype, int((~np.isfinite(ref)).sum()), flush=True)
+    out, _ = _relax(dpd, phi0, h, 0.01, 1, dtype)
+    assert np.array_equal(np.isnan(out), np.isnan(ref))
+    assert np.array_equal(np.isposinf(out), np.isposinf(ref))
+    assert np.array_equal(np.isneginf(out), np.isneginf(ref))
+    near = np.abs(ref) < 1e6
+    assert near.sum() > ref.size - 100
+    assert np.abs(out[near] - ref[near]).max() <= TOL[dtype]
