@@ -8,6 +8,13 @@ def require_gpu():
         raise RuntimeError("GPU tests need a gfx950 device")
 
 
+def replay(sim, n):
+    """n calls of one step: with use_graph each replays the captured step, where a call of
+    several steps launches directly."""
+    for _ in range(n):
+        sim.step(1)
+
+
 def force_scale(f_fluid):
     """F_scale: RMS over fluid particles of |f| (the force-norm scale)."""
     return float(np.sqrt((np.asarray(f_fluid, np.float64) ** 2).sum(axis=1).mean()))

@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_helpers import require_gpu, sorted_pairs
+from gpu_helpers import replay, require_gpu, sorted_pairs
 from test_gpu_parity import _one_step_compare, _stress_system
 
 pytestmark = pytest.mark.gpu
@@ -122,7 +122,7 @@ def test_graph_replay_equals_direct_launches(dpd):
     direct = dpd.Simulation(boxes)
     graph = dpd.Simulation(boxes, graph=True)
     direct.step(25)
-    graph.step(25)
+    replay(graph, 25)
     assert graph.counters()["k"] == 25
     for r in range(len(boxes)):
         _assert_same(_snap(graph, r), _snap(direct, r), ("graph", r))
@@ -130,7 +130,7 @@ def test_graph_replay_equals_direct_launches(dpd):
     st = _snap(direct, 3)
     for sim in (direct, graph):
         sim.set_state(st["pos"], st["vel"], st["force"], 7, r=3)
-        sim.step(6)
+        replay(sim, 6)
     for r in range(len(boxes)):
         _assert_same(_snap(graph, r), _snap(direct, r), ("graph after set_state", r))
     assert graph.counters()["k"] == 13

@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import workloads
+from gpu_helpers import replay as replay_steps
 from gpu_helpers import require_gpu, sorted_pairs
 
 pytestmark = pytest.mark.gpu
@@ -167,7 +168,7 @@ def test_small_context_graph_replays(dpd):
     direct, replay = dpd.Simulation(s), dpd.Simulation(s, graph=True)
     for k in range(6):
         direct.step(3)
-        replay.step(3)
+        replay_steps(replay, 3)
         a, b = direct.state(), replay.state()
         for q in a:
             assert torch.equal(a[q], b[q]), (k, q)

@@ -15,7 +15,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_helpers import require_gpu
+from gpu_helpers import replay, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -66,7 +66,7 @@ def _same(a, b, what):
 def test_restart_is_bit_identical(dpd):
     boxes = _boxes()
     a = dpd.Simulation(boxes, graph=True)
-    a.step(23)
+    replay(a, 23)
     blob = a.snapshot()
     say("snapshot bytes", blob.nbytes)
     a.step(17)
@@ -75,11 +75,11 @@ def test_restart_is_bit_identical(dpd):
     b = dpd.Simulation(boxes, graph=True)
     b.step(3)                       # some other state, to be overwritten
     b.restore(blob)
-    b.step(17)
+    replay(b, 17)
     _same(_state(b, 3), ref, "fresh context")
     b.close()
     a.restore(blob)
-    a.step(17)
+    replay(a, 17)
     _same(_state(a, 3), ref, "rewound")
     a.close()
 

@@ -17,7 +17,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_helpers import by_gid, force_scale, require_gpu
+from gpu_helpers import by_gid, force_scale, replay, require_gpu
 from test_gpu_parity import FORCE_TOL, _one_step_compare, _small_curved
 
 pytestmark = pytest.mark.gpu
@@ -107,7 +107,7 @@ def test_batch_mixing_forces_and_graph(dpd):
         _same(_snap(batch, r), _snap(alone, 0), ("batch vs alone", r))
         alone.close()
     graph = dpd.Simulation(boxes, graph=True)
-    graph.step(15)
+    replay(graph, 15)
     for r in range(3):
         _same(_snap(graph, r), _snap(batch, r), ("graph", r))
     graph.close()
@@ -122,9 +122,9 @@ def test_set_params_switches_the_force(dpd):
     runs = []
     for graph in (True, False):
         sim = dpd.Simulation(s, graph=graph)
-        sim.step(6)
+        replay(sim, 6)
         sim.set_params(on)
-        sim.step(6)
+        replay(sim, 6)
         runs.append(_snap(sim, 0))
         sim.close()
     _same(runs[0], runs[1], "graph vs direct")

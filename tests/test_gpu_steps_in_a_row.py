@@ -1,10 +1,11 @@
 """Steps that follow one another in a call (the pair kernel goes on to the next drift)
-against the same steps one call each, bit for bit."""
+against the same steps one call each, bit for bit, and captured steps replayed between
+such calls, which exchange buffers that the captured steps hold."""
 import numpy as np
 import pytest
 
 import workloads
-from gpu_helpers import require_gpu
+from gpu_helpers import replay, require_gpu
 from test_gpu_small_contexts import _edge_box, _sph
 from test_gpu_walls import _aimed_couette
 
@@ -63,6 +64,13 @@ CASES = {
                                                       seed=68 + r, specular=r == 1)
                              for r in range(3)] + [_slab(np.float32, 72)],
     "specular": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=0.0, seed=36, specular=True)],
+    # and with float64 grids
+    "large_moving64": lambda: [workloads.couette_system(L=(41.0, 40.0, 17.5), U=4.0, seed=73,
+                                                        specular=True, grid_dtype=np.float64)],
+    "moving64": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=4.0, seed=74,
+                                                  grid_dtype=np.float64)],
+    "specular64": lambda: [workloads.couette_system(L=(8.0, 6.0, 7.0), U=0.0, seed=75,
+                                                    specular=True, grid_dtype=np.float64)],
 }
 
 
@@ -104,3 +112,36 @@ def test_same_bits(dpd, name, graph):
     same("timed")
     one.close()
     row.close()
+
+
+@pytest.mark.parametrize("name", ["one_block", "float32", "batch12", "large", "moving",
+                                  "moving_batch", "large_moving"])
+def test_replays_between_rows(dpd, name):
+    """Steps captured from either buffer set and replayed before and after calls of several
+    steps, which exchange the predictions and counts once or twice (and the buffer sets), and
+    before and after the persistent step, against direct launches of single steps."""
+    import torch
+    boxes = CASES[name]()
+    print("replays between rows", name, [s.n for s in boxes], flush=True)
+    one, both = dpd.Simulation(boxes), dpd.Simulation(boxes, graph=True)
+    moving = "moving" in name
+    for turn, row in enumerate((0, 2, 3, 2, 2, 4, 3, 5, 0)):
+        if row:
+            both.step(row)
+            replay(one, row)
+        if turn == 5 and not moving:   # the persistent step's arguments hold one of each pair
+            both.use_persistent(True)
+            replay(both, 2)
+            both.step(3)
+            both.use_persistent(False)
+            replay(one, 5)
+        replay(both, 3)
+        replay(one, 3)
+        assert one.counters() == both.counters(), (turn, row)
+        for r in range(len(boxes)):
+            a, b = one.state(r), both.state(r)
+            for k in a:
+                assert torch.equal(a[k], b[k]), (turn, row, r, k)
+            assert torch.equal(one.forces(r), both.forces(r)), (turn, row, r)
+    one.close()
+    both.close()

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_helpers import require_gpu
+from gpu_helpers import replay, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -35,7 +35,8 @@ def test_steps_on_a_side_stream(dpd):
     side = torch.cuda.Stream()
     for graph in (False, True):
         sim = dpd.Simulation(s, stream=side, graph=graph)
-        sim.step(30)
+        sim.step(17)
+        replay(sim, 13)
         got = _snap(sim)
         for k in ("pos", "vel", "events", "cell_of", "force"):
             assert np.array_equal(got[k], want[k]), (graph, k)

@@ -15,7 +15,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_helpers import require_gpu
+from gpu_helpers import replay, require_gpu
 from test_gpu_parity import _one_step_compare
 
 pytestmark = pytest.mark.gpu
@@ -167,7 +167,7 @@ def test_moving_walls_batch_graph_and_autotune(dpd, tmp_path, monkeypatch):
         _same(_snap(batch, r), _snap(alone, 0), ("batch vs alone", r))
         alone.close()
     graph = dpd.Simulation(boxes, graph=True)
-    graph.step(12)
+    replay(graph, 12)
     for r in range(3):
         _same(_snap(graph, r), _snap(batch, r), ("graph", r))
     # the autotuner's trials leave the state (walls included) as it was
@@ -176,7 +176,7 @@ def test_moving_walls_batch_graph_and_autotune(dpd, tmp_path, monkeypatch):
     graph.autotune(2)
     for r in range(3):
         _same(_snap(graph, r), before[r], ("autotune", r))
-    graph.step(5)
+    replay(graph, 5)
     batch.step(5)
     for r in range(3):
         _same(_snap(graph, r), _snap(batch, r), ("after autotune", r))
