@@ -237,8 +237,10 @@ int dpd_counters(dpd_ctx *ctx, int64_t *out);
  * the wall part of the merged cell runs; "pair_codes" writes the coarse
  * position codes of the merged runs that the pair kernel's candidate
  * pre-test reads, which small contexts do without; where every box is small,
- * one launch named "sort_cells" builds the whole cell list; "step_persistent" is the one launch of a step under
- * dpd_use_persistent, which then replaces the six step kernels).
+ * one launch named "sort_cells" builds the whole cell list; "step_persistent"
+ * is the one launch of a step under dpd_use_persistent, which then replaces
+ * the six step kernels).  While times are recorded, a call of several steps
+ * makes them one by one, so that every drift is a launch of its own.
  * Synchronises. */
 #define DPD_NUM_KERNELS 9
 int dpd_kernel_times(dpd_ctx *ctx, int32_t enable, double *out_ms, int64_t *out_launches);
@@ -276,12 +278,12 @@ int dpd_replica_profile(dpd_ctx *ctx, int32_t r, int32_t axis, int32_t nbins, do
 
 /* enable != 0: dpd_step replays one captured HIP graph per step (the launch
  * sequence of a step, captured on first use on a private stream and replayed
- * on the context stream; calls of several steps launch directly where the
- * pair kernel goes on to the next step's drift, which is faster; the random-number index k lives on the device
- * and is
- * advanced inside the graph, so replays draw fresh numbers).  Results are
- * bit-identical to direct launches.  Per-kernel timing, when enabled, uses
- * direct launches.  A captured graph is dropped by set_state and autotune. */
+ * on the context stream; the random-number index k lives on the device and is
+ * advanced inside the graph, so replays draw fresh numbers).  Calls of
+ * several steps launch directly where the pair kernel goes on to the next
+ * step's drift, which is faster.  Results are bit-identical to direct
+ * launches.  Per-kernel timing, when enabled, uses direct launches.  A
+ * captured graph is dropped by set_state and autotune. */
 int dpd_use_graph(dpd_ctx *ctx, int32_t enable);
 
 /* enable = 1: run each step as one persistent launch (plus a one-block
@@ -292,38 +294,36 @@ int dpd_use_graph(dpd_ctx *ctx, int32_t enable);
  * for the items of the previous phase of box r through per-box arrival
  * counters (each wait bounded; a wait that reaches its bound is reported as
  * DPD_E_DEVICE at the next synchronising call).  Results are bit-identical to
- * the per-phase launches, and it combines with dpd_use_graph.  The
- * persistent launch integrates at most 2 particles per thread, so a context
- * at 4 is set to 2 (see dpd_autotune).  DPD_E_INVAL for
+ * the per-phase launches, and it combines with dpd_use_graph.  A call with
+ * enable = 1 sets the context to 2 particles per thread, the most that the
+ * persistent launch integrates (see dpd_autotune).  DPD_E_INVAL for
  * contexts with moving walls or boxes on the LDS-staged brick pair kernel;
  * enable = 0 returns to the per-phase launches and keeps the shapes. */
 int dpd_use_persistent(dpd_ctx *ctx, int32_t enable);
 
 /* Choose the launch shapes of the integrate kernel (particles per thread:
- * P or 1, with P 4 for contexts of at least 2^20
- * fluid particles without moving walls or specular reflection and 2
- * otherwise, and 2 under dpd_use_persistent; a context starts with 1 below
- * 2^20 fluid particles, a batch below 2^18, and with P above) and of the
- * pair-force kernel (work-group size, 128 or 256; default 256) by
- * timing a call of `steps` steps, as dpd_step makes it, with each of the four
- * combinations from the current
- * state: one untimed round of all four, then two timed rounds in opposite
- * orders, each combination keeping its faster time (the first trials of a
- * run are slower, which would favour the last combination tried); the
- * state, k and the step counter are restored after each trial, so
- * the context is left as it was apart from the shapes (results do not depend
- * on them).  In a call of several steps the integrate kernel may run for the
- * first of them alone (the pair kernel drifts the particles for the others):
- * pass the number that the program's own calls have.  Where the pair force
- * has no work-group size to choose (up to 65,536 fluid particles in the
- * context, bricks, the persistent step), the combinations with 128 are not
- * tried and have the times of those with 256.  If the environment variable
- * DPD_TUNE_CACHE names a file, a
- * choice recorded there for the same device and sizes is used without trials
- * and new choices are appended.  shape_out (host int32[2], may be NULL)
- * receives {particles per thread, work-group size}; ms_out (host double[4],
- * may be NULL) the ms per step of {P/256, 1/256, P/128, 1/128}, -1 when not
- * timed.  Synchronises. */
+ * P or 1, with P 4 for contexts of at least 2^20 fluid particles without
+ * moving walls or specular reflection and 2 otherwise, and 2 under
+ * dpd_use_persistent; a context starts with 1 below 2^20 fluid particles, a
+ * batch below 2^18, and with P above) and of the pair-force kernel
+ * (work-group size, 128 or 256; default 256) by timing a call of `steps`
+ * steps, as dpd_step makes it, with each of the four combinations from the
+ * current state: one untimed round of all four, then two timed rounds in
+ * opposite orders, each combination keeping its faster time (the first trials
+ * of a run are slower, which would favour the last combination tried); the
+ * state, k and the step counter are restored after each trial, so the context
+ * is left as it was apart from the shapes (results do not depend on them).
+ * In a call of several steps the integrate kernel may run for the first of
+ * them alone (the pair kernel drifts the particles for the others): pass the
+ * number that the program's own calls have.  Where the pair force has no
+ * work-group size to choose (up to 65,536 fluid particles in the context,
+ * bricks, the persistent step), the combinations with 128 are not tried and
+ * have the times of those with 256.  If the environment variable
+ * DPD_TUNE_CACHE names a file, a choice recorded there for the same device
+ * and sizes is used without trials and new choices are appended.  shape_out
+ * (host int32[2], may be NULL) receives {particles per thread, work-group
+ * size}; ms_out (host double[4], may be NULL) the ms per step of {P/256,
+ * 1/256, P/128, 1/128}, -1 when not timed.  Synchronises. */
 int dpd_autotune(dpd_ctx *ctx, int32_t steps, int32_t *shape_out, double *ms_out);
 
 /* Replace the parameters of box r (every field of dpd_params; rc and flags
@@ -363,14 +363,14 @@ int dpd_set_phi(dpd_ctx *ctx, int32_t r, const void *data, int32_t on_device);
  * nbins float64) by the hand-written adjoint of every step of the window
  * (pair force of Eq. 3-10, the Groot-Warren update and the bounce-back of
  * Eq. 16-17 with the recorded events held fixed, and the starting force),
- * from the steps kept or recomputing each ckpt-step segment from its checkpoint.
- * The bins, pair
- * sets and events are those of the forward window.  grads (host, 6 float64)
- * receives dL/d{a_ff, a_fw, gamma, g_x, g_y, g_z} (gamma through both the
- * dissipative amplitude and sigma = sqrt(2 gamma kBT); the sigma path is
- * omitted where sigma = 0); dL_dphi (device, grid nodes float64 in the
- * grid's layout, may be NULL) receives dL/d(phi node values), nonzero only
- * at the nodes of cubes where a bounce-back of code 1 started or ended.
+ * from the steps kept or recomputing each ckpt-step segment from its
+ * checkpoint.  The bins, pair sets and events are those of the forward
+ * window.  grads (host, 6 float64) receives dL/d{a_ff, a_fw, gamma, g_x, g_y,
+ * g_z} (gamma through both the dissipative amplitude and sigma = sqrt(2 gamma
+ * kBT); the sigma path is omitted where sigma = 0); dL_dphi (device, grid
+ * nodes float64 in the grid's layout, may be NULL) receives dL/d(phi node
+ * values), nonzero only at the nodes of cubes where a bounce-back of code 1
+ * started or ended.
  * The context's state, k and counters are unchanged.  DPD_E_STATE without a
  * recorded window or after dpd_set_params / dpd_set_phi / dpd_set_state. */
 int dpd_window_forward(dpd_ctx *ctx, int32_t steps, int32_t ckpt, int32_t axis,

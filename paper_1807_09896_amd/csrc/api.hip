@@ -856,7 +856,6 @@ int force_pass(dpd_ctx *c, hipStream_t s, int init, const dpd::NextStep *next = 
   return DPD_OK;
 }
 
-// The launches of one step on stream s (swaps cur).
 // The walls of every box binned at their positions into wcell_tmp, wrank and wcount, with
 // copies in wtmp and wvtmp; with move, those of every box whose solid moves first
 // advance by dt v.
@@ -947,6 +946,7 @@ int drift(dpd_ctx *c, hipStream_t s) {
   return DPD_OK;
 }
 
+// The launches of one step on stream s (swaps cur).
 int enqueue_step(dpd_ctx *c, hipStream_t s) {
   const int a = c->cur;
   if (c->persistent) {

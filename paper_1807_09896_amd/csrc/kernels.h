@@ -9,7 +9,8 @@
 
 namespace dpd {
 
-// Number of scan blocks for n cells (each block scans kScanChunk counts).
+// Cell scan: each thread of a block takes kScanItems cells, or kScanFew (scan_items); the
+// persistent step's scan always kScanItems, kScanChunk a block.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanChunk = kScanThreads * kScanItems;

@@ -346,10 +346,12 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(
 
 // Moving walls: the walls' counts scanned into wstart in the same pass.
 //
-// The five launches that list fluid and moving walls together (k_scan_reduce, this
-// one, k_scatter_both, k_sort_both, k_permute) take the place of nine of 5 to 8 us
-// each, most of it the launch: a step of 746,000 fluid and 304,000 wall particles
-// 178 to 167 us.
+// After k_wall_move_bin (one launch per box with walls) five launches list fluid and
+// moving walls together: k_scan_reduce, this one, k_scatter_both, k_sort_both and
+// k_permute, and k_quant_runs writes the codes of large contexts.  The five take the
+// place of nine of 5 to 8 us each, most of it the launch: a step of 746,000 fluid and
+// 304,000 wall particles 178 to 167 us.  (With 16 cells a thread, from 2^20 cells on, the
+// 64-bit sums take this kernel to 238 VGPRs, one wavefront per SIMD.)
 template <int ITEMS>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down_both(
     int64_t n, int32_t *__restrict__ count, int32_t *__restrict__ start,
@@ -1578,7 +1580,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(6))) void k_
 // T (the grid's type, or void): the particle goes on to the drift and the binning of
 // the next step (integrate_one, as k_integrate), so that steps that follow one another in a
 // call are two launches instead of three: 19.6 to 16.2 us a step at 2,400 particles,
-// 24.1 to 21.9 at 16,500.  Five wavefronts per SIMD (96 VGPRs): with four the blocks of
+// 24.1 to 21.9 at 16,500.  Five wavefronts per SIMD (96 VGPRs, of which the drifting
+// instances spill one to four, 8 to 20 B of scratch a lane): with four the blocks of
 // 16,500 particles took a second round, 24.4 us.
 // ---------------------------------------------------------------------------
 template <bool INIT, bool SPH, typename T, bool REFLECT>
