@@ -623,6 +623,10 @@ int build_persistent(dpd_ctx *c) {
   }
   for (int r = 0; r < R; ++r) {
     const Replica &p = c->rep[r];
+    // an empty box has nothing to sort; its sort items would find no scatter item to wait
+    // for, and read run starts that the scan may not have written yet (where the context's
+    // lists come from k_cells_box, nothing else has)
+    if (p.n == 0) continue;
     for (int64_t a = p.co; a < p.co + p.ncell; a += kSortItem)
       add(dpd::kPhSort, r, a, std::min(a + kSortItem, p.co + p.ncell));
   }

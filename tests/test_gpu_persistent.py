@@ -140,3 +140,35 @@ def test_refused_where_not_served(dpd, monkeypatch):
     with pytest.raises(DPDError):
         sim.use_persistent(True)
     sim.close()
+
+
+def _part(s, keep):
+    """The system with the particles `keep` alone."""
+    import copy
+    s = copy.copy(s)
+    s.pos, s.vel, s.type = s.pos[keep], s.vel[keep], s.type[keep]
+    s.gid = np.random.default_rng(5).permutation(len(s.pos)).astype(np.uint32)
+    return s
+
+
+@pytest.mark.parametrize("alone", [False, True])
+def test_empty_boxes(dpd, alone):
+    """Boxes without particles have phases without work, whose successors wait for nothing:
+    alone, and first, last and between boxes of walls alone, one particle and both."""
+    s = workloads.tiny_slab_system(seed=21)
+    none = _part(s, np.zeros(s.n, bool))
+    walls, one = _part(s, s.type != 0), _part(s, np.flatnonzero(s.type == 0)[:1])
+    boxes = [none] if alone else [none, s, walls, none, one, none]
+    say("persistent with empty boxes", [b.n for b in boxes])
+    ref, per = dpd.Simulation(boxes), dpd.Simulation(boxes)
+    per.use_persistent(True)
+    for n in (1, 4):
+        ref.step(n)
+        per.step(n)
+        per.sync()
+        for r, b in enumerate(boxes):
+            if b.n:
+                _same(_snap(per, r), _snap(ref, r), (n, r))
+    assert ref.counters() == per.counters()
+    ref.close()
+    per.close()
